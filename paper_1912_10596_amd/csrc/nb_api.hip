@@ -29,7 +29,7 @@ template <int BPT>
 __global__ void k_adjoint2(AdjArgs a);
 template <int NF, bool TLDS>
 __global__ void k_adaptive(StepArgs a);
-__global__ void k_zero_sync(unsigned int* sync, int keep_status, const unsigned* cancel);
+__global__ void k_zero_sync(unsigned int* sync, int keep_status, const unsigned* cancel, int words);
 __global__ void k_zero_u64(unsigned long long* p, long long n);
 __global__ void k_set_step(long long* step_ctl, long long step);
 __global__ void k_status_out(const unsigned int* sync, const long long* step_ctl, long long* host);
@@ -505,7 +505,7 @@ extern "C" int nb_pee_offsets(const nb_model* m, int64_t* off) {
 
 static size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
-// Workspace: state planes | tables | sync and tagged reduction words | step counter |
+// Workspace: state planes | tables | barrier and reduction words | step counter |
 // (batches) model descriptors | wave row ranges | moment accumulators | (adjoint) its
 // regions | (adaptive) the second state buffer.
 struct Layout {
@@ -654,14 +654,18 @@ static int set_device_step(nb_model* m, long long step) {
   return NB_OK;
 }
 
-// Clear the barrier words, optionally keeping the status word (a kernel: capturable).
-static int zero_sync(nb_model* m, int keep) {
+// Clear the first `words` barrier words (the part the next launch uses), optionally keeping
+// the status word (a kernel: capturable).
+static int clear_sync(nb_model* m, int keep, const unsigned* cancel, int words) {
   unsigned int* sync = sync_words(m);
-  const unsigned* cancel = m->cancel_dev;
-  void* zargs[] = {&sync, &keep, &cancel};
-  NB_HIP(hipLaunchKernel((const void*)&k_zero_sync, dim3(256), dim3(256), zargs, 0, m->stream));
+  void* zargs[] = {&sync, &keep, &cancel, &words};
+  NB_HIP(hipLaunchKernel((const void*)&k_zero_sync, dim3((unsigned)((words + 1023) / 1024)), dim3(256), zargs, 0,
+                         m->stream));
   return NB_OK;
 }
+static int zero_sync(nb_model* m, int keep, int words) { return clear_sync(m, keep, m->cancel_dev, words); }
+// Words the fixed-step launches of a model use.
+static int step_sync_words(const nb_model* m) { return m->batch ? kSyncArriveEnd : kSyncRedEnd; }
 
 extern "C" int nb_reset(nb_model* m) {
   if (!m) return fail(NB_EINVAL, "model is NULL");
@@ -856,11 +860,8 @@ extern "C" int nb_bind(nb_model* m, void* dev_ws, size_t bytes, void* hip_stream
     int rc = upload_partition(m);
     if (rc) return rc;
   }
-  unsigned int* sync = (unsigned int*)(m->ws + m->off_sync);
-  int keep = 0;
-  const unsigned* no_cancel = nullptr;
-  void* zargs[] = {&sync, &keep, &no_cancel};
-  NB_HIP(hipLaunchKernel((const void*)&k_zero_sync, dim3(256), dim3(256), zargs, 0, m->stream));
+  const int rc = clear_sync(m, 0, nullptr, kSyncWords);
+  if (rc) return rc;
   NB_HIP(hipStreamSynchronize(m->stream));
   return nb_reset(m);
 }
@@ -878,10 +879,8 @@ static int check_status(nb_model* m) {
   const unsigned st = (unsigned)(m->pinned[0] & 0xffffffffll);
   m->step = m->pinned[1];
   if (st) {
-    int keep = 0;
-    const unsigned* no_cancel = nullptr;
-    void* zargs[] = {&sync, &keep, &no_cancel};
-    NB_HIP(hipLaunchKernel((const void*)&k_zero_sync, dim3(256), dim3(256), zargs, 0, m->stream));
+    const int rc = clear_sync(m, 0, nullptr, kSyncWords);
+    if (rc) return rc;
     NB_HIP(hipStreamSynchronize(m->stream));
     if (st & 4u) return fail(NB_ETIMEOUT, "cancelled by the host (nb_cancel)");
     if (st & 2u) return fail(NB_ETIMEOUT, "grid barrier time limit exceeded");
@@ -909,7 +908,7 @@ static long long launch_chunk(const nb_model* m) {
 // Enqueue one stepping launch of k steps (from the device step counter) on the stream.
 static int enqueue_advance(nb_model* m, long long k) {
   unsigned int* sync = sync_words(m);
-  int rc0 = zero_sync(m, 1);
+  int rc0 = zero_sync(m, 1, step_sync_words(m));
   if (rc0) return rc0;
   const unsigned long long timeout = m->ticks_per_s * 20ull;
   if (m->batch) {
@@ -990,7 +989,7 @@ static int enqueue_advance(nb_model* m, long long k) {
   a.win_hi = s.fp32_from;
   int rc = launch(advance_kernel(m, m->bs), advance_dyn_lds(m));
   if (rc) return rc;
-  rc = zero_sync(m, 1);
+  rc = zero_sync(m, 1, kSyncRedEnd);
   if (rc) return rc;
   a.win_lo = s.fp32_from;
   a.win_hi = m->p.n_steps;
@@ -1077,7 +1076,7 @@ extern "C" int nb_step_static(nb_model* m, int64_t n) {
   m->sync_static = (unsigned int*)s;
   m->acc_static = s + kStaticAccOff;
   // the previous call on this device left its epochs (and maybe a status) in the array
-  rc = zero_sync(m, 0);
+  rc = zero_sync(m, 0, step_sync_words(m));
   if (!rc) rc = nb_step(m, n);
   m->sync_static = nullptr;
   m->acc_static = nullptr;
@@ -1105,7 +1104,7 @@ extern "C" int nb_run_adaptive(nb_model* m, double tol, double h_max_km, int64_t
   std::memcpy(&init[kCtlH], &h0, sizeof(double));
   long long* ctl = (long long*)(m->ws + m->off_ctl);
   NB_HIP(hipMemcpyAsync(ctl, init, sizeof(init), hipMemcpyHostToDevice, m->stream));
-  int rc = zero_sync(m, 1);
+  int rc = zero_sync(m, 1, kSyncErrEnd);
   if (rc) return rc;
   StepArgs a{};
   a.X = m->ws + m->off_X;
@@ -1697,7 +1696,7 @@ extern "C" int nb_adjoint(nb_model* m, const double* dev_dl_dpee, double* grad_o
   m->jhist = nullptr;
   // reverse pass
   unsigned int* sync = (unsigned int*)(m->ws + m->off_sync);
-  int rc0 = zero_sync(m, 1);
+  int rc0 = zero_sync(m, 1, kSyncWords);
   if (rc0) return rc0;
   const Sub& s = m->subs[0];
   AdjArgs a{};

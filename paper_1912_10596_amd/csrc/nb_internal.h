@@ -9,26 +9,37 @@ constexpr int kMaxBlocks = 2048;  // upper bound on blocks of one stepping launc
                                   // hold at most 4 blocks of 512 threads each)
 
 // Offsets (in 32-bit words) of the synchronisation words.  Every word that more than one
-// block writes or polls sits on a 128-byte line of its own: the abort and status words,
-// kFlagCopies copies of the release flag (block b polls copy b % kFlagCopies) and one
-// arrival word per block.
+// block writes or polls sits on a 128-byte line of its own or in one of the reduction
+// regions below.
 constexpr int kLineWords = 32;
 constexpr int kFlagCopies = 8;
 constexpr int kSyncAbort = 1 * kLineWords;   // set when any block gives up waiting
 constexpr int kSyncStatus = 2 * kLineWords;  // bit 0: fixed-point range error, bit 1: barrier timeout,
                                              // bit 2: cancelled by the host, bit 3: renormalisation
                                              // factor far from 1
-constexpr int kSyncFlag = 4 * kLineWords;    // [kFlagCopies] lines: epoch + 1 of the last release
+// Moment reductions of the stepping kernels: kRedCopies copies of kRedStride 64-bit counted
+// accumulators, then (in two regions, even and odd barrier epochs) as many published sums.
+// Block b adds to copy b % kRedCopies (consecutive blocks go to the 8 dies in turn, so a
+// copy is added to from one die); a copy's words start on a line of their own.
+constexpr int kRedCopies = 8, kRedStride = 64;
+constexpr int kSyncRed = 4 * kLineWords;
+constexpr int kSyncPub = kSyncRed + 2 * kRedCopies * kRedStride;
+constexpr int kSyncRedEnd = kSyncPub + 2 * 2 * kRedCopies * kRedStride;
+// Adaptive runs: one tagged 64-bit error word per block, in two regions (even, odd epochs).
+constexpr int kSyncErr = kSyncRedEnd;
+constexpr int kSyncErrEnd = kSyncErr + 2 * 2 * kMaxBlocks;
+// Batches: kFlagCopies copies of the release flag (block b polls copy b % kFlagCopies), each
+// the epoch + 1 of the last release, and one arrival line per block.
+constexpr int kSyncFlag = kSyncErrEnd;
 constexpr int kSyncArrive = kSyncFlag + kFlagCopies * kLineWords;  // [kMaxBlocks] lines
-// Tagged 64-bit words of the moment reductions (every word carries the barrier epoch it
-// belongs to, so no separate arrival or release word is needed): kFlagCopies copies of
-// reduced moments (the adjoint's sums; block b reads copy b % kFlagCopies), kTagLines lines
-// each; then block partials, one slot of kTagLines lines per block, in two regions used by
-// the stepping kernels at even and odd epochs (the adjoint uses the first).
+constexpr int kSyncArriveEnd = kSyncArrive + kMaxBlocks * kLineWords;
+// The adjoint's sums: tagged 64-bit words (every word carries the barrier epoch it belongs
+// to), kFlagCopies copies of the results (block b reads copy b % kFlagCopies) of kTagLines
+// lines each, then one slot of kTagLines lines of partials per block.
 constexpr int kTagLines = 4;
-constexpr int kSyncJTag = kSyncArrive + kMaxBlocks * kLineWords;
+constexpr int kSyncJTag = kSyncArriveEnd;
 constexpr int kSyncPart = kSyncJTag + kFlagCopies * kTagLines * kLineWords;
-constexpr int kSyncWords = kSyncPart + 2 * kMaxBlocks * kTagLines * kLineWords;
+constexpr int kSyncWords = kSyncPart + kMaxBlocks * kTagLines * kLineWords;
 constexpr int kTagWords64 = kTagLines * kLineWords / 2;   // 64-bit words per copy or slot
 
 constexpr int kVacRows3 = 7;    // 3f table rows before the weights: 6 vacuum entries and e_k
@@ -42,7 +53,7 @@ struct StepArgs {
   const double* tab;       // tables: 2f [bx|bz|G_0..G_{NS-1}] x NE; 3f [h_ee..h_mt (6)|e_k|G_s]
                            // x NE with e_k = 1/E_k; extended model: then cos, sin of every
                            // azimuthal bin
-  unsigned int* sync;      // kSyncWords words (barrier words and the tagged reduction words)
+  unsigned int* sync;      // kSyncWords words (barrier and reduction words)
   long long* step_ctl;     // [0] device step counter (read at launch start, advanced at the
                            // end); [1] target of a group of windowed launches
   long long plane;         // plane stride (elements)
@@ -121,7 +132,7 @@ struct AdjArgs {
   double* state_bar;       // nullptr, or [3][nb]: dL/d(state at the first step)
   double* spill;           // [9][plane]: the beams' adjoint registers (spill mode only)
   double* out;             // [8]: dL/d{L_e, L_ebar, L_x, theta_v, n0}
-  unsigned int* sync;      // kSyncWords words (barrier words and the tagged reduction words)
+  unsigned int* sync;      // kSyncWords words (barrier and reduction words)
   long long plane, nb;
   int NE, NU;
   long long n0, nsteps, ckpt, nseg;  // first step, steps, checkpoint period, segments

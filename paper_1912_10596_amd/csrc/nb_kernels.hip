@@ -10,8 +10,8 @@
 //   4. accumulates the beam's moment contribution as a 64-bit fixed-point integer; the
 //      row's energy sum is a wavefront butterfly of 128-bit integers, then the angle sum
 //      (1/cos weighting for J0) is added to per-lane totals,
-// then the block folds its waves through LDS, publishes its partial as epoch-tagged words,
-// and every block gathers all partials into J^(i) (no release flag; agent-scope atomics).
+// then the block folds its waves through LDS and adds its partial to counted accumulators,
+// whose published totals every block reads as J^(i) (agent-scope atomics).
 // Four barriers per step; the final pass writes rho_{n+1} and also produces the next
 // step's stage-1 moments.
 #include "nb_device.h"
@@ -26,159 +26,209 @@ __device__ __forceinline__ Radial radial_at(const StepArgs& a, double r) {
   return radial(a.R, a.ne_power, a.lam0, r);
 }
 
-// Grid-wide reduction of the stage moments with tagged words, gathered by every block.
-// Every 64-bit word that crosses blocks carries the epoch of the barrier it belongs to, so
-// a reader knows from the word itself whether it is current, and no arrival or release
-// word (and no store acknowledgement before one) lies on the critical path:
-//  * every block publishes its partial (NV 128-bit sums, each below 2^95 in magnitude) as
-//    2 NV words of a 16-bit tag and a 48-bit chunk: bits 0..47, then bits 48..95, into its
-//    slot of the region of the epoch's parity;
-//  * every block polls all partial words (each of its threads owns one chunk position of
-//    a set of blocks and re-polls only the words not yet current, all loads in flight),
-//    adds the chunks in 64-bit integers (below 2^61 for up to kMaxBlocks blocks) and
-//    combines them to the exact 128-bit totals: the same integers in every block, whatever
-//    the order, so every block holds the same moments after one publish-and-poll hop.
-// The two parity regions make every word safe to rewrite: block b writes its slot of
-// parity e % 2 at epoch e only after reading every partial of epoch e - 1, and every
-// block c wrote that partial only after it had finished reading epoch e - 2, the previous
-// contents of the same parity region.  All words are zeroed before each launch and
-// epochs start at 1, so a tag equal to the wanted epoch is never stale (the 16-bit tags
-// repeat only every 65536 barriers).
+// Grid-wide reduction of the stage moments: counted accumulators, one copy per die, whose
+// totals are published and read by every block.
+//  * A block's partial is NV 128-bit sums, each below 2^93 in magnitude (a row's term is
+//    below 2^62), as 2 NV chunks: bits 0..46 and bits 47..93 (biased by 2^46).  A 64-bit
+//    accumulator holds the sum of chunks in its upper 55 bits and the count of adds, modulo
+//    512, in its lower 9, so one atomic add both delivers a chunk and announces it.  Block b
+//    adds to copy b % 8, n_c <= 256 blocks to a copy.
+//  * Accumulators are never cleared during a launch.  The block whose add completes the
+//    count (e + 1) n_c of epoch e knows it from the value the add returned, and stores the
+//    word's running sum, modulo 2^55, under a 9-bit epoch tag into the published words of
+//    the epoch's parity.  (A copy of one block needs no accumulator: its block keeps the
+//    running sum itself.)
+//  * Every block polls the 8 copies of the 2 NV published words for the epoch's tag, takes
+//    the differences from the previous epoch's running sums (below 2^55, at most 256 chunks
+//    below 2^47), adds the copies in 64-bit integers and combines the chunks to the exact
+//    128-bit totals: the same integers in every block, whatever the order.
+// A published word of parity e % 2 is overwritten at epoch e by a block that has passed
+// barrier e - 1, so every block has added for e - 1 and hence has read all of e - 2.  All
+// words are zeroed before each launch and tags start at 1; a polled word holds tag e - 1 or
+// e + 1 (modulo 512), never an older one.
+// A grid of one block keeps its moments in LDS.
+// Bound: two trips beyond the die (the add within it, then store to poll) of about 0.8 us
+// together with the skew of the blocks.  Measured per barrier in a loop of nothing else, 250
+// blocks, 12 / 32 words: 2.2 / 2.7 us, and 3.6 / 3.8 us with arrivals spread over 2 us,
+// against 3.1 / 3.6 and 4.9 / 5.3 us for slots of tagged words that every block gathers from
+// every other (64 KB per block and poll round).  Polling the accumulators themselves saves
+// a trip (1.65 / 1.76 us) but every early poll delays the adds that it waits for: 5.6 / 7.3
+// us with the spread arrivals, and the 200k-beam step 33 against 26 us.
 // Returns false if the barrier was abandoned (time limit or abort).
-constexpr unsigned long long kMask48 = (1ull << 48) - 1ull;
-// 48-bit chunk k of a 128-bit value below 2^95 in magnitude: k = 0 the unsigned bits
-// 0..47, k = 1 the signed bits 48..95 (as a 48-bit field of the tagged word, and as its
-// integer value).
+constexpr unsigned long long kMask47 = (1ull << 47) - 1ull;
+constexpr unsigned long long kTag9 = 511ull;
+// 47-bit chunk k of a 128-bit value below 2^93 in magnitude: k = 0 the unsigned bits
+// 0..46, k = 1 the signed bits 47..93 plus 2^46.
 __device__ __forceinline__ unsigned long long chunk_field(const I128& x, int k) {
-  return (k ? ((x.lo >> 48) | ((unsigned long long)x.hi << 16)) : x.lo) & kMask48;
+  const unsigned long long hi = (x.lo >> 47) | ((unsigned long long)x.hi << 17);
+  return (k ? hi + (1ull << 46) : x.lo) & kMask47;
 }
-__device__ __forceinline__ long long chunk_value(unsigned long long field, int k) {
-  return k ? ((long long)(field << 16) >> 16) : (long long)field;
+// Sum over 8 consecutive lanes (all active), in every one of them: lane i ^ 1, i ^ 2, 7 - i.
+template <int CTRL>
+__device__ __forceinline__ unsigned long long dpp_u64(unsigned long long x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)x, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(x >> 32), CTRL, 0xf, 0xf, true);
+  return ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo;
 }
-
-// blk: the block's partial (threads tid < NV hold component tid); own: unused (every
-// block reads its own partial back with the others).  MAXE adds one more word to every
-// partial, efield (thread NV): the block's largest error estimate as the top 48 bits of its
-// binary form (a non-negative double, so the integer order of the fields is the order of
-// the values); every block takes the largest field, which lands in *sE.
-// NM moment groups of NV / NM components: J0 | J1 (| J_sc | J_ss); J1 is at scale 2^e1,
-// the others at 2^e0.
-// BS: threads per block (the launch's block size), so that the thread groups and every
-// poll address are compile-time constants.
-template <int NV, bool MAXE, int NM, int BS>
-__device__ __forceinline__ bool grid_reduce(const StepArgs& a, unsigned epoch, I128 blk, long long own,
-                            unsigned long long efield, double* sJ, long long* sacc, double* sE) {
-  constexpr int W = 2 * NV + (MAXE ? 1 : 0);   // words per partial
-  constexpr int G = BS / W;                    // thread groups, one chunk position per thread
-  static_assert(W <= kTagWords64, "tagged slot too small");
-  const int tid = threadIdx.x;
-  const unsigned want = epoch + 1u;
-  const unsigned long long tag16 = (unsigned long long)(want & 0xffffu);
-  unsigned long long* part = reinterpret_cast<unsigned long long*>(a.sync + kSyncPart) +
-                             (size_t)(epoch & 1u) * kMaxBlocks * kTagWords64;
-  unsigned long long* slot = part + (size_t)blockIdx.x * kTagWords64;
-  if (tid < NV) {
-    __hip_atomic_store(slot + 2 * tid, (tag16 << 48) | chunk_field(blk, 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(slot + 2 * tid + 1, (tag16 << 48) | chunk_field(blk, 1), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-  }
-  if (MAXE && tid == NV)
-    __hip_atomic_store(slot + 2 * NV, (tag16 << 48) | efield, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  int ok = 1;
-  const int pos = tid % W, g = tid / W;
-  long long acc = 0;
-  if (g < G) {
-    const unsigned long long t0 = wall_clock64();
-    for (unsigned b0 = g; b0 < gridDim.x && ok; b0 += 16 * G) {
-      unsigned pend = 0;
-      unsigned long long w[16];
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (b0 + i * G < gridDim.x) pend |= 1u << i;
-      for (unsigned it = 1; pend; ++it) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-          if (pend & (1u << i))
-            w[i] = __hip_atomic_load(part + (size_t)(b0 + i * G) * kTagWords64 + pos, __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          if ((pend & (1u << i)) && (w[i] >> 48) == tag16) {
-            if (MAXE && pos == 2 * NV) acc = max(acc, (long long)(w[i] & kMask48));
-            else acc += chunk_value(w[i] & kMask48, pos & 1);
-            pend &= ~(1u << i);
-          }
-        }
-        if (!pend) break;
-        if ((it & 31u) == 0u && give_up(a.sync, a.cancel, t0, a.timeout_ticks, it)) {
-          ok = 0;
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-      }
-    }
-  }
-  sacc[tid] = acc;
-  if (__syncthreads_or(!ok)) return false;
-  if (tid < NV) {
-    long long c0 = 0, c1 = 0;
-    for (int gg = 0; gg < G; ++gg) {
-      c0 += sacc[gg * W + 2 * tid];
-      c1 += sacc[gg * W + 2 * tid + 1];
-    }
-    const I128 tot = i128_add(I128{(unsigned long long)c0, 0ll},
-                              I128{(unsigned long long)c1 << 48, c1 >> 16});
-    sJ[tid] = i128_to_double(tot) * ((tid / (NV / NM)) == 1 ? a.p2e1 : a.p2e0);
-  } else if (MAXE && tid == NV) {
-    long long f = 0;
-    for (int gg = 0; gg < G; ++gg) f = max(f, sacc[gg * W + 2 * NV]);
-    *sE = as_double((unsigned long long)f << 16);
-  }
-  __syncthreads();
-  return true;
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppRor8 = 0x128;
+__device__ __forceinline__ unsigned long long sum8(unsigned long long x) {
+  x += dpp_u64<kDppXor1>(x);
+  x += dpp_u64<kDppXor2>(x);
+  x += dpp_u64<kDppHalfMirror>(x);
+  return x;
 }
 
-// Fold the waves' per-lane totals (lane v holds value v) and run the grid reduction.
-// MAXE: also the largest of the lanes' error estimates emax (then swm holds one double per
-// wave and the grid's largest estimate lands in *sE).  BS: threads per block.
+// LDS words of the reduction: the waves' partials, the running sums (read: those of the
+// previous epoch, by polling thread; own: this block's, in a copy of one block), the block's
+// abandoned flag and, for adaptive runs, the waves' error words.
+template <int NV, int BS, bool MAXE = false>
+struct RedLds {
+  I128 sw[BS / 64][NV];
+  unsigned long long read[2 * NV * kRedCopies], own[2 * NV];
+  unsigned long long swm[MAXE ? BS / 64 : 1];
+  int bad;
+};
+template <int NV, int BS, bool MAXE>
+__device__ __forceinline__ void red_init(RedLds<NV, BS, MAXE>& R) {   // then a block barrier
+  for (int i = threadIdx.x; i < 2 * NV * kRedCopies; i += BS) R.read[i] = 0ull;
+  if (threadIdx.x < 2 * NV) R.own[threadIdx.x] = 0ull;
+  if (threadIdx.x == 0) R.bad = 0;
+}
+
+// Fold the waves' per-lane totals (lane v holds value v) and run the grid reduction; the
+// moments land in sJ.  NM moment groups of NV / NM components: J0 | J1 (| J_sc | J_ss); J1 is
+// at scale 2^e1, the others at 2^e0.
+// MAXE: also the largest of the lanes' error estimates emax, into *sE: every block stores
+// its largest as the top 48 bits of the binary form (a non-negative double, so the integer
+// order of the fields is the order of the values) under a 16-bit epoch tag in a word of its
+// own, of the region of the epoch's parity, and takes the maximum over all blocks' words
+// (block b writes its word of parity e % 2 at epoch e only after barrier e - 1, when every
+// block has read all words of epoch e - 2).
+// BS: threads per block (the launch's block size).
 // (always inlined: a call would take the address of the launch arguments and make the
 // compiler keep a private copy of them)
-template <int NV, bool MAXE, int NM, int BS>
-__device__ __forceinline__ bool finish_stage_bs(const StepArgs& a, unsigned epoch, I128 T, I128 (*sw)[NV],
-                                long long* sacc, double* sJ, double emax, double* swm, double* sE) {
+template <bool MAXE, int NM, int NV, int BS, bool RM>
+__device__ __forceinline__ bool finish_stage(const StepArgs& a, unsigned epoch, I128 T, RedLds<NV, BS, RM>& R,
+                                             double* sJ, double emax = 0.0, double* sE = nullptr) {
   constexpr int WPB = BS / 64;
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  if (lane < NV) sw[wid][lane] = T;
+  constexpr int W = 2 * NV;   // words per copy
+  static_assert(W <= kRedStride && W <= BS, "too many words");
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const auto scale = [&](int v) { return (v / (NV / NM)) == 1 ? a.p2e1 : a.p2e0; };
+  if (lane < NV) R.sw[wid][lane] = T;
   if constexpr (MAXE) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
       const double o = __shfl_xor(emax, off, 64);
       emax = (o > emax) ? o : emax;
     }
-    if (lane == 0) swm[wid] = emax;
+    if (lane == 0) R.swm[wid] = as_bits(emax) >> 16;
   }
   __syncthreads();
-  I128 blk = i128_zero();
-  long long own = 0;
-  unsigned long long efield = 0;
-  if (threadIdx.x < NV)
-    for (int w = 0; w < WPB; ++w) blk = i128_add(blk, sw[w][threadIdx.x]);
-  if (blockIdx.x == 0 && threadIdx.x < 2 * NV) {
-    I128 c = i128_zero();
-    for (int w = 0; w < WPB; ++w) c = i128_add(c, sw[w][threadIdx.x >> 1]);
-    own = chunk_value(chunk_field(c, threadIdx.x & 1), threadIdx.x & 1);
+  I128 blk{0ull, 0ll};
+  unsigned long long f = 0;   // MAXE: the block's error field
+  if (tid < W) {
+    blk = R.sw[0][tid >> 1];
+#pragma unroll
+    for (int w = 1; w < WPB; ++w) blk = i128_add(blk, R.sw[w][tid >> 1]);
   }
   if constexpr (MAXE) {
-    if (threadIdx.x == NV || (blockIdx.x == 0 && threadIdx.x == 2 * NV)) {
-      double m = 0.0;
-      for (int w = 0; w < WPB; ++w) m = (swm[w] > m) ? swm[w] : m;
-      efield = as_bits(m) >> 16;
-      if (threadIdx.x == 2 * NV) own = (long long)efield;
-    }
+    f = R.swm[0];
+#pragma unroll
+    for (int w = 1; w < WPB; ++w) f = max(f, R.swm[w]);
   }
-  return grid_reduce<NV, MAXE, NM, BS>(a, epoch, blk, own, efield, sJ, sacc, sE);
+  if (gridDim.x == 1) {
+    if (tid < W && !(tid & 1)) sJ[tid >> 1] = i128_to_double(blk) * scale(tid >> 1);
+    if (MAXE && tid == 0) *sE = as_double(f << 16);
+    __syncthreads();
+    return true;
+  }
+  unsigned long long* red = reinterpret_cast<unsigned long long*>(a.sync + kSyncRed);
+  unsigned long long* pub =
+      reinterpret_cast<unsigned long long*>(a.sync + kSyncPub) + (size_t)(epoch & 1u) * kRedCopies * kRedStride;
+  const unsigned long long tag = (epoch + 1u) & 511u;
+  const unsigned long long tag16 = (epoch + 1u) & 0xffffu;
+  unsigned long long* ew =
+      reinterpret_cast<unsigned long long*>(a.sync + kSyncErr) + (size_t)(epoch & 1u) * kMaxBlocks;
+  if (tid < W) {
+    const unsigned me = blockIdx.x % kRedCopies;
+    const unsigned nc = (gridDim.x + (kRedCopies - 1) - me) / kRedCopies;   // blocks of the copy
+    const unsigned long long add = chunk_field(blk, tid & 1) << 9;
+    unsigned long long sum;
+    bool last = true;
+    if (nc == 1) {
+      sum = R.own[tid] + add;
+      R.own[tid] = sum;
+    } else {
+      const unsigned long long n0 = (unsigned long long)epoch * nc;   // adds before this epoch
+      sum = __hip_atomic_fetch_add(red + me * kRedStride + tid, add + 1ull, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT) + add + 1ull;
+      last = (((unsigned)sum - (unsigned)n0) & 511u) == (nc & 511u);
+      sum -= n0 + nc;
+    }
+    if (last)
+      __hip_atomic_store(pub + me * kRedStride + tid, (sum & ~kTag9) | tag, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (MAXE && tid == 0)
+    __hip_atomic_store(ew + blockIdx.x, (tag16 << 48) | f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  int ok = 1;
+  const unsigned long long t0 = wall_clock64();
+  // thread i: copy i % 8 of word i / 8 (the 8 copies of a word in 8 consecutive lanes, the
+  // two words of a value in 16)
+  for (int i = tid; i < W * kRedCopies; i += BS) {
+    const unsigned c = i % kRedCopies;
+    const unsigned long long* w = pub + c * kRedStride + i / kRedCopies;
+    const unsigned long long prev = R.read[i];
+    unsigned long long x = prev | tag;   // a copy without blocks
+    for (unsigned it = 1; c < gridDim.x; ++it) {
+      x = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if ((x & kTag9) == tag) break;
+      if ((it & 31u) == 0u && give_up(a.sync, a.cancel, t0, a.timeout_ticks, it)) {
+        ok = 0;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+    x &= ~kTag9;
+    R.read[i] = x;
+    const int k = (i / kRedCopies) & 1;
+    const unsigned long long mine = sum8((x - prev) >> 9) - (k ? (unsigned long long)gridDim.x << 46 : 0ull);
+    const unsigned long long other = dpp_u64<kDppRor8>(mine);
+    const unsigned long long c0 = k ? other : mine, c1 = k ? mine : other;
+    const I128 tot = i128_add(I128{c0, 0ll}, I128{c1 << 47, (long long)c1 >> 17});
+    const int v = i / (2 * kRedCopies);
+    const double J = i128_to_double(tot) * scale(v);
+    if (i % (2 * kRedCopies) == 0) sJ[v] = J;
+  }
+  if constexpr (MAXE) {
+    f = 0;
+    for (unsigned b = tid; b < gridDim.x; b += BS) {
+      unsigned long long x = 0;
+      for (unsigned it = 1; ok; ++it) {
+        x = __hip_atomic_load(ew + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((x >> 48) == tag16) break;
+        if ((it & 31u) == 0u && give_up(a.sync, a.cancel, t0, a.timeout_ticks, it)) ok = 0;
+        __builtin_amdgcn_s_sleep(1);
+      }
+      f = max(f, x & ((1ull << 48) - 1ull));
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) f = max(f, (unsigned long long)__shfl_xor(f, off, 64));
+    __syncthreads();   // every thread has read the waves' words above
+    if (lane == 0) R.swm[wid] = f;
+  }
+  if (!ok) R.bad = 1;
+  __syncthreads();
+  if constexpr (MAXE) {
+    f = R.swm[0];
+#pragma unroll
+    for (int w = 1; w < WPB; ++w) f = max(f, R.swm[w]);
+    if (tid == 0) *sE = as_double(f << 16);
+    __syncthreads();
+  }
+  return R.bad == 0;
 }
-
 
 // Radii and length of one step: stage radii r0, rm = r0 + h/2 and r1.  On the fixed grid
 // r1 = r_start + (n + 1) h (not r0 + h), as in the serial definition.
@@ -1334,8 +1384,7 @@ k_advance(StepArgs a) {
   constexpr int NV = NM * NC;
   constexpr int WPB = BS / 64;
   __shared__ double sJ[4][NV];
-  __shared__ I128 sw[WPB][NV];
-  __shared__ long long sacc[BS];
+  __shared__ RedLds<NV, BS> R;
   // per wavefront: row constants (mixed: then 32 floats), then the first row's geometry
   __shared__ double snn_all[WPB][F32 ? 64 : 48];
   // the two-flavour extended model's rows fold kFoldRowsExt at a time (group2)
@@ -1352,8 +1401,9 @@ k_advance(StepArgs a) {
   const double* tab = a.tab;
   const float* ftab = nullptr;
   if (launch_aborted(a.sync)) return;
+  red_init(R);
   if (NF == 2 && threadIdx.x == 0) sincos_coefs(s_sct);
-  if constexpr (NF == 2) __syncthreads();
+  __syncthreads();
   if constexpr (TLDS) {
     const int ntab = ((NF == 2) ? 2 : kVacRows3) * a.NE + a.NS * a.NE;
     for (int i = threadIdx.x; i < ntab; i += BS) dyn_tab[i] = a.tab[i];
@@ -1415,7 +1465,7 @@ k_advance(StepArgs a) {
     if constexpr (NF == 2) stage2<0, false, EXT>(a, geo_fixed(a, step0), (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, lane, fl, T, err, enone, snn, s_sct, false, srt[EXT ? wid : 0]);
     else if constexpr (F32) stage3m<0, TLDS>(a, geo_fixed(a, step0), sJ, tab, ftab, snn, gw, nw, lane, fl, T, err);
     else { stage3<ST, 0, false, EXT>(a, geo_fixed(a, step0), (const ST*)a.X, (ST*)a.X, sJ, tab, snn, gw, nw, lane, fl, T, err, enone); prefetch_first<ST>(a, gw, nrow3, lane, pre); }
-    ok = finish_stage_bs<NV, false, NM, BS>(a, epoch++, T, sw, sacc, sJ[0], 0.0, nullptr, nullptr);
+    ok = finish_stage<false, NM>(a, epoch++, T, R, sJ[0]);
   }
   // the adjoint's forward pass records every stage's moments: [step][slot][NV]
   auto record = [&](long long step, int slot) {
@@ -1428,25 +1478,25 @@ k_advance(StepArgs a) {
     if constexpr (NF == 2) stage2<1, false, EXT>(a, geo_fixed(a, n), (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, lane, fl, T, err, enone, snn, s_sct, true, srt[EXT ? wid : 0]);
     else if constexpr (F32) stage3m<1, TLDS>(a, geo_fixed(a, n), sJ, tab, ftab, snn, gw, nw, lane, fl, T, err, gc);
     else { stage3<ST, 1, false, EXT, PK>(a, geo_fixed(a, n), (const ST*)a.X, (ST*)a.X, sJ, tab, snn, gw, nw, lane, fl, T, err, enone, pre, gc, snp, flp, owner); prefetch_first<ST>(a, gw, nrow3, lane, pre); }
-    if (!(ok = finish_stage_bs<NV, false, NM, BS>(a, epoch++, T, sw, sacc, sJ[1], 0.0, nullptr, nullptr))) break;
+    if (!(ok = finish_stage<false, NM>(a, epoch++, T, R, sJ[1]))) break;
     record(n, 1);
     T = i128_zero();
     if constexpr (NF == 2) stage2<2, false, EXT>(a, geo_fixed(a, n), (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, lane, fl, T, err, enone, snn, s_sct, true, srt[EXT ? wid : 0]);
     else if constexpr (F32) stage3m<2, TLDS>(a, geo_fixed(a, n), sJ, tab, ftab, snn, gw, nw, lane, fl, T, err, gc);
     else { stage3<ST, 2, false, EXT, PK>(a, geo_fixed(a, n), (const ST*)a.X, (ST*)a.X, sJ, tab, snn, gw, nw, lane, fl, T, err, enone, pre, gc, snp, flp, owner); prefetch_first<ST>(a, gw, nrow3, lane, pre); }
-    if (!(ok = finish_stage_bs<NV, false, NM, BS>(a, epoch++, T, sw, sacc, sJ[2], 0.0, nullptr, nullptr))) break;
+    if (!(ok = finish_stage<false, NM>(a, epoch++, T, R, sJ[2]))) break;
     record(n, 2);
     T = i128_zero();
     if constexpr (NF == 2) stage2<3, false, EXT>(a, geo_fixed(a, n), (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, lane, fl, T, err, enone, snn, s_sct, true, srt[EXT ? wid : 0]);
     else if constexpr (F32) stage3m<3, TLDS>(a, geo_fixed(a, n), sJ, tab, ftab, snn, gw, nw, lane, fl, T, err, gc);
     else { stage3<ST, 3, false, EXT, PK>(a, geo_fixed(a, n), (const ST*)a.X, (ST*)a.X, sJ, tab, snn, gw, nw, lane, fl, T, err, enone, pre, gc, snp, flp, owner); prefetch_first<ST>(a, gw, nrow3, lane, pre); }
-    if (!(ok = finish_stage_bs<NV, false, NM, BS>(a, epoch++, T, sw, sacc, sJ[3], 0.0, nullptr, nullptr))) break;
+    if (!(ok = finish_stage<false, NM>(a, epoch++, T, R, sJ[3]))) break;
     record(n, 3);
     T = i128_zero();
     if constexpr (NF == 2) stage2<4, false, EXT>(a, geo_fixed(a, n), (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, lane, fl, T, err, enone, snn, s_sct, true, srt[EXT ? wid : 0]);
     else if constexpr (F32) stage3m<4, TLDS>(a, geo_fixed(a, n), sJ, tab, ftab, snn, gw, nw, lane, fl, T, err, gc);
     else { stage3<ST, 4, false, EXT, PK>(a, geo_fixed(a, n), (const ST*)a.X, (ST*)a.X, sJ, tab, snn, gw, nw, lane, fl, T, err, enone, pre, gc, snp, flp, owner); prefetch_first<ST>(a, gw, nrow3, lane, pre); }
-    ok = finish_stage_bs<NV, false, NM, BS>(a, epoch++, T, sw, sacc, sJ[0], 0.0, nullptr, nullptr);
+    ok = finish_stage<false, NM>(a, epoch++, T, R, sJ[0]);
     record(n + 1, 0);
   }
   if (err) __hip_atomic_fetch_or(a.sync + kSyncStatus, (unsigned)err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1504,9 +1554,7 @@ __global__ void __launch_bounds__(kBlock) k_adaptive(StepArgs a) {
   __shared__ double sJ[4][NV];
   __shared__ double sJsave[NV];
   __shared__ double sE[1];
-  __shared__ double swm[kBlock / 64];
-  __shared__ I128 sw[kBlock / 64][NV];
-  __shared__ long long sacc[kBlock];
+  __shared__ RedLds<NV, kBlock, true> R;
   __shared__ double snn_all[kBlock / 64][48];   // row constants, then the first row's geometry
   __shared__ long long sfold[kBlock / 64][(NC + 2) * 64];
   __shared__ double s_sct[kSinCosTab];   // sin/cos constants of the two-flavour rotations
@@ -1518,8 +1566,9 @@ __global__ void __launch_bounds__(kBlock) k_adaptive(StepArgs a) {
   const long long nw = (long long)gridDim.x * (kBlock / 64);
   if (launch_aborted(a.sync)) return;
   const double* tab = a.tab;
+  red_init(R);
   if (NF == 2 && threadIdx.x == 0) sincos_coefs(s_sct);
-  if constexpr (NF == 2) __syncthreads();
+  __syncthreads();
   if constexpr (TLDS) {
     const int ntab = ((NF == 2) ? 2 : kVacRows3) * a.NE + a.NS * a.NE;
     for (int i = threadIdx.x; i < ntab; i += kBlock) dyn_tab[i] = a.tab[i];
@@ -1550,7 +1599,7 @@ __global__ void __launch_bounds__(kBlock) k_adaptive(StepArgs a) {
   using K3 = std::integral_constant<int, 3>;
   using K4 = std::integral_constant<int, 4>;
   stage(K0{}, StepGeo{r, r, r, 0.0});
-  bool ok = finish_stage_bs<NV, false, 2, kBlock>(a, epoch++, T, sw, sacc, sJ[0], 0.0, nullptr, nullptr);
+  bool ok = finish_stage<false, 2>(a, epoch++, T, R, sJ[0]);
   if (threadIdx.x < NV) sJsave[threadIdx.x] = sJ[0][threadIdx.x];
   while (ok) {
     const bool last = (r + h >= a.r_end);
@@ -1558,17 +1607,17 @@ __global__ void __launch_bounds__(kBlock) k_adaptive(StepArgs a) {
     const StepGeo G{r, r + 0.5 * hs, last ? a.r_end : r + hs, hs};
     T = i128_zero();
     stage(K1{}, G);
-    if (!(ok = finish_stage_bs<NV, false, 2, kBlock>(a, epoch++, T, sw, sacc, sJ[1], 0.0, nullptr, nullptr))) break;
+    if (!(ok = finish_stage<false, 2>(a, epoch++, T, R, sJ[1]))) break;
     T = i128_zero();
     stage(K2{}, G);
-    if (!(ok = finish_stage_bs<NV, false, 2, kBlock>(a, epoch++, T, sw, sacc, sJ[2], 0.0, nullptr, nullptr))) break;
+    if (!(ok = finish_stage<false, 2>(a, epoch++, T, R, sJ[2]))) break;
     T = i128_zero();
     stage(K3{}, G);
-    if (!(ok = finish_stage_bs<NV, false, 2, kBlock>(a, epoch++, T, sw, sacc, sJ[3], 0.0, nullptr, nullptr))) break;
+    if (!(ok = finish_stage<false, 2>(a, epoch++, T, R, sJ[3]))) break;
     T = i128_zero();
     emax = 0.0;
     stage(K4{}, G);
-    if (!(ok = finish_stage_bs<NV, true, 2, kBlock>(a, epoch++, T, sw, sacc, sJ[0], emax, swm, sE))) break;
+    if (!(ok = finish_stage<true, 2>(a, epoch++, T, R, sJ[0], emax, sE))) break;
     ++natt;
     const double E = *sE;
     if (E <= a.tol2) {
@@ -1823,12 +1872,12 @@ __global__ void k_set_target(long long* step_ctl, long long k, long long total) 
   step_ctl[1] = min(step_ctl[0] + k, total);
 }
 
-// Clear the barrier and reduction words before a persistent launch (keep_status: keep the
-// status bits of earlier launches of the same call).  If the host has set the model's
+// Clear the first `words` barrier and reduction words (those the launch uses) before a
+// persistent launch (keep_status: keep the status bits of earlier launches of the same call).  If the host has set the model's
 // cancel word (fine-grained host memory; nullptr: none), the abort word is set instead of
 // cleared, with status bit 2, so that the next persistent launch returns at once.
-__global__ void k_zero_sync(unsigned int* sync, int keep_status, const unsigned* cancel) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kSyncWords; i += gridDim.x * blockDim.x) {
+__global__ void k_zero_sync(unsigned int* sync, int keep_status, const unsigned* cancel, int words) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < words; i += gridDim.x * blockDim.x) {
     if (i == kSyncStatus) continue;   // written with the abort word
     if (i == kSyncAbort) {
       const unsigned c =

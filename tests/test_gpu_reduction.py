@@ -1,0 +1,47 @@
+"""The grid reduction of the stage moments at the edges of its grid sizes and epoch tags: one
+block (no exchange), at most eight (every copy has one block), nine and more (some or all
+copies have several), past 512 barriers (the 9-bit tags and counts wrap); against the oracle,
+bit for bit."""
+import numpy as np
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def nb():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no HIP device visible")
+    import paper_1912_10596_amd as nb
+    nb.lib()
+    return nb
+
+
+@pytest.mark.parametrize("nf", [2, 3])
+@pytest.mark.parametrize("blocks", [1, 2, 7, 8, 9, 16, 18])
+def test_grid_sizes_and_tag_wrap(nb, oracle, nf, blocks):
+    d = workloads.small_params(n_flavor=nf, n_energy=9, n_u=72, n_steps=300)
+    print(f"reduction: {nf} flavours, {blocks} blocks, 1200 barriers", flush=True)
+    m = nb.Model(d)
+    m.set_tuning(512, blocks)
+    assert m.get_tuning()["blocks"] == blocks
+    m.run()
+    o = oracle.Model(d)
+    o.run()
+    np.testing.assert_array_equal(m.get_state().cpu().numpy(), o.get_state())
+
+
+@pytest.mark.parametrize("n_u", [3, 40, 90])
+def test_adaptive_grid_sizes(nb, oracle, n_u):
+    d = workloads.small_params(n_flavor=2, n_energy=7, n_u=n_u, n_steps=200, r_start_km=600.0,
+                               r_end_km=604.0)
+    print(f"reduction: adaptive, {2 * n_u} rows", flush=True)
+    m = nb.Model(d, adaptive=True)
+    st = m.run_adaptive(1e-7)
+    o = oracle.Model(d)
+    so = o.run_adaptive(1e-7)
+    assert (st["accepted"], st["rejected"]) == (so["accepted"], so["rejected"])
+    np.testing.assert_array_equal(m.get_state().cpu().numpy(), o.get_state())
