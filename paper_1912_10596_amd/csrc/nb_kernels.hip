@@ -78,6 +78,11 @@ __device__ __forceinline__ unsigned long long sum8(unsigned long long x) {
   return x;
 }
 
+template <int NC>
+__device__ __forceinline__ int fold_comp(int lane);     // lane layout of the moment totals, below
+template <int NC>
+__device__ __forceinline__ int fold_moment(int lane);
+
 // LDS words of the reduction: the waves' partials, the running sums (read: those of the
 // previous epoch, by polling thread; own: this block's, in a copy of one block), the block's
 // abandoned flag and, for adaptive runs, the waves' error words.
@@ -95,8 +100,8 @@ __device__ __forceinline__ void red_init(RedLds<NV, BS, MAXE>& R) {   // then a 
   if (threadIdx.x == 0) R.bad = 0;
 }
 
-// Fold the waves' per-lane totals (lane v holds value v) and run the grid reduction; the
-// moments land in sJ.  NM moment groups of NV / NM components: J0 | J1 (| J_sc | J_ss); J1 is
+// Fold the waves' per-lane totals (in the lanes of fold_comp, fold_moment) and run the grid
+// reduction; the moments land in sJ.  NM moment groups of NV / NM components: J0 | J1 (| J_sc | J_ss); J1 is
 // at scale 2^e1, the others at 2^e0.
 // MAXE: also the largest of the lanes' error estimates emax, into *sE: every block stores
 // its largest as the top 48 bits of the binary form (a non-negative double, so the integer
@@ -114,8 +119,10 @@ __device__ __forceinline__ bool finish_stage(const StepArgs& a, unsigned epoch, 
   constexpr int W = 2 * NV;   // words per copy
   static_assert(W <= kRedStride && W <= BS, "too many words");
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const auto scale = [&](int v) { return (v / (NV / NM)) == 1 ? a.p2e1 : a.p2e0; };
-  if (lane < NV) R.sw[wid][lane] = T;
+  constexpr int NC = NV / NM;
+  const auto scale = [&](int v) { return (v / NC) == 1 ? a.p2e1 : a.p2e0; };
+  if (fold_moment<NC>(lane) < NM && fold_comp<NC>(lane) < NC)
+    R.sw[wid][fold_moment<NC>(lane) * NC + fold_comp<NC>(lane)] = T;
   if constexpr (MAXE) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
@@ -249,6 +256,8 @@ __device__ __forceinline__ StepGeo geo_fixed(const StepArgs& a, long long n) {
 struct Scales {
   double s1, s0, p2e1, p2e0;
 };
+// Energies of one row segment (32 of a lane's beams): longer rows add several segments' sums.
+constexpr int kSegNE = 64 * 32;
 // Start value of a lane's 64-bit sums over the segment k0, k0 + 64, ... < kend: minus
 // kFixMagic once per contribution (modulo 2^64), so that adding the contributions' bit
 // patterns leaves the sum of their integers.
@@ -256,56 +265,61 @@ __device__ __forceinline__ unsigned long long fix_base(int k0, int kend) {
   const unsigned long long n = (kend > k0) ? (unsigned long long)((kend - k0 + 63) >> 6) : 0ull;
   return 0ull - n * kFixMagic;
 }
-// End of a row segment: the lanes' 64-bit sums -> exact per-component wave sums, added to
-// `mine` of lanes v < 2 NC (component v % NC).  Through this wave's LDS scratch fl
-// ((NC + 2) x 64 words): every lane stores its NC sums; lane (g, c) of G = 64/NC groups adds
-// component c of L = ceil(64/G) lanes as a 128-bit integer; lanes v < 2 NC add the G group
-// sums of component v % NC.  Integer sums, so the order does not matter.
-template <int NC, int NM = 2>
-__device__ __forceinline__ void fold_segment(const long long* acc, int lane, long long* fl, I128& mine) {
-  // Every lane sum is below 2^56 in magnitude (at most 32 contributions below 2^51, or a
-  // mixed-precision lane sum converted below 2^56), so one component's 64 lane sums add up
-  // below 2^62: plain 64-bit integer sums, widened to 128 bits once per segment.
-  constexpr int G = 64 / NC, L = (64 + G - 1) / G;
-#pragma unroll
-  for (int i = 0; i < NC; ++i) fl[i * 64 + lane] = acc[i];
-  __asm__ volatile("" ::: "memory");   // the wave's LDS operations complete in program order
-  long long* gs = fl + NC * 64;
-  const int c = lane % NC, g = lane / NC;
-  if (g < G) {
-    long long part = 0;
-#pragma unroll
-    for (int i = 0; i < L; ++i) {
-      const int src = g * L + i;
-      if (src < 64) part += fl[c * 64 + src];
-    }
-    gs[g * NC + c] = part;
-  }
-  __asm__ volatile("" ::: "memory");
-  if (lane < NM * NC) {
-    const int cc = lane % NC;
-    long long t = 0;
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg) t += gs[gg * NC + cc];
-    mine = i128_add(mine, i128_from(t));
-  }
-  __asm__ volatile("" ::: "memory");
+// Lane layout of a wavefront's moment totals: component c of moment m (J0, J1, J_sc, J_ss)
+// sits in lane c * (64 / (NC rounded up to a power of two)) + m.
+template <int NC>
+__device__ __forceinline__ int fold_comp(int lane) { return lane >> (NC == 3 ? 4 : 3); }
+template <int NC>
+__device__ __forceinline__ int fold_moment(int lane) { return lane & (NC == 3 ? 15 : 7); }
+
+// a over the lower, b over the upper half of the wavefront (of each 32 lanes), every lane
+// adding the value of the lane 32 (16) further: two components' sums in one register pair.
+__device__ __forceinline__ unsigned long long swap_add32(unsigned long long a, unsigned long long b) {
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)a, (unsigned)b, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(a >> 32), (unsigned)(b >> 32), false, false);
+  return (((unsigned long long)hi[0] << 32) | lo[0]) + (((unsigned long long)hi[1] << 32) | lo[1]);
 }
-// End of a row: lanes v < NC add the J0 angle term (energy sum / cos), lanes
-// NC <= v < 2 NC the J1 energy sum, to their running totals; with NM = 4 (extended model)
-// lanes 2 NC <= v < 3 NC add the J_sc term (energy sum sin(theta) cos(phi) / cos: asc =
-// (sin(theta) / cos) cos(phi)) and 3 NC <= v < 4 NC the J_ss term (ass, sin(phi)).
+__device__ __forceinline__ unsigned long long swap_add16(unsigned long long a, unsigned long long b) {
+  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)a, (unsigned)b, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(a >> 32), (unsigned)(b >> 32), false, false);
+  return (((unsigned long long)hi[0] << 32) | lo[0]) + (((unsigned long long)hi[1] << 32) | lo[1]);
+}
+// Exact sums of the lanes' NC 64-bit values over the wavefront (all lanes active): component
+// fold_comp(lane) in every lane of its group.  Halving steps: each step adds pairs of lanes
+// for two components at once, so NC components need about 2 NC + 8 adds instead of 6 NC, and
+// no LDS trip (through LDS, with one lane per partial sum, a fold of 3 components took 1340
+// cycles and one of 8 took 780-950; this one about 250).
+// Every lane value is below 2^56 in magnitude (at most 32 contributions below 2^51, or a
+// mixed-precision lane sum converted below 2^56), so the sums stay below 2^62.
+template <int NC>
+__device__ __forceinline__ long long wave_fold(const unsigned long long (&x)[NC], int lane) {
+  unsigned long long t;
+  if constexpr (NC == 3) {
+    t = swap_add16(swap_add32(x[0], x[2]), swap_add32(x[1], 0ull));
+    t += dpp_u64<kDppRor8>(t);
+  } else {
+    static_assert(NC == 8, "3 or 8 components");
+    const unsigned long long z0 = swap_add16(swap_add32(x[0], x[4]), swap_add32(x[2], x[6]));
+    const unsigned long long z1 = swap_add16(swap_add32(x[1], x[5]), swap_add32(x[3], x[7]));
+    const bool up = lane & 8;
+    t = (up ? z1 : z0) + dpp_u64<kDppRor8>(up ? z0 : z1);
+  }
+  return (long long)sum8(t);
+}
+// End of a row: the lanes of moment 0 add the J0 angle term (energy sum / cos), those of
+// moment 1 the J1 energy sum, to their running totals; with NM = 4 (extended model) those of
+// moments 2 and 3 the J_sc term (energy sum sin(theta) cos(phi) / cos: asc = (sin(theta) /
+// cos) cos(phi)) and the J_ss term (ass, sin(phi)).  mine: the row's sum of the lane's
+// component, v the same as a double.
 template <int NC, int NM = 2>
-__device__ __forceinline__ void close_row(const Scales& sc, int lane, const I128& mine,
-                                          double icmom, I128& T, int& err, double asc = 0.0,
-                                          double ass = 0.0) {
-  if (lane < NC) {
-    T = i128_add(T, i128_from(to_fix(icmom * (i128_to_double(mine) * sc.p2e1), sc.s0, kTwo62, err)));
-  } else if (lane < 2 * NC) {
+__device__ __forceinline__ void close_row(const Scales& sc, int lane, const I128& mine, double v, double icmom,
+                                          I128& T, int& err, double asc = 0.0, double ass = 0.0) {
+  const int m = fold_moment<NC>(lane);
+  if (m == 1) {
     T = i128_add(T, mine);
-  } else if (NM == 4 && lane < 4 * NC) {
-    const double f = (lane < 3 * NC) ? asc : ass;
-    T = i128_add(T, i128_from(to_fix(f * (i128_to_double(mine) * sc.p2e1), sc.s0, kTwo62, err)));
+  } else if (m < NM && fold_comp<NC>(lane) < NC) {
+    const double f = (m == 0) ? icmom : ((m == 2) ? asc : ass);
+    T = i128_add(T, i128_from(to_fix(f * (v * sc.p2e1), sc.s0, kTwo62, err)));
   }
 }
 
@@ -418,7 +432,7 @@ constexpr int kRowC = 26;    // doubles per row-constant block (25 used)
 template <int KIND, bool ADAPT = false, bool EXT = false, bool PRE = false>
 __device__ __forceinline__ void row2(const double* X, double* Xo, long long plane, long long rb, int NE,
                                      int s, double u, double h, const double* tab, double* cb,
-                                     const double* const* J, int renorm, int lane, long long* fl, I128& T,
+                                     const double* const* J, int renorm, int lane, I128& T,
                                      int& err, double& emax, double cp = 0.0, double sp = 0.0,
                                      int an = -1, bool geo = false, const double* sct = nullptr,
                                      double* rcp = nullptr) {
@@ -505,10 +519,11 @@ __device__ __forceinline__ void row2(const double* X, double* Xo, long long plan
       acc[1] += fix_bits(P1, ws);
       acc[2] += fix_bits(P2, wa);
     }
-    fold_segment<3, NM>(reinterpret_cast<const long long*>(acc), lane, fl, mine);
+    mine = i128_add(mine, i128_from(wave_fold<3>(acc, lane)));
   }
   __asm__ volatile("" ::: "memory");
-  close_row<3, NM>(Scales{cb[kC2Sc + 0], cb[kC2Sc + 1], cb[kC2Sc + 2], cb[kC2Sc + 3]}, lane, mine, rc[20], T,
+  const double v = (NE <= kSegNE) ? (double)(long long)mine.lo : i128_to_double(mine);
+  close_row<3, NM>(Scales{cb[kC2Sc + 0], cb[kC2Sc + 1], cb[kC2Sc + 2], cb[kC2Sc + 3]}, lane, mine, v, rc[20], T,
                    err, rc[21], rc[22]);
 }
 
@@ -520,64 +535,46 @@ __device__ __forceinline__ void row2(const double* X, double* Xo, long long plan
 // lanes idle.  A row's exact sum is folded in the chunk where the row ends (its lanes fold,
 // the others go on with the next row), so every row adds the same integer sum as in row2
 // and the moments keep their bits.  A lane adds at most ceil(NE / 64) + 1 contributions
-// to a row, so with NE <= kGroupMaxNE its 64-bit sums stay below 2^56 as fold_segment needs.
+// to a row, so with NE <= kGroupMaxNE its 64-bit sums stay below 2^56 as wave_fold needs.
 constexpr int kRowS = 23, kRowA = 24;
 constexpr int kGroupMaxNE = 64 * 31;
 // Rows folded together by group2.  The extended model's rows (100 energies) end in most
-// chunks, and a fold and close of one row costs about as many issue slots as of four, so its
-// wavefront folds four rows at a time (60M beams: 2.79 -> 2.45 ms per step).  The batch
-// kernel folds one: its rows are longer (50-400 energies) and at 128 VGPRs the staged
-// totals spill (two rows at a time: 2.88 -> 4.63 ms).
+// chunks, so its wavefront stages ended rows in LDS and folds and closes four at a time (20M
+// beams, 31 energies: 351 us per step against 366 with one row at a time; 100 energies: 771
+// against 782).  The batch kernel folds each row as it ends (wave_fold): its rows are longer
+// (50-400 energies) and at 128 VGPRs staged totals spill (two rows at a time: 2.88 -> 4.63 ms).
 constexpr int kFoldRowsExt = 4, kFoldRowsBatch = 1;
-// A wavefront's fold scratch for group2 with R rows per fold: 3 R staged components, each
+// A wavefront's fold scratch for group2 with R > 1 rows per fold: 3 R staged components, each
 // in a run of fold2_stride(R) words, then the 3 R G partial sums (G = 64 / 3 R per
-// component).  With R > 1 a run is 64 + G words and lane g of component c adds words g,
-// g + G, ...: the padding puts component c's run G banks after component c - 1's, so these
-// reads meet no bank conflicts (the extended model's 12 components would otherwise read
-// one bank 12-fold; 60M beams 2.43 -> 2.35 ms per step).  With R = 1 (3 components) the
-// plain layout is kept: its index arithmetic costs the batch kernel more in spills than
-// the conflicts (2.89 against 3.04 ms).
-__host__ __device__ constexpr int fold2_stride(int R) { return (R > 1) ? 64 + 64 / (3 * R) : 64; }
+// component).  A run is 64 + G words and lane g of component c adds words g, g + G, ...: the
+// padding puts component c's run G banks after component c - 1's, so these reads meet no
+// bank conflicts (the extended model's 12 components would otherwise read one bank 12-fold;
+// 60M beams 2.43 -> 2.35 ms per step).
+__host__ __device__ constexpr int fold2_stride(int R) { return 64 + 64 / (3 * R); }
 __host__ __device__ constexpr int fold2_words(int R) { return 3 * R * fold2_stride(R) + 64; }
 
 // Fold of up to R rows whose lane sums were staged as they ended: component c of slot q in
-// fl[(q * 3 + c) * S + lane], q < nrows, S = fold2_stride(R).  The same integer reduction as
-// fold_segment over 3 R components at once: G partial sums per component, each over every
-// G-th word (R > 1) or over a run of words (R = 1), then lane v adds the G partial sums of
-// its component.  Lane m * 3 R + q * 3 + c then closes moment m, component c of the row in
-// slot q (its row constants at rr0 + q * kRowC) exactly as close_row does, into Tq.  One
-// set of instructions folds and closes R rows, instead of one per row.
+// fl[(q * 3 + c) * S + lane], q < nrows, S = fold2_stride(R).  G partial sums per component,
+// each over every G-th word, then lane v adds the G partial sums of its component.  Lane
+// m * 3 R + q * 3 + c then closes moment m, component c of the row in slot q (its row
+// constants at rr0 + q * kRowC) exactly as close_row does, into Tq.  One set of
+// instructions folds and closes R rows, instead of one per row.
 template <int R, int NM>
 __device__ __forceinline__ void fold_rows2(int lane, long long* fl, int nrows, const double* rr0,
                                            const Scales& sc, I128& Tq, int& err) {
   constexpr int NCR = 3 * R, G = 64 / NCR, L = (64 + G - 1) / G, S = fold2_stride(R);
-  constexpr bool PAD = R > 1;
   long long* gs = fl + NCR * S;
   __asm__ volatile("" ::: "memory");   // the wave's LDS operations complete in program order
-  // lane (cc, g): partial sum g of component cc, stored at gs[cc * G + g] (R > 1) or
-  // gs[g * NCR + cc] (R = 1)
-  if (PAD) {
-    const int cc = lane / G, g = lane - cc * G;
-    if (cc < NCR) {
-      long long part = 0;
+  // lane (cc, g): partial sum g of component cc, stored at gs[cc * G + g]
+  const int cc = lane / G, g = lane - cc * G;
+  if (cc < NCR) {
+    long long part = 0;
 #pragma unroll
-      for (int i = 0; i < L; ++i) {
-        const int src = i * G + g;
-        if (src < 64) part += fl[cc * S + src];
-      }
-      gs[cc * G + g] = part;
+    for (int i = 0; i < L; ++i) {
+      const int src = i * G + g;
+      if (src < 64) part += fl[cc * S + src];
     }
-  } else {
-    const int cc = lane % NCR, g = lane / NCR;
-    if (g < G) {
-      long long part = 0;
-#pragma unroll
-      for (int i = 0; i < L; ++i) {
-        const int src = g * L + i;
-        if (src < 64) part += fl[cc * S + src];
-      }
-      gs[g * NCR + cc] = part;
-    }
+    gs[cc * G + g] = part;
   }
   __asm__ volatile("" ::: "memory");
   if (lane < NM * NCR) {
@@ -585,7 +582,7 @@ __device__ __forceinline__ void fold_rows2(int lane, long long* fl, int nrows, c
     if (q < nrows) {
       long long t = 0;
 #pragma unroll
-      for (int gg = 0; gg < G; ++gg) t += gs[PAD ? qc * G + gg : gg * NCR + qc];
+      for (int gg = 0; gg < G; ++gg) t += gs[qc * G + gg];
       const double* rr = rr0 + q * kRowC;
       if (m == 1) {
         Tq = i128_add(Tq, i128_from(t));
@@ -603,7 +600,7 @@ __device__ __forceinline__ void group2(double* X, long long plane, long long gb0
                                        const double* tab, double* cb, const double* rt, int renorm,
                                        int lane, long long* fl, I128& T, int& err, const double* sct) {
   constexpr int NM = EXT ? 4 : 2;
-  constexpr int NCR = 3 * R, S = fold2_stride(R);
+  constexpr int NCR = 3 * R, S = fold2_stride(R);   // R > 1
   const Scales sc{cb[kC2Sc + 0], cb[kC2Sc + 1], cb[kC2Sc + 2], cb[kC2Sc + 3]};
   const int nbeam = gn * NE;
   const int nchunk = (nbeam + 63) >> 6;
@@ -705,16 +702,24 @@ __device__ __forceinline__ void group2(double* X, long long plane, long long gb0
         ++cnt;
       }
       const unsigned long long bias = cnt * kFixMagic;
-      long long* slot = fl + ns * 3 * S + lane;
-      slot[0] = (long long)(acc[0] - bias);
-      slot[S] = (long long)(acc[1] - bias);
-      slot[2 * S] = (long long)(acc[2] - bias);
+      const unsigned long long ended[3] = {acc[0] - bias, acc[1] - bias, acc[2] - bias};
       acc[0] = acc[1] = acc[2] = 0ull;
       cnt = 0;
-      ++r;
-      if (++ns == R) {
-        fold_rows2<R, NM>(lane, fl, R, rt + (r - R) * kRowC, sc, Tq, err);
-        ns = 0;
+      if constexpr (R == 1) {
+        const long long t = wave_fold<3>(ended, lane);
+        const double* rr = rt + r * kRowC;
+        close_row<3, NM>(sc, lane, i128_from(t), (double)t, rr[20], T, err, rr[21], rr[22]);
+        ++r;
+      } else {
+        long long* slot = fl + ns * 3 * S + lane;
+        slot[0] = (long long)ended[0];
+        slot[S] = (long long)ended[1];
+        slot[2 * S] = (long long)ended[2];
+        ++r;
+        if (++ns == R) {
+          fold_rows2<R, NM>(lane, fl, R, rt + (r - R) * kRowC, sc, Tq, err);
+          ns = 0;
+        }
       }
     }
     if (on && i == r) {      // the row that goes on into the next chunk
@@ -727,6 +732,7 @@ __device__ __forceinline__ void group2(double* X, long long plane, long long gb0
       ++i;
     }
   }
+  if constexpr (R == 1) return;
   if (ns) fold_rows2<R, NM>(lane, fl, ns, rt + (r - ns) * kRowC, sc, Tq, err);
   // the closed rows' totals (lane m * 3 R + q * 3 + c) into T (lane m * 3 + c): integer sums
   __asm__ volatile("" ::: "memory");
@@ -735,8 +741,9 @@ __device__ __forceinline__ void group2(double* X, long long plane, long long gb0
     fl[2 * lane + 1] = Tq.hi;
   }
   __asm__ volatile("" ::: "memory");
-  if (lane < NM * 3) {
-    const int m = lane / 3, c = lane - 3 * m;
+  const int m = fold_moment<3>(lane);
+  if (m < NM && fold_comp<3>(lane) < 3) {
+    const int c = fold_comp<3>(lane);
 #pragma unroll
     for (int q = 0; q < R; ++q) {
       const int src = m * NCR + q * 3 + c;
@@ -792,7 +799,7 @@ __device__ __forceinline__ void stage2(const StepArgs& a, const StepGeo& G, cons
         for (int i = 0; i < gn; ++i, ++row) {
           const long long sj = row / NP;
           const int s = (int)(sj / NU);
-          row2<KIND, ADAPT, true, true>(X, Xo, plane, row * NE, NE, s, 0.0, h, tab, cb, J, renorm, lane, fl, T,
+          row2<KIND, ADAPT, true, true>(X, Xo, plane, row * NE, NE, s, 0.0, h, tab, cb, J, renorm, lane, T,
                                         err, emax, 0.0, 0.0, s >= (NS >> 1), false, sct, rt + i * kRowC);
         }
       }
@@ -803,7 +810,7 @@ __device__ __forceinline__ void stage2(const StepArgs& a, const StepGeo& G, cons
       const int s = (int)(row / a.NU);
       const int j = (int)(row - (long long)s * a.NU);
       row2<KIND, ADAPT>(X, Xo, a.plane, row * a.NE, a.NE, s, u_of(j, a.NU), G.h, tab, cb, J, a.renorm,
-                        lane, fl, T, err, emax, 0.0, 0.0, s >= (a.NS >> 1), geo && row == gw, sct);
+                        lane, T, err, emax, 0.0, 0.0, s >= (a.NS >> 1), geo && row == gw, sct);
     }
   }
 }
@@ -1152,7 +1159,7 @@ __device__ __forceinline__ void row3(const StepArgs& a, const ST* X, ST* Xo, lon
           if (lane >> 5) flp[i * 32 + (lane & 31)] = (long long)xv;
           else acc[i] += xv;
         }
-        fold_segment<8, NM>(reinterpret_cast<const long long*>(acc), lane, fl, mine);
+        mine = i128_add(mine, i128_from(wave_fold<8>(acc, lane)));
       }
       __syncthreads();   // the owner's handed-over contributions are in the partner's scratch
       if (!owner) {
@@ -1160,15 +1167,15 @@ __device__ __forceinline__ void row3(const StepArgs& a, const ST* X, ST* Xo, lon
 #pragma unroll
           for (int i = 0; i < 8; ++i) acc[i] += (unsigned long long)fl[i * 32 + lane];
         }
-        __asm__ volatile("" ::: "memory");
-        fold_segment<8, NM>(reinterpret_cast<const long long*>(acc), lane, fl, mine);
+        mine = i128_add(mine, i128_from(wave_fold<8>(acc, lane)));
       }
     } else {
-      fold_segment<8, NM>(reinterpret_cast<const long long*>(acc), lane, fl, mine);
+      mine = i128_add(mine, i128_from(wave_fold<8>(acc, lane)));
     }
   }
   const double snmom = (KIND == 0) ? sn0 : ((KIND <= 2) ? snm : sn1);
-  close_row<8, NM>(Scales{a.s1, a.s0, a.p2e1, a.p2e0}, lane, mine, icmom, T, err, (snmom * icmom) * cp,
+  const double v = (NE <= kSegNE) ? (double)(long long)mine.lo : i128_to_double(mine);
+  close_row<8, NM>(Scales{a.s1, a.s0, a.p2e1, a.p2e0}, lane, mine, v, icmom, T, err, (snmom * icmom) * cp,
                    (snmom * icmom) * sp);
 }
 
@@ -1337,12 +1344,13 @@ __device__ __forceinline__ void row3m(const StepArgs& a, long long row, const Ra
 #pragma unroll
       for (int i = 0; i < 8; ++i) dacc[i] = fma((i < 3 || i == 4 || i == 6) ? wa : w, v8[i], dacc[i]);
     }
-    long long acc[8];
+    unsigned long long acc[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = to_fix(dacc[i], a.s1, kTwo56, err);
-    fold_segment<8>(acc, lane, fl, mine);
+    for (int i = 0; i < 8; ++i) acc[i] = (unsigned long long)to_fix(dacc[i], a.s1, kTwo56, err);
+    mine = i128_add(mine, i128_from(wave_fold<8>(acc, lane)));
   }
-  close_row<8>(Scales{a.s1, a.s0, a.p2e1, a.p2e0}, lane, mine, icmom, T, err);
+  const double v = (NE <= kSeg) ? (double)(long long)mine.lo : i128_to_double(mine);
+  close_row<8>(Scales{a.s1, a.s0, a.p2e1, a.p2e0}, lane, mine, v, icmom, T, err);
 }
 
 // Mixed-precision stage: every row with FP32 per-beam arithmetic.  The host runs these
@@ -1388,7 +1396,7 @@ k_advance(StepArgs a) {
   // per wavefront: row constants (mixed: then 32 floats), then the first row's geometry
   __shared__ double snn_all[WPB][F32 ? 64 : 48];
   // the two-flavour extended model's rows fold kFoldRowsExt at a time (group2)
-  __shared__ long long sfold[WPB][(NF == 2 && EXT) ? fold2_words(kFoldRowsExt) : (NC + 2) * 64];
+  __shared__ long long sfold[WPB][(NF == 2) ? (EXT ? fold2_words(kFoldRowsExt) : 1) : 256];
   __shared__ double s_sct[kSinCosTab];   // sin/cos constants of the two-flavour rotations
   // extended two-flavour model: each wave's row-constant table
   __shared__ double srt[(NF == 2 && EXT) ? WPB : 1][(NF == 2 && EXT) ? kGroup2 * kRowC : 1];
@@ -1556,7 +1564,7 @@ __global__ void __launch_bounds__(kBlock) k_adaptive(StepArgs a) {
   __shared__ double sE[1];
   __shared__ RedLds<NV, kBlock, true> R;
   __shared__ double snn_all[kBlock / 64][48];   // row constants, then the first row's geometry
-  __shared__ long long sfold[kBlock / 64][(NC + 2) * 64];
+  __shared__ long long sfold[kBlock / 64][(NF == 2) ? 1 : 64];
   __shared__ double s_sct[kSinCosTab];   // sin/cos constants of the two-flavour rotations
   extern __shared__ __align__(16) double dyn_tab[];
   // the wavefront index as a wave-uniform (scalar) value: the row indices, their divisions
@@ -1719,11 +1727,13 @@ __device__ bool grid_barrier(const BatchArgs& a, unsigned epoch) {
 constexpr int kGroup = 16;
 template <int KIND>
 __device__ void batch_stage(const BatchArgs& a, long long n, unsigned epoch, long long r0w,
-                            long long r1w, int lane, double (*Jv)[6], long long* fl, double* cb,
-                            double* rt, const double* sct, int& err) {
+                            long long r1w, int lane, double (*Jv)[6], double* cb, double* rt,
+                            const double* sct, int& err) {
   const double r0 = a.rs + (double)n * a.h;
   const double rm = r0 + 0.5 * a.h;
   const double r1 = a.rs + (double)(n + 1) * a.h;
+  // the moment component of the lane's total (J0 | J1), or -1
+  const int tv = (fold_moment<3>(lane) < 2 && fold_comp<3>(lane) < 3) ? fold_moment<3>(lane) * 3 + fold_comp<3>(lane) : -1;
   // epoch of the slot holding J^(i+1) of this step: epoch - KIND + i
   int m = -1;
   long long mrow0 = 0, mrow1 = 0, mbeam0 = 0, mtab0 = 0;
@@ -1732,7 +1742,7 @@ __device__ void batch_stage(const BatchArgs& a, long long n, unsigned epoch, lon
   I128 T = i128_zero();
   for (long long row = r0w; row < r1w;) {
     if (m < 0 || row >= mrow1) {
-      if (m >= 0 && lane < 6) acc_add(acc_slot(a, epoch, m) + lane * kAccLimbs, T);
+      if (m >= 0 && tv >= 0) acc_add(acc_slot(a, epoch, m) + tv * kAccLimbs, T);
       T = i128_zero();
       if (m < 0) {                      // first model of the range: binary search
         int lo = 0, hi = a.nmodels - 1;
@@ -1780,7 +1790,7 @@ __device__ void batch_stage(const BatchArgs& a, long long n, unsigned epoch, lon
     __asm__ volatile("" ::: "memory");
     if (mNE <= kGroupMaxNE) {
       group2<KIND, false, kFoldRowsBatch>(a.X, a.plane, mbeam0 + (row - mrow0) * mNE, mNE, gn, a.tab + mtab0, cb, rt,
-                          a.renorm, lane, fl, T, err, sct);
+                          a.renorm, lane, nullptr, T, err, sct);
       row += gn;
     } else {
       for (int i = 0; i < gn; ++i, ++row) {
@@ -1788,12 +1798,12 @@ __device__ void batch_stage(const BatchArgs& a, long long n, unsigned epoch, lon
         const int s = (int)(lr / mNU);
         double enone = 0.0;
         row2<KIND, false, false, true>(a.X, a.X, a.plane, mbeam0 + lr * mNE, mNE, s, 0.0, a.h, a.tab + mtab0,
-                                       cb, J, a.renorm, lane, fl, T, err, enone, 0.0, 0.0, -1, false, sct,
+                                       cb, J, a.renorm, lane, T, err, enone, 0.0, 0.0, -1, false, sct,
                                        rt + i * kRowC);
       }
     }
   }
-  if (m >= 0 && lane < 6) acc_add(acc_slot(a, epoch, m) + lane * kAccLimbs, T);
+  if (m >= 0 && tv >= 0) acc_add(acc_slot(a, epoch, m) + tv * kAccLimbs, T);
   // clear the set the next epoch will collect into
   if (blockIdx.x == 0) {
     unsigned long long* z = a.acc + (size_t)((epoch + 1u) % kAccSets) * a.nmodels * 6 * kAccLimbs;
@@ -1813,8 +1823,6 @@ __device__ void batch_stage(const BatchArgs& a, long long n, unsigned epoch, lon
 template <int BS>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) k_batch2(BatchArgs a) {
   __shared__ double sJw[BS / 64][4][6];
-  // (fold2_words(R) also covers row2's fold_segment<3>: 3 * 64 + 63 words)
-  __shared__ long long sfold[BS / 64][fold2_words(kFoldRowsBatch)];
   __shared__ double scb[BS / 64][kC2Size];
   __shared__ double srt[BS / 64][kGroup * kRowC];   // each wave's row-constant table
   __shared__ double s_sct[kSinCosTab];   // sin/cos constants of the rotations
@@ -1833,16 +1841,16 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
   unsigned epoch = 0;
   int err = 0;
   bool ok;
-  batch_stage<0>(a, step0, epoch, r0w, r1w, lane, Jv, sfold[wid], scb[wid], srt[wid], s_sct, err);
+  batch_stage<0>(a, step0, epoch, r0w, r1w, lane, Jv, scb[wid], srt[wid], s_sct, err);
   ok = grid_barrier(a, epoch++);
   for (long long n = step0; ok && n < step0 + nsteps; ++n) {
-    batch_stage<1>(a, n, epoch, r0w, r1w, lane, Jv, sfold[wid], scb[wid], srt[wid], s_sct, err);
+    batch_stage<1>(a, n, epoch, r0w, r1w, lane, Jv, scb[wid], srt[wid], s_sct, err);
     if (!(ok = grid_barrier(a, epoch++))) break;
-    batch_stage<2>(a, n, epoch, r0w, r1w, lane, Jv, sfold[wid], scb[wid], srt[wid], s_sct, err);
+    batch_stage<2>(a, n, epoch, r0w, r1w, lane, Jv, scb[wid], srt[wid], s_sct, err);
     if (!(ok = grid_barrier(a, epoch++))) break;
-    batch_stage<3>(a, n, epoch, r0w, r1w, lane, Jv, sfold[wid], scb[wid], srt[wid], s_sct, err);
+    batch_stage<3>(a, n, epoch, r0w, r1w, lane, Jv, scb[wid], srt[wid], s_sct, err);
     if (!(ok = grid_barrier(a, epoch++))) break;
-    batch_stage<4>(a, n, epoch, r0w, r1w, lane, Jv, sfold[wid], scb[wid], srt[wid], s_sct, err);
+    batch_stage<4>(a, n, epoch, r0w, r1w, lane, Jv, scb[wid], srt[wid], s_sct, err);
     ok = grid_barrier(a, epoch++);
   }
   if (err) __hip_atomic_fetch_or(a.sync + kSyncStatus, (unsigned)err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

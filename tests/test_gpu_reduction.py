@@ -45,3 +45,17 @@ def test_adaptive_grid_sizes(nb, oracle, n_u):
     so = o.run_adaptive(1e-7)
     assert (st["accepted"], st["rejected"]) == (so["accepted"], so["rejected"])
     np.testing.assert_array_equal(m.get_state().cpu().numpy(), o.get_state())
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(n_phi=3)], ids=["bulb", "extended"])
+@pytest.mark.parametrize("nf", [2, 3])
+@pytest.mark.parametrize("n_energy", [1, 63, 64, 65, 1984, 1985, 2048, 2049, 4100])
+def test_row_lengths(nb, oracle, nf, n_energy, kw):
+    """Row sums at the edges of the lane chunks and of the 2048-energy row segments."""
+    d = dict(workloads.small_params(n_flavor=nf, n_energy=n_energy, n_u=3, n_steps=3), **kw)
+    print(f"row fold: {nf} flavours, {n_energy} energies, {kw}", flush=True)
+    m = nb.Model(d)
+    m.run()
+    o = oracle.Model(d)
+    o.run()
+    np.testing.assert_array_equal(m.get_state().cpu().numpy(), o.get_state())
