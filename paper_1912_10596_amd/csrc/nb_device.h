@@ -92,6 +92,38 @@ __device__ __forceinline__ void sincos_tab(double x, const double* c, double& sn
   cs = ((quad + 1) & 2) ? -b : b;
 }
 
+// ------------------------------------------------- square root and division in range
+// The steps of the IEEE correctly rounded operations without their scaling and special
+// cases, for operands whose exponents leave room (each caller says why they do): the same
+// results with about a third fewer instructions.
+// sqrt(x), 2^-767 <= x < 2^1022: rsq refined by Goldschmidt steps.  h is left at
+// 1 / (2 sqrt(x)) to about 2^-50.
+__device__ __forceinline__ double sqrt_in_range(double x, double& h) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y;
+  h = 0.5 * y;
+  const double e = fma(-h, g, 0.5);
+  h = fma(h, e, h);
+  g = fma(g, e, g);
+  g = fma(fma(-g, g, x), h, g);
+  return fma(fma(-g, g, x), h, g);
+}
+// a / b from r = 1/b to rounding: the quotient's residual is exact, so its correction rounds
+// correctly.  2^-500 <= |b| <= 2^500, and a zero or as large (a = -0 gives +0).
+__device__ __forceinline__ double div_by_rcp(double a, double b, double r) {
+  const double q = a * r;
+  return fma(fma(-b, q, a), r, q);
+}
+__device__ __forceinline__ double rcp_step(double b, double r) { return fma(r, fma(-b, r, 1.0), r); }
+__device__ __forceinline__ double div_in_range(double a, double b) {
+  return div_by_rcp(a, b, rcp_step(b, rcp_step(b, __builtin_amdgcn_rcp(b))));
+}
+// a / g with g = sqrt(x) of any x > 0 (so 2^-537 <= g) and h = 1 / (2 g) to about 2^-50, as
+// sqrt_in_range leaves it: one step from 2 h takes the place of a reciprocal and two.
+__device__ __forceinline__ double div_by_sqrt(double a, double g, double h) {
+  return div_by_rcp(a, g, rcp_step(g, h + h));
+}
+
 // ------------------------------------------------------------- fixed point
 // 128-bit two's complement integer held as two 64-bit halves.
 struct I128 {
@@ -210,6 +242,9 @@ __device__ __forceinline__ double cnorm2v(const cplx v[3]) {
 // 2x2 exponential of Eq. U:
 //   psi' = e^{-i (l1 - hm)} (v1^+ psi) v1 + cos(th) P psi - i sin(th)/th (K0 - hm) P psi,
 // P = I - v1 v1^+, th = |(K0 - hm) w| / |w| for any w in the plane, here w = P psi.
+// The Halley quotients and 1/|c|^2 are the in-range forms: with p > 2^-200 the quotients'
+// operands are zero or above 2^-650 (an exact fma cannot cancel below 2^-106 of its terms) and
+// |c|^2 is above 2^-404.
 // Nothing is normalised: (v1^+ psi) v1 = al c with al = (c^+ psi) / |c|^2.  The magnitudes
 // then grow like |K0|^5; with the sin/cos reduction (phases below 2^50) the form holds for
 // 2^-100 < |K0| < 1e15; |K0|^2 / 2 <= 2^-200 is taken as K0 = 0 (error below 1e-30).
@@ -249,7 +284,7 @@ __device__ __forceinline__ void exp3_apply(const Herm3& K, cplx psi[3]) {
     const double fv = fma(lam, l2 - p, -qa);
     const double dv = fma(3.0, l2, -p);
     const double den = fma(dv, dv, -((3.0 * lam) * fv));
-    lam = lam - (fv * dv) / den;
+    lam = lam - div_in_range(fv * dv, den);
   }
   const double l1 = sg * lam;
   // eigenvector c: the column of adj(K0 - l1) = mu v1 v1^+ (mu > 0) with the largest
@@ -276,7 +311,7 @@ __device__ __forceinline__ void exp3_apply(const Herm3& K, cplx psi[3]) {
   if (!(nb > 0.0)) return;
   const double hm = -0.5 * l1;
   const double d0 = a0 - hm, d1 = a1 - hm, d2 = a2 - hm;
-  const cplx al = rmul(1.0 / nb, dotc(best, psi));   // (v1^+ psi) v1 = al c
+  const cplx al = rmul(div_in_range(1.0, nb), dotc(best, psi));   // (v1^+ psi) v1 = al c
   cplx pp[3], kp[3];
 #pragma unroll
   for (int c = 0; c < 3; ++c)   // P psi = psi - al c
@@ -285,12 +320,18 @@ __device__ __forceinline__ void exp3_apply(const Herm3& K, cplx psi[3]) {
   k0_minus(pp, d0, d1, d2, x, y, z, kp);
   // (K0 - hm)^2 = th^2 on the plane: th = |(K0 - hm) P psi| / |P psi| (0 for P psi = 0)
   const double npp = cnorm2v(pp);
-  const double th = (npp > 0.0) ? sqrt(cnorm2v(kp) / npp) : 0.0;
+  const double th2 = cnorm2v(kp) / npp;
+  double ih;
+  double th = sqrt_in_range(th2, ih);
+  if (!(th2 >= 0x1p-767)) {   // tiny, zero or no P psi (rare)
+    th = (npp > 0.0) ? sqrt(th2) : 0.0;
+    ih = 0.5 / th;
+  }
   const double phi = l1 - hm;
   double sp, cp, st, ct;
   sincos_nb(phi, sp, cp);
   sincos_nb(th, st, ct);
-  const double sc = (th > 0.0) ? st / th : 1.0;
+  const double sc = (th > 0.0) ? div_by_sqrt(st, th, ih) : 1.0;
   const cplx ap = cmul(al, mk(cp, -sp));
 #pragma unroll
   for (int c = 0; c < 3; ++c)   // ap c + cos(th) P psi - i sin(th)/th (K0 - hm) P psi
@@ -306,12 +347,16 @@ __device__ __forceinline__ void rotate2(const double x0, const double x1, const 
                                         double& P0, double& P1, double& P2,
                                         const double* tab = nullptr) {
   const double t2 = (x0 * x0 + x1 * x1) + x2 * x2;
-  const double th = sqrt(t2);
-  if (th == 0.0) return;
-  double s, c;
+  double ih, s, c;
+  double th = sqrt_in_range(t2, ih);
+  if (!(t2 >= 0x1p-767)) {   // tiny or zero (rare)
+    th = sqrt(t2);
+    if (th == 0.0) return;
+    ih = 0.5 / th;
+  }
   if constexpr (TAB) sincos_tab(0.5 * th, tab, s, c);
   else sincos_nb(0.5 * th, s, c);
-  const double k = s / th;
+  const double k = div_by_sqrt(s, th, ih);
   const double v0 = x0 * k, v1 = x1 * k, v2 = x2 * k;
   double t0 = v1 * P2 - v2 * P1;
   double t1 = v2 * P0 - v0 * P2;
