@@ -109,12 +109,18 @@ __device__ __forceinline__ void red_init(RedLds<NV, BS, MAXE>& R) {   // then a 
 // own, of the region of the epoch's parity, and takes the maximum over all blocks' words
 // (block b writes its word of parity e % 2 at epoch e only after barrier e - 1, when every
 // block has read all words of epoch e - 2).
+// overlap: work of every thread that does not need the moments, run between the publication
+// and the poll.
 // BS: threads per block (the launch's block size).
 // (always inlined: a call would take the address of the launch arguments and make the
 // compiler keep a private copy of them)
-template <bool MAXE, int NM, int NV, int BS, bool RM>
+struct NoOverlap {
+  __device__ __forceinline__ void operator()() const {}
+};
+template <bool MAXE, int NM, int NV, int BS, bool RM, typename OV = NoOverlap>
 __device__ __forceinline__ bool finish_stage(const StepArgs& a, unsigned epoch, I128 T, RedLds<NV, BS, RM>& R,
-                                             double* sJ, double emax = 0.0, double* sE = nullptr) {
+                                             double* sJ, OV overlap = OV{}, double emax = 0.0,
+                                             double* sE = nullptr) {
   constexpr int WPB = BS / 64;
   constexpr int W = 2 * NV;   // words per copy
   static_assert(W <= kRedStride && W <= BS, "too many words");
@@ -144,12 +150,6 @@ __device__ __forceinline__ bool finish_stage(const StepArgs& a, unsigned epoch, 
 #pragma unroll
     for (int w = 1; w < WPB; ++w) f = max(f, R.swm[w]);
   }
-  if (gridDim.x == 1) {
-    if (tid < W && !(tid & 1)) sJ[tid >> 1] = i128_to_double(blk) * scale(tid >> 1);
-    if (MAXE && tid == 0) *sE = as_double(f << 16);
-    __syncthreads();
-    return true;
-  }
   unsigned long long* red = reinterpret_cast<unsigned long long*>(a.sync + kSyncRed);
   unsigned long long* pub =
       reinterpret_cast<unsigned long long*>(a.sync + kSyncPub) + (size_t)(epoch & 1u) * kRedCopies * kRedStride;
@@ -157,7 +157,7 @@ __device__ __forceinline__ bool finish_stage(const StepArgs& a, unsigned epoch, 
   const unsigned long long tag16 = (epoch + 1u) & 0xffffu;
   unsigned long long* ew =
       reinterpret_cast<unsigned long long*>(a.sync + kSyncErr) + (size_t)(epoch & 1u) * kMaxBlocks;
-  if (tid < W) {
+  if (tid < W && gridDim.x > 1) {
     const unsigned me = blockIdx.x % kRedCopies;
     const unsigned nc = (gridDim.x + (kRedCopies - 1) - me) / kRedCopies;   // blocks of the copy
     const unsigned long long add = chunk_field(blk, tid & 1) << 9;
@@ -177,8 +177,15 @@ __device__ __forceinline__ bool finish_stage(const StepArgs& a, unsigned epoch, 
       __hip_atomic_store(pub + me * kRedStride + tid, (sum & ~kTag9) | tag, __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (MAXE && tid == 0)
+  if (MAXE && tid == 0 && gridDim.x > 1)
     __hip_atomic_store(ew + blockIdx.x, (tag16 << 48) | f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  overlap();
+  if (gridDim.x == 1) {
+    if (tid < W && !(tid & 1)) sJ[tid >> 1] = i128_to_double(blk) * scale(tid >> 1);
+    if (MAXE && tid == 0) *sE = as_double(f << 16);
+    __syncthreads();
+    return true;
+  }
   int ok = 1;
   const unsigned long long t0 = wall_clock64();
   // thread i: copy i % 8 of word i / 8 (the 8 copies of a word in 8 consecutive lanes, the
@@ -354,16 +361,12 @@ __device__ __forceinline__ void stage_geo(double u, double h, const Radial& g0, 
 }
 
 // ----------------------------------------------------------------- two flavours
-// Every two-flavour stage keeps its stage-wide and per-row constants in a per-wavefront LDS
-// block, written by lane 0 and re-read where they are used, so that the beam loop holds
-// only per-beam values in registers (which lets four wavefronts share a SIMD):
+// Every two-flavour step keeps its radial profiles and scales in a per-wavefront LDS block, and
+// its rows' constants in a per-wavefront LDS table, re-read where they are used, so that
+// the beam loop holds only per-beam values in registers:
 constexpr int kC2Rad = 0;    // q2, lam, mu at the stage radii r0, rm, r1 (9)
 constexpr int kC2Sc = 9;     // fixed-point scales s1, s0, p2e1, p2e0 (4)
-constexpr int kC2Row = 13;   // generator i = 1..4: h/cos, lam, nu-nu term (3): 5 each (20);
-                             // then 1/cos at the moments' radius and the azimuthal factors (3)
-constexpr int kC2Geo = 36;   // the wavefront's first row's stage geometry (11, stage_geo)
-constexpr int kC2Size = 48;
-// Stage-wide constants: the radial profiles at the three stage radii and the scales.
+constexpr int kC2Size = 14;
 __device__ __forceinline__ void put_stage2(double* cb, int lane, const Radial& g0, const Radial& gm,
                                            const Radial& g1, const Scales& sc) {
   if (lane == 0) {
@@ -374,84 +377,131 @@ __device__ __forceinline__ void put_stage2(double* cb, int lane, const Radial& g
   }
   __asm__ volatile("" ::: "memory");   // the wave's LDS operations complete in program order
 }
-// Stage generator i of beam (bx, bz) from its row constants c = [h/cos, lam, nu-nu term]
-// (the arithmetic of gen2).
-__device__ __forceinline__ void gen2c(int an, double bx, double bz, const double* c, double f[3]) {
-  const double nn[3] = {c[2], c[3], c[4]};
-  gen2(an, bx, bz, c[1], nn, c[0], f);
+// A row's constants rc, the same for every beam of the row:
+//   rc[5 (i - 1) ...]  stage generator i = 1..4: h/cos, sg lam, and the nu-nu term (sg n_x,
+//                      n_y, sg n_z), with sg = -1 for antineutrino rows (B_vac - lam e_z -
+//                      nn^*), so that the generator needs no selection by species
+//   rc[20]             1/cos at the moments' radius; rc[21..22] the extended model's
+//                      azimuthal factors
+//   rc[kRowS], rc[kRowA]  species row, sg
+constexpr int kRowS = 23, kRowA = 24;
+constexpr int kRowC = 26;    // doubles per block of a row group's table (25 used)
+// Rows whose constants a wavefront of the bulb model keeps through a step (kRowP doubles
+// each): also cos at the three stage radii, 1/cos at rm and r1, and u.
+constexpr int kRowCos = 25, kRowIcm = 28, kRowIc1 = 29, kRowU = 30, kRowP = 33, kRowKeep = 16;
+// Stage generator of beam (bx, bz) from its block c = [h/cos, sg lam, nu-nu term] (the
+// arithmetic of gen2: subtracting a term is adding its negative).
+__device__ __forceinline__ void gen2c(double bx, double bz, const double* c, double f[3]) {
+  const double B0 = bx + c[2], B1 = c[3], B2 = (bz + c[1]) + c[4];
+  f[0] = c[0] * B0;
+  f[1] = c[0] * B1;
+  f[2] = c[0] * B2;
+}
+__device__ __forceinline__ void put_gen2(double* c, double hc, double sg, double lam, const double* n) {
+  c[0] = hc; c[1] = sg * lam; c[2] = sg * n[0]; c[3] = n[1]; c[4] = sg * n[2];
 }
 
-// The constants of one row for a stage (the arithmetic every beam of the row shares):
-// rc[5 (i - 1) ...] = h/cos, lam and the nu-nu term (3) of stage generator i, then rc[20] =
-// 1/cos at the moments' radius and rc[21..22] the extended model's azimuthal factors.
-// gcache: the wavefront's first-row geometry slot (or nullptr).  Values are written to rc
-// only where write is true.
+// All the constants of one row for a stage (a wavefront with more rows than it keeps, the
+// extended model and batches: lane l of a row group computes row l's).
 template <int KIND, bool EXT>
-__device__ __forceinline__ void row_setup2(double u, double h, double* cb, const double* const* J,
-                                           double cp, double sp, double* gcache, bool write, double* rc) {
+__device__ __forceinline__ void row_setup2(double u, double h, const double* cb, const double* const* J,
+                                           double cp, double sp, int s, double sg, double* rc) {
   const Radial g0{cb[kC2Rad + 0], cb[kC2Rad + 1], cb[kC2Rad + 2], 0.0};
   const Radial gm{cb[kC2Rad + 3], cb[kC2Rad + 4], cb[kC2Rad + 5], 0.0};
   const Radial g1{cb[kC2Rad + 6], cb[kC2Rad + 7], cb[kC2Rad + 8], 0.0};
   RowGeo rg;
   double icmom, sn0, snm, sn1;
-  stage_geo<KIND, EXT>(u, h, g0, gm, g1, gcache, rg, icmom, sn0, snm, sn1);
+  stage_geo<KIND, EXT>(u, h, g0, gm, g1, nullptr, rg, icmom, sn0, snm, sn1);
   double n[3];
   if (KIND == 1 || KIND == 2 || KIND == 4) {
     nunu_row<3, EXT>(J[0], g0.mu, rg.c0, sn0, cp, sp, n);
-    if (write) { rc[0] = rg.hc0; rc[1] = g0.lam; rc[2] = n[0]; rc[3] = n[1]; rc[4] = n[2]; }
+    put_gen2(rc, rg.hc0, sg, g0.lam, n);
   }
   if (KIND == 2 || KIND == 4) {
     nunu_row<3, EXT>(J[1], gm.mu, rg.cm, snm, cp, sp, n);
-    if (write) { rc[5] = rg.hcm; rc[6] = gm.lam; rc[7] = n[0]; rc[8] = n[1]; rc[9] = n[2]; }
+    put_gen2(rc + 5, rg.hcm, sg, gm.lam, n);
   }
   if (KIND >= 3) {
     nunu_row<3, EXT>(J[2], gm.mu, rg.cm, snm, cp, sp, n);
-    if (write) { rc[10] = rg.hcm; rc[11] = gm.lam; rc[12] = n[0]; rc[13] = n[1]; rc[14] = n[2]; }
+    put_gen2(rc + 10, rg.hcm, sg, gm.lam, n);
   }
   if (KIND == 4) {
     nunu_row<3, EXT>(J[3], g1.mu, rg.c1, sn1, cp, sp, n);
-    if (write) { rc[15] = rg.hc1; rc[16] = g1.lam; rc[17] = n[0]; rc[18] = n[1]; rc[19] = n[2]; }
+    put_gen2(rc + 15, rg.hc1, sg, g1.lam, n);
   }
   const double snmom = (KIND == 0) ? sn0 : ((KIND <= 2) ? snm : sn1);
-  if (write) { rc[20] = icmom; rc[21] = (snmom * icmom) * cp; rc[22] = (snmom * icmom) * sp; }
+  rc[20] = icmom; rc[21] = (snmom * icmom) * cp; rc[22] = (snmom * icmom) * sp;
+  rc[kRowS] = (double)s;
+  rc[kRowA] = sg;
 }
-constexpr int kRowC = 26;    // doubles per row-constant block (25 used)
 
-// Stage stencil for one (species s, emission bin u) row of NE beams starting at beam rb.
+// Kept rows (bulb model, at most kRowKeep rows per wavefront): the step's geometry, the same
+// for its four stages, is computed lane-parallel (lane l: the wavefront's row l) while the
+// wavefront waits at the barrier before the step, and each stage adds only the nu-nu term of
+// the newest moments.  Every value is the one row_setup2 computes.  (The set-up of a stage,
+// radial profiles included, was 1800-3200 cycles between the barrier and the first beam, of
+// about 13000 per stage for a model of one block; it is now the nu-nu term, about 350.)
+__device__ __forceinline__ void keep_geo2(const double* cb, double h, int lane, int nrw, double* rt) {
+  if (lane < nrw) {
+    double* rc = rt + lane * kRowP;
+    const Radial g0{cb[kC2Rad + 0], 0.0, 0.0, 0.0}, gm{cb[kC2Rad + 3], 0.0, 0.0, 0.0}, g1{cb[kC2Rad + 6], 0.0, 0.0, 0.0};
+    const RowGeo rg = row_geo(rc[kRowU], h, g0, gm, g1);
+    const double sg = rc[kRowA];
+    rc[0] = rg.hc0; rc[1] = sg * cb[kC2Rad + 1];
+    rc[5] = rg.hcm; rc[6] = sg * cb[kC2Rad + 4];
+    rc[10] = rg.hcm; rc[11] = sg * cb[kC2Rad + 4];
+    rc[15] = rg.hc1; rc[16] = sg * cb[kC2Rad + 7];
+    rc[kRowCos] = rg.c0; rc[kRowCos + 1] = rg.cm; rc[kRowCos + 2] = rg.c1;
+    rc[kRowIcm] = 1.0 / rg.cm;
+    rc[kRowIc1] = 1.0 / rg.c1;
+  }
+  __asm__ volatile("" ::: "memory");
+}
+template <int KIND>
+__device__ __forceinline__ void keep_nunu2(const double* cb, const double (*sJ)[6], int lane, int nrw, double* rt) {
+  if (lane < nrw) {
+    double* rc = rt + lane * kRowP;
+    if (KIND == 0) {
+      rc[20] = 1.0 / rc[kRowCos];
+    } else {
+      constexpr int at = (KIND == 1) ? 0 : ((KIND == 4) ? 2 : 1);   // the newest moments' radius
+      const double* J = sJ[KIND == 0 ? 0 : KIND - 1];
+      double n[3];
+      nunu<3>(J, cb[kC2Rad + 3 * at + 2], rc[kRowCos + at], n);
+      double* c = rc + 5 * (KIND == 0 ? 0 : KIND - 1);
+      const double sg = rc[kRowA];
+      c[2] = sg * n[0]; c[3] = n[1]; c[4] = sg * n[2];
+      if (KIND == 1) rc[20] = rc[kRowIcm];
+      if (KIND == 3) rc[20] = rc[kRowIc1];
+    }
+  }
+  __asm__ volatile("" ::: "memory");
+}
+
+// Stage stencil for one row of NE beams starting at beam rb, with its constants at rc.
 // KIND: 0 moments of rho_n at r_n; 1 stage Y2 (moments at r_n + h/2); 2 stage Y3
 // (r_n + h/2); 3 stage Y4 (r_{n+1}); 4 final update, store and moments at r_{n+1}.
-// J[i]: stage moments J^(i+1) (J0 | J1, 6 doubles).  A lane adds the fixed-point
-// contributions of up to 32 of its beams in 64-bit integers (each below 2^51) before they
-// are folded into exact 128-bit wave sums; a beam whose state has squared norm 2 or more
-// (NaN included) sets err.  cb: the wavefront's constant block (put_stage2 written).
+// A lane adds the fixed-point contributions of up to 32 of its beams in 64-bit integers
+// (each below 2^51) before they are folded into exact 128-bit wave sums; a beam whose state
+// has squared norm 2 or more (NaN included) sets err.
 // ADAPT (final update only): the new state goes to Xo instead of X, and emax keeps the
 // largest embedded error estimate |Theta - f2|^2 of the lane's beams.
-// EXT: extended bulb model, azimuth (cp, sp) = (cos, sin) of the row's azimuthal bin.
-// geo: this row is the wavefront's first (its stage geometry is cached across stages).
-// PRE: the row's constants were computed beforehand (row_setup2) and sit at rcp.
-template <int KIND, bool ADAPT = false, bool EXT = false, bool PRE = false>
+// EXT: extended bulb model.  pre: the lane's first beam, if it was loaded before.
+// sct: the block's sin/cos constants (sincos_coefs, in LDS).
+template <int KIND, bool ADAPT = false, bool EXT = false>
 __device__ __forceinline__ void row2(const double* X, double* Xo, long long plane, long long rb, int NE,
-                                     int s, double u, double h, const double* tab, double* cb,
-                                     const double* const* J, int renorm, int lane, I128& T,
-                                     int& err, double& emax, double cp = 0.0, double sp = 0.0,
-                                     int an = -1, bool geo = false, const double* sct = nullptr,
-                                     double* rcp = nullptr) {
-  // sct: the block's sin/cos constants (sincos_coefs, in LDS)
+                                     const double* tab, const double* cb, const double* rc, int renorm, int lane,
+                                     I128& T, int& err, double& emax, const double* sct,
+                                     const double* pre = nullptr) {
   constexpr int NM = EXT ? 4 : 2;
-  // the lane's first beam of the row, loaded before the row set-up so that the set-up
-  // arithmetic overlaps the load
   double q0 = 0.0, q1 = 0.0, q2 = 0.0;
-  if (lane < NE) {
+  if (pre) {
+    q0 = pre[0]; q1 = pre[1]; q2 = pre[2];
+  } else if (lane < NE) {
     q0 = X[rb + lane]; q1 = X[rb + lane + plane]; q2 = X[rb + lane + 2 * plane];
   }
-  // species row s, antiparticle flag an (default: s itself, two tracked species)
-  if (an < 0) an = s;
-  double* rc = PRE ? rcp : cb + kC2Row;
-  __asm__ volatile("" ::: "memory");   // stage constants re-read from LDS for every row
-  if constexpr (!PRE)
-    row_setup2<KIND, EXT>(u, h, cb, J, cp, sp, geo ? cb + kC2Geo : nullptr, lane == 0, rc);
-  __asm__ volatile("" ::: "memory");
-  const double* G = tab + (size_t)(2 + s) * NE;
+  const double* G = tab + (size_t)(2 + (int)rc[kRowS]) * NE;
+  const double sg = rc[kRowA];
   I128 mine = i128_zero();
   for (int k0 = lane; k0 - lane < NE; k0 += 64 * 32) {
     const int kend = min(NE, k0 + 64 * 32);
@@ -469,23 +519,23 @@ __device__ __forceinline__ void row2(const double* X, double* Xo, long long plan
       if (KIND >= 1) {
         const double bx = tab[k], bz = tab[NE + k];
         double f1[3], f2[3], f3[3], f4[3];
-        if (KIND != 3) gen2c(an, bx, bz, rc + 0, f1);
+        if (KIND != 3) gen2c(bx, bz, rc + 0, f1);
         if (KIND == 1) {
           rotate2<true>(0.5 * f1[0], 0.5 * f1[1], 0.5 * f1[2], P0, P1, P2, sct);
         } else if (KIND == 2) {
-          gen2c(an, bx, bz, rc + 5, f2);
+          gen2c(bx, bz, rc + 5, f2);
           const double cr0 = f1[1] * f2[2] - f1[2] * f2[1];
           const double cr1 = f1[2] * f2[0] - f1[0] * f2[2];
           const double cr2 = f1[0] * f2[1] - f1[1] * f2[0];
           rotate2<true>(0.5 * f2[0] - 0.125 * cr0, 0.5 * f2[1] - 0.125 * cr1, 0.5 * f2[2] - 0.125 * cr2,
                   P0, P1, P2, sct);
         } else if (KIND == 3) {
-          gen2c(an, bx, bz, rc + 10, f3);
+          gen2c(bx, bz, rc + 10, f3);
           rotate2<true>(f3[0], f3[1], f3[2], P0, P1, P2, sct);
         } else {
-          gen2c(an, bx, bz, rc + 5, f2);
-          gen2c(an, bx, bz, rc + 10, f3);
-          gen2c(an, bx, bz, rc + 15, f4);
+          gen2c(bx, bz, rc + 5, f2);
+          gen2c(bx, bz, rc + 10, f3);
+          gen2c(bx, bz, rc + 15, f4);
           const double cr0 = f1[1] * f4[2] - f1[2] * f4[1];
           const double cr1 = f1[2] * f4[0] - f1[0] * f4[2];
           const double cr2 = f1[0] * f4[1] - f1[1] * f4[0];
@@ -514,7 +564,7 @@ __device__ __forceinline__ void row2(const double* X, double* Xo, long long plan
       // rho~: rho for neutrinos, -rho^* (Bloch (-x, y, -z)) for antineutrinos
       if (!(fma(P0, P0, fma(P1, P1, P2 * P2)) < 2.0)) err |= 1;
       const double ws = G[k] * cb[kC2Sc + 0];
-      const double wa = an ? -ws : ws;
+      const double wa = sg * ws;
       acc[0] += fix_bits(P0, wa);
       acc[1] += fix_bits(P1, ws);
       acc[2] += fix_bits(P2, wa);
@@ -530,13 +580,12 @@ __device__ __forceinline__ void row2(const double* X, double* Xo, long long plan
 // A group of gn rows of one model whose beams are contiguous from beam gb0 (NE energies a
 // row), streamed as full 64-lane chunks: lane l of chunk c takes the group's beam
 // f = 64 c + l, row i = f / NE, energy k = f - i NE, and reads its row's constants from the
-// group table rt (row i's block; [kRowS] = species row, [kRowA] = antiparticle flag).  The
+// group table rt (row i's block).  The
 // last chunk of one row and the first of the next share a wavefront instead of leaving
 // lanes idle.  A row's exact sum is folded in the chunk where the row ends (its lanes fold,
 // the others go on with the next row), so every row adds the same integer sum as in row2
 // and the moments keep their bits.  A lane adds at most ceil(NE / 64) + 1 contributions
 // to a row, so with NE <= kGroupMaxNE its 64-bit sums stay below 2^56 as wave_fold needs.
-constexpr int kRowS = 23, kRowA = 24;
 constexpr int kGroupMaxNE = 64 * 31;
 // Rows folded together by group2.  The extended model's rows (100 energies) end in most
 // chunks, so its wavefront stages ended rows in LDS and folds and closes four at a time (20M
@@ -597,7 +646,7 @@ __device__ __forceinline__ void fold_rows2(int lane, long long* fl, int nrows, c
 
 template <int KIND, bool EXT, int R>
 __device__ __forceinline__ void group2(double* X, long long plane, long long gb0, int NE, int gn,
-                                       const double* tab, double* cb, const double* rt, int renorm,
+                                       const double* tab, const double* cb, const double* rt, int renorm,
                                        int lane, long long* fl, I128& T, int& err, const double* sct) {
   constexpr int NM = EXT ? 4 : 2;
   constexpr int NCR = 3 * R, S = fold2_stride(R);   // R > 1
@@ -644,27 +693,27 @@ __device__ __forceinline__ void group2(double* X, long long plane, long long gb0
     unsigned long long x0 = 0ull, x1 = 0ull, x2 = 0ull;
     if (on) {
       const double* rc = rt + i * kRowC;
-      const int sr = (int)rc[kRowS], an = (int)rc[kRowA];
+      const int sr = (int)rc[kRowS];
       if (KIND >= 1) {
         const double bx = PF ? bxc : tab[k], bz = PF ? bzc : tab[NE + k];
         double f1[3], f2[3], f3[3], f4[3];
-        if (KIND != 3) gen2c(an, bx, bz, rc + 0, f1);
+        if (KIND != 3) gen2c(bx, bz, rc + 0, f1);
         if (KIND == 1) {
           rotate2<true>(0.5 * f1[0], 0.5 * f1[1], 0.5 * f1[2], P0, P1, P2, sct);
         } else if (KIND == 2) {
-          gen2c(an, bx, bz, rc + 5, f2);
+          gen2c(bx, bz, rc + 5, f2);
           const double cr0 = f1[1] * f2[2] - f1[2] * f2[1];
           const double cr1 = f1[2] * f2[0] - f1[0] * f2[2];
           const double cr2 = f1[0] * f2[1] - f1[1] * f2[0];
           rotate2<true>(0.5 * f2[0] - 0.125 * cr0, 0.5 * f2[1] - 0.125 * cr1, 0.5 * f2[2] - 0.125 * cr2,
                         P0, P1, P2, sct);
         } else if (KIND == 3) {
-          gen2c(an, bx, bz, rc + 10, f3);
+          gen2c(bx, bz, rc + 10, f3);
           rotate2<true>(f3[0], f3[1], f3[2], P0, P1, P2, sct);
         } else {
-          gen2c(an, bx, bz, rc + 5, f2);
-          gen2c(an, bx, bz, rc + 10, f3);
-          gen2c(an, bx, bz, rc + 15, f4);
+          gen2c(bx, bz, rc + 5, f2);
+          gen2c(bx, bz, rc + 10, f3);
+          gen2c(bx, bz, rc + 15, f4);
           const double cr0 = f1[1] * f4[2] - f1[2] * f4[1];
           const double cr1 = f1[2] * f4[0] - f1[0] * f4[2];
           const double cr2 = f1[0] * f4[1] - f1[1] * f4[0];
@@ -688,7 +737,7 @@ __device__ __forceinline__ void group2(double* X, long long plane, long long gb0
       // rho~: rho for neutrinos, -rho^* (Bloch (-x, y, -z)) for antineutrinos
       if (!(fma(P0, P0, fma(P1, P1, P2 * P2)) < 2.0)) err |= 1;
       const double ws = (PF ? wsc : tab[(size_t)(2 + sr) * NE + k]) * cb[kC2Sc + 0];
-      const double wa = an ? -ws : ws;
+      const double wa = rc[kRowA] * ws;
       x0 = fix_bits(P0, wa);
       x1 = fix_bits(P1, ws);
       x2 = fix_bits(P2, wa);
@@ -753,27 +802,50 @@ __device__ __forceinline__ void group2(double* X, long long plane, long long gb0
   __asm__ volatile("" ::: "memory");
 }
 
-// rt (extended model): the wavefront's row-constant table of kGroup2 blocks of kRowC.
+// rt: the wavefront's row-constant table, kGroup2 blocks of kRowC doubles (extended model) or
+// kRowKeep of kRowP (bulb model, which keeps up to kRowKeep rows through a step).
 constexpr int kGroup2 = 16;
-template <int KIND, bool ADAPT = false, bool EXT = false>
-__device__ __forceinline__ void stage2(const StepArgs& a, const StepGeo& G, const double* X, double* Xo,
-                                       const double (*sJ)[EXT ? 12 : 6], const double* tab, long long gw,
-                                       long long nw, int lane, long long* fl, I128& T, int& err,
-                                       double& emax, double* cb, const double* sct, bool geo = false,
-                                       double* rt = nullptr) {
+constexpr int row_table2(bool ext) { return ext ? kGroup2 * kRowC : kRowKeep * kRowP; }
+// Rows gw, gw + nw, ... of nrow.
+__device__ __forceinline__ int wave_rows(long long gw, long long nw, long long nrow) {
+  return gw < nrow ? (int)((nrow - 1 - gw) / nw + 1) : 0;
+}
+// Once per launch: the labels of the bulb model's kept rows.
+__device__ __forceinline__ void keep_rows2(const StepArgs& a, long long gw, long long nw, int lane, int nrw, double* rt) {
+  if (nrw <= kRowKeep && lane < nrw) {
+    const long long row = gw + lane * nw;
+    const int s = (int)(row / a.NU);
+    rt[lane * kRowP + kRowU] = u_of((int)(row - (long long)s * a.NU), a.NU);
+    rt[lane * kRowP + kRowS] = (double)s;
+    rt[lane * kRowP + kRowA] = (s >= (a.NS >> 1)) ? -1.0 : 1.0;
+  }
+  __asm__ volatile("" ::: "memory");
+}
+// Before every step: its radial profiles, and the kept rows' geometry.
+template <bool EXT>
+__device__ __forceinline__ void prep2(const StepArgs& a, const StepGeo& G, int lane, int nrw, double* cb, double* rt) {
+  __asm__ volatile("" ::: "memory");
   put_stage2(cb, lane, radial_at(a, G.r0), radial_at(a, G.rm), radial_at(a, G.r1),
              Scales{a.s1, a.s0, a.p2e1, a.p2e0});
+  if (!EXT && nrw <= kRowKeep) keep_geo2(cb, G.h, lane, nrw, rt);
+}
+template <int KIND, bool ADAPT = false, bool EXT = false>
+__device__ __forceinline__ void stage2(const StepArgs& a, double h, const double* X, double* Xo,
+                                       const double (*sJ)[EXT ? 12 : 6], const double* tab, long long gw,
+                                       long long nw, int nrw, int lane, long long* fl, I128& T, int& err,
+                                       double& emax, const double* cb, const double* sct, double* rt,
+                                       const double* pre = nullptr) {
   const double* J[4] = {sJ[0], sJ[1], sJ[2], sJ[3]};
+  // (the launch arguments are read into locals first: the LDS-order barriers below would
+  // otherwise make the compiler re-read them from a private copy of the argument block)
+  const int NE = a.NE, NU = a.NU, NS = a.NS, renorm = a.renorm;
+  const long long plane = a.plane;
   if constexpr (EXT) {
     // rows (s, j, p): species, emission bin, azimuthal bin.  Each wavefront takes a
     // contiguous range of rows, in groups of up to kGroup2: lane l computes the constants of
     // the group's row l (row_setup2: geometry, nu-nu terms with the row's azimuth) into the
     // table rt, then the rows run one after the other.
-    // (the launch arguments are read into locals first: the LDS-order barriers below would
-    // otherwise make the compiler re-read them from a private copy of the argument block)
-    const int NE = a.NE, NU = a.NU, NP = a.NP, NS = a.NS, renorm = a.renorm;
-    const long long plane = a.plane;
-    const double h = G.h;
+    const int NP = a.NP;
     const double* phi = a.tab + (size_t)(2 + NS) * NE;
     const long long nrow = (long long)NS * NU * NP;
     const long long per = (nrow + nw - 1) / nw;
@@ -787,30 +859,38 @@ __device__ __forceinline__ void stage2(const StepArgs& a, const StepGeo& G, cons
         const int p = (int)(r - sj * NP);
         const int s = (int)(sj / NU);
         const int j = (int)(sj - (long long)s * NU);
-        row_setup2<KIND, true>(u_of(j, NU), h, cb, J, phi[p], phi[NP + p], nullptr, true, rt + lane * kRowC);
-        rt[lane * kRowC + kRowS] = (double)s;
-        rt[lane * kRowC + kRowA] = (double)(s >= (NS >> 1));
+        row_setup2<KIND, true>(u_of(j, NU), h, cb, J, phi[p], phi[NP + p], s, (s >= (NS >> 1)) ? -1.0 : 1.0,
+                               rt + lane * kRowC);
       }
       __asm__ volatile("" ::: "memory");
       if (!ADAPT && NE <= kGroupMaxNE) {
         group2<KIND, true, kFoldRowsExt>(Xo, plane, row * NE, NE, gn, tab, cb, rt, renorm, lane, fl, T, err, sct);
         row += gn;
       } else {
-        for (int i = 0; i < gn; ++i, ++row) {
-          const long long sj = row / NP;
-          const int s = (int)(sj / NU);
-          row2<KIND, ADAPT, true, true>(X, Xo, plane, row * NE, NE, s, 0.0, h, tab, cb, J, renorm, lane, T,
-                                        err, emax, 0.0, 0.0, s >= (NS >> 1), false, sct, rt + i * kRowC);
-        }
+        for (int i = 0; i < gn; ++i, ++row)
+          row2<KIND, ADAPT, true>(X, Xo, plane, row * NE, NE, tab, cb, rt + i * kRowC, renorm, lane, T, err, emax,
+                                  sct);
       }
     }
+  } else if (nrw <= kRowKeep) {
+    keep_nunu2<KIND>(cb, sJ, lane, nrw, rt);
+    for (int i = 0; i < nrw; ++i)
+      row2<KIND, ADAPT>(X, Xo, plane, (gw + i * nw) * NE, NE, tab, cb, rt + i * kRowP, renorm, lane, T, err, emax,
+                        sct, i == 0 ? pre : nullptr);
   } else {
-    const long long nrow = (long long)a.NS * a.NU;
-    for (long long row = gw; row < nrow; row += nw) {
-      const int s = (int)(row / a.NU);
-      const int j = (int)(row - (long long)s * a.NU);
-      row2<KIND, ADAPT>(X, Xo, a.plane, row * a.NE, a.NE, s, u_of(j, a.NU), G.h, tab, cb, J, a.renorm,
-                        lane, T, err, emax, 0.0, 0.0, s >= (a.NS >> 1), geo && row == gw, sct);
+    for (int r0 = 0; r0 < nrw; r0 += kRowKeep) {
+      const int gn = min(nrw - r0, kRowKeep);
+      __asm__ volatile("" ::: "memory");   // the previous group's rows have read their blocks
+      if (lane < gn) {
+        const long long row = gw + (r0 + lane) * nw;
+        const int s = (int)(row / NU);
+        row_setup2<KIND, false>(u_of((int)(row - (long long)s * NU), NU), h, cb, J, 0.0, 0.0, s,
+                                (s >= (NS >> 1)) ? -1.0 : 1.0, rt + lane * kRowP);
+      }
+      __asm__ volatile("" ::: "memory");
+      for (int i = 0; i < gn; ++i)
+        row2<KIND, ADAPT>(X, Xo, plane, (gw + (r0 + i) * nw) * NE, NE, tab, cb, rt + i * kRowP, renorm, lane, T, err,
+                          emax, sct, r0 + i == 0 ? pre : nullptr);
     }
   }
 }
@@ -1199,13 +1279,12 @@ __device__ __forceinline__ void stage3(const StepArgs& a, const StepGeo& G, cons
 }
 // Load the lane's first beam of the wavefront's first row (the next stage starts there),
 // so that the load completes while the wavefront waits at the grid barrier.
-template <typename ST>
-__device__ __forceinline__ void prefetch_first(const StepArgs& a, long long gw, long long nrow, int lane,
+template <int NSC, typename ST>
+__device__ __forceinline__ void prefetch_first(const StepArgs& a, const ST* X, long long gw, long long nrow, int lane,
                                                ST* pre) {
   if (gw < nrow && lane < a.NE) {
-    const ST* X = (const ST*)a.X;
 #pragma unroll
-    for (int c = 0; c < 6; ++c) pre[c] = X[gw * a.NE + lane + c * a.plane];
+    for (int c = 0; c < NSC; ++c) pre[c] = X[gw * a.NE + lane + c * a.plane];
   }
 }
 
@@ -1398,8 +1477,8 @@ k_advance(StepArgs a) {
   // the two-flavour extended model's rows fold kFoldRowsExt at a time (group2)
   __shared__ long long sfold[WPB][(NF == 2) ? (EXT ? fold2_words(kFoldRowsExt) : 1) : 256];
   __shared__ double s_sct[kSinCosTab];   // sin/cos constants of the two-flavour rotations
-  // extended two-flavour model: each wave's row-constant table
-  __shared__ double srt[(NF == 2 && EXT) ? WPB : 1][(NF == 2 && EXT) ? kGroup2 * kRowC : 1];
+  // two flavours: each wave's row-constant table
+  __shared__ double srt[NF == 2 ? WPB : 1][NF == 2 ? row_table2(EXT) : 1];
   extern __shared__ __align__(16) double dyn_tab[];
   // the wavefront index as a wave-uniform (scalar) value: the row indices, their divisions
   // and the row base offsets derived from it then live in scalar registers
@@ -1445,7 +1524,7 @@ k_advance(StepArgs a) {
   bool ok = true;
   double enone = 0.0;   // error estimate (adaptive runs only)
   I128 T = i128_zero();
-  // 3f FP64 arithmetic: each stage's first beam is loaded before the preceding barrier
+  // FP64 arithmetic, bulb model and 3f: each stage's first beam is loaded before the preceding barrier
   ST pre[6] = {};
   const long long nrow3 = (long long)a.NS * a.NU * (EXT ? a.NP : 1);
   if constexpr (PK) {
@@ -1457,6 +1536,12 @@ k_advance(StepArgs a) {
       return;
     }
   }
+  const int nrw = wave_rows(gw, nw, nrow3);
+  double* rt = srt[NF == 2 ? wid : 0];
+  if constexpr (NF == 2) {
+    if (!EXT) keep_rows2(a, gw, nw, lane, nrw, rt);
+    prep2<EXT>(a, geo_fixed(a, step0), lane, nrw, snn, rt);
+  }
   // the partner wavefront's constant block and fold scratch (packed tails)
   const double* snp = snn_all[wid ^ (WPB / 2)];
   long long* flp = sfold[wid ^ (WPB / 2)];
@@ -1466,13 +1551,14 @@ k_advance(StepArgs a) {
   // initial moment pass
   const long long kind = NF * 16 + (sizeof(ST) == 4 ? 8 : 0) + (F32 ? 4 : 0) + (EXT ? 2 : 0);
   if (a.step_ctl[kCtlMTag] == step0 && a.step_ctl[kCtlMKind] == kind) {
-    if constexpr (NF == 3 && !F32) prefetch_first<ST>(a, gw, nrow3, lane, pre);
+    if constexpr (NF == 3 && !F32) prefetch_first<6>(a, (const ST*)a.X, gw, nrow3, lane, pre);
+    if constexpr (NF == 2 && !EXT) prefetch_first<3>(a, (const ST*)a.X, gw, nrow3, lane, pre);
     if (threadIdx.x < NV) sJ[0][threadIdx.x] = as_double((unsigned long long)a.step_ctl[kCtlMom + threadIdx.x]);
     __syncthreads();
   } else {
-    if constexpr (NF == 2) stage2<0, false, EXT>(a, geo_fixed(a, step0), (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, lane, fl, T, err, enone, snn, s_sct, false, srt[EXT ? wid : 0]);
+    if constexpr (NF == 2) { stage2<0, false, EXT>(a, a.h, (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, nrw, lane, fl, T, err, enone, snn, s_sct, rt); if (!EXT) prefetch_first<3>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
     else if constexpr (F32) stage3m<0, TLDS>(a, geo_fixed(a, step0), sJ, tab, ftab, snn, gw, nw, lane, fl, T, err);
-    else { stage3<ST, 0, false, EXT>(a, geo_fixed(a, step0), (const ST*)a.X, (ST*)a.X, sJ, tab, snn, gw, nw, lane, fl, T, err, enone); prefetch_first<ST>(a, gw, nrow3, lane, pre); }
+    else { stage3<ST, 0, false, EXT>(a, geo_fixed(a, step0), (const ST*)a.X, (ST*)a.X, sJ, tab, snn, gw, nw, lane, fl, T, err, enone); prefetch_first<6>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
     ok = finish_stage<false, NM>(a, epoch++, T, R, sJ[0]);
   }
   // the adjoint's forward pass records every stage's moments: [step][slot][NV]
@@ -1483,28 +1569,30 @@ k_advance(StepArgs a) {
   record(step0, 0);
   for (long long n = step0; ok && n < step0 + nsteps; ++n) {
     T = i128_zero();
-    if constexpr (NF == 2) stage2<1, false, EXT>(a, geo_fixed(a, n), (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, lane, fl, T, err, enone, snn, s_sct, true, srt[EXT ? wid : 0]);
+    if constexpr (NF == 2) { stage2<1, false, EXT>(a, a.h, (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, nrw, lane, fl, T, err, enone, snn, s_sct, rt, EXT ? nullptr : pre); if (!EXT) prefetch_first<3>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
     else if constexpr (F32) stage3m<1, TLDS>(a, geo_fixed(a, n), sJ, tab, ftab, snn, gw, nw, lane, fl, T, err, gc);
-    else { stage3<ST, 1, false, EXT, PK>(a, geo_fixed(a, n), (const ST*)a.X, (ST*)a.X, sJ, tab, snn, gw, nw, lane, fl, T, err, enone, pre, gc, snp, flp, owner); prefetch_first<ST>(a, gw, nrow3, lane, pre); }
+    else { stage3<ST, 1, false, EXT, PK>(a, geo_fixed(a, n), (const ST*)a.X, (ST*)a.X, sJ, tab, snn, gw, nw, lane, fl, T, err, enone, pre, gc, snp, flp, owner); prefetch_first<6>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
     if (!(ok = finish_stage<false, NM>(a, epoch++, T, R, sJ[1]))) break;
     record(n, 1);
     T = i128_zero();
-    if constexpr (NF == 2) stage2<2, false, EXT>(a, geo_fixed(a, n), (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, lane, fl, T, err, enone, snn, s_sct, true, srt[EXT ? wid : 0]);
+    if constexpr (NF == 2) { stage2<2, false, EXT>(a, a.h, (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, nrw, lane, fl, T, err, enone, snn, s_sct, rt, EXT ? nullptr : pre); if (!EXT) prefetch_first<3>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
     else if constexpr (F32) stage3m<2, TLDS>(a, geo_fixed(a, n), sJ, tab, ftab, snn, gw, nw, lane, fl, T, err, gc);
-    else { stage3<ST, 2, false, EXT, PK>(a, geo_fixed(a, n), (const ST*)a.X, (ST*)a.X, sJ, tab, snn, gw, nw, lane, fl, T, err, enone, pre, gc, snp, flp, owner); prefetch_first<ST>(a, gw, nrow3, lane, pre); }
+    else { stage3<ST, 2, false, EXT, PK>(a, geo_fixed(a, n), (const ST*)a.X, (ST*)a.X, sJ, tab, snn, gw, nw, lane, fl, T, err, enone, pre, gc, snp, flp, owner); prefetch_first<6>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
     if (!(ok = finish_stage<false, NM>(a, epoch++, T, R, sJ[2]))) break;
     record(n, 2);
     T = i128_zero();
-    if constexpr (NF == 2) stage2<3, false, EXT>(a, geo_fixed(a, n), (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, lane, fl, T, err, enone, snn, s_sct, true, srt[EXT ? wid : 0]);
+    if constexpr (NF == 2) { stage2<3, false, EXT>(a, a.h, (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, nrw, lane, fl, T, err, enone, snn, s_sct, rt, EXT ? nullptr : pre); if (!EXT) prefetch_first<3>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
     else if constexpr (F32) stage3m<3, TLDS>(a, geo_fixed(a, n), sJ, tab, ftab, snn, gw, nw, lane, fl, T, err, gc);
-    else { stage3<ST, 3, false, EXT, PK>(a, geo_fixed(a, n), (const ST*)a.X, (ST*)a.X, sJ, tab, snn, gw, nw, lane, fl, T, err, enone, pre, gc, snp, flp, owner); prefetch_first<ST>(a, gw, nrow3, lane, pre); }
+    else { stage3<ST, 3, false, EXT, PK>(a, geo_fixed(a, n), (const ST*)a.X, (ST*)a.X, sJ, tab, snn, gw, nw, lane, fl, T, err, enone, pre, gc, snp, flp, owner); prefetch_first<6>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
     if (!(ok = finish_stage<false, NM>(a, epoch++, T, R, sJ[3]))) break;
     record(n, 3);
     T = i128_zero();
-    if constexpr (NF == 2) stage2<4, false, EXT>(a, geo_fixed(a, n), (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, lane, fl, T, err, enone, snn, s_sct, true, srt[EXT ? wid : 0]);
+    if constexpr (NF == 2) { stage2<4, false, EXT>(a, a.h, (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, nrw, lane, fl, T, err, enone, snn, s_sct, rt, EXT ? nullptr : pre); if (!EXT) prefetch_first<3>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
     else if constexpr (F32) stage3m<4, TLDS>(a, geo_fixed(a, n), sJ, tab, ftab, snn, gw, nw, lane, fl, T, err, gc);
-    else { stage3<ST, 4, false, EXT, PK>(a, geo_fixed(a, n), (const ST*)a.X, (ST*)a.X, sJ, tab, snn, gw, nw, lane, fl, T, err, enone, pre, gc, snp, flp, owner); prefetch_first<ST>(a, gw, nrow3, lane, pre); }
-    ok = finish_stage<false, NM>(a, epoch++, T, R, sJ[0]);
+    else { stage3<ST, 4, false, EXT, PK>(a, geo_fixed(a, n), (const ST*)a.X, (ST*)a.X, sJ, tab, snn, gw, nw, lane, fl, T, err, enone, pre, gc, snp, flp, owner); prefetch_first<6>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
+    ok = finish_stage<false, NM>(a, epoch++, T, R, sJ[0], [&] {
+      if constexpr (NF == 2) prep2<EXT>(a, geo_fixed(a, n + 1), lane, nrw, snn, rt);
+    });
     record(n + 1, 0);
   }
   if (err) __hip_atomic_fetch_or(a.sync + kSyncStatus, (unsigned)err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1596,9 +1684,12 @@ __global__ void __launch_bounds__(kBlock) k_adaptive(StepArgs a) {
   long long nacc = 0, nrej = 0, natt = 0;
   double emax = 0.0;
   I128 T = i128_zero();
+  const int nrw = wave_rows(gw, nw, (long long)a.NS * a.NU);
+  __shared__ double srt[NF == 2 ? kBlock / 64 : 1][NF == 2 ? row_table2(false) : 1];
+  double* rt = srt[NF == 2 ? wid : 0];
   auto stage = [&](auto kind, const StepGeo& G) {
     constexpr int K = decltype(kind)::value;
-    if constexpr (NF == 2) stage2<K, K == 4>(a, G, X, Xn, sJ, tab, gw, nw, lane, fl, T, err, emax, snn, s_sct, true);
+    if constexpr (NF == 2) stage2<K, K == 4>(a, G.h, X, Xn, sJ, tab, gw, nw, nrw, lane, fl, T, err, emax, snn, s_sct, rt);
     else stage3<double, K, K == 4>(a, G, X, Xn, sJ, tab, snn, gw, nw, lane, fl, T, err, emax, nullptr, gc);
   };
   using K0 = std::integral_constant<int, 0>;
@@ -1606,6 +1697,10 @@ __global__ void __launch_bounds__(kBlock) k_adaptive(StepArgs a) {
   using K2 = std::integral_constant<int, 2>;
   using K3 = std::integral_constant<int, 3>;
   using K4 = std::integral_constant<int, 4>;
+  if constexpr (NF == 2) {
+    keep_rows2(a, gw, nw, lane, nrw, rt);
+    prep2<false>(a, StepGeo{r, r, r, 0.0}, lane, nrw, snn, rt);
+  }
   stage(K0{}, StepGeo{r, r, r, 0.0});
   bool ok = finish_stage<false, 2>(a, epoch++, T, R, sJ[0]);
   if (threadIdx.x < NV) sJsave[threadIdx.x] = sJ[0][threadIdx.x];
@@ -1613,6 +1708,7 @@ __global__ void __launch_bounds__(kBlock) k_adaptive(StepArgs a) {
     const bool last = (r + h >= a.r_end);
     const double hs = last ? a.r_end - r : h;
     const StepGeo G{r, r + 0.5 * hs, last ? a.r_end : r + hs, hs};
+    if constexpr (NF == 2) prep2<false>(a, G, lane, nrw, snn, rt);
     T = i128_zero();
     stage(K1{}, G);
     if (!(ok = finish_stage<false, 2>(a, epoch++, T, R, sJ[1]))) break;
@@ -1625,7 +1721,7 @@ __global__ void __launch_bounds__(kBlock) k_adaptive(StepArgs a) {
     T = i128_zero();
     emax = 0.0;
     stage(K4{}, G);
-    if (!(ok = finish_stage<true, 2>(a, epoch++, T, R, sJ[0], emax, sE))) break;
+    if (!(ok = finish_stage<true, 2>(a, epoch++, T, R, sJ[0], NoOverlap{}, emax, sE))) break;
     ++natt;
     const double E = *sE;
     if (E <= a.tol2) {
@@ -1783,9 +1879,7 @@ __device__ void batch_stage(const BatchArgs& a, long long n, unsigned epoch, lon
       const int lr = (int)(row + lane - mrow0);
       const int s = lr / mNU;
       const int j = lr - s * mNU;
-      row_setup2<KIND, false>(u_of(j, mNU), a.h, cb, J, 0.0, 0.0, nullptr, true, rt + lane * kRowC);
-      rt[lane * kRowC + kRowS] = (double)s;
-      rt[lane * kRowC + kRowA] = (double)s;   // two tracked species: row s is anti iff s = 1
+      row_setup2<KIND, false>(u_of(j, mNU), a.h, cb, J, 0.0, 0.0, s, s ? -1.0 : 1.0, rt + lane * kRowC);
     }
     __asm__ volatile("" ::: "memory");
     if (mNE <= kGroupMaxNE) {
@@ -1794,12 +1888,9 @@ __device__ void batch_stage(const BatchArgs& a, long long n, unsigned epoch, lon
       row += gn;
     } else {
       for (int i = 0; i < gn; ++i, ++row) {
-        const long long lr = row - mrow0;
-        const int s = (int)(lr / mNU);
         double enone = 0.0;
-        row2<KIND, false, false, true>(a.X, a.X, a.plane, mbeam0 + lr * mNE, mNE, s, 0.0, a.h, a.tab + mtab0,
-                                       cb, J, a.renorm, lane, T, err, enone, 0.0, 0.0, -1, false, sct,
-                                       rt + i * kRowC);
+        row2<KIND>(a.X, a.X, a.plane, mbeam0 + (row - mrow0) * mNE, mNE, a.tab + mtab0, cb, rt + i * kRowC, a.renorm,
+                   lane, T, err, enone, sct);
       }
     }
   }
