@@ -332,32 +332,16 @@ __device__ __forceinline__ void close_row(const Scales& sc, int lane, const I128
 
 // Row geometry of a stage: cos(theta) and h / cos(theta) at the three stage radii, 1/cos at
 // the radius of the stage's moments, and (extended model) sin(theta) at the three radii.
-// The wavefront's first row keeps it in LDS (gc, 11 doubles: c0 cm c1 hc0 hcm hc1, 1/cm,
-// 1/c1, sin(theta)) from stage 1 of a step for stages 2-4, which use the same radii.
 template <int KIND, bool EXT>
 __device__ __forceinline__ void stage_geo(double u, double h, const Radial& g0, const Radial& gm,
-                                          const Radial& g1, double* gc, RowGeo& rg, double& icmom,
-                                          double& sn0, double& snm, double& sn1) {
-  if (KIND >= 2 && gc) {
-    rg.c0 = gc[0]; rg.cm = gc[1]; rg.c1 = gc[2];
-    rg.hc0 = gc[3]; rg.hcm = gc[4]; rg.hc1 = gc[5];
-    icmom = (KIND == 2) ? gc[6] : gc[7];
-    sn0 = gc[8]; snm = gc[9]; sn1 = gc[10];
-    return;
-  }
+                                          const Radial& g1, RowGeo& rg, double& icmom, double& sn0, double& snm,
+                                          double& sn1) {
   rg = row_geo(u, h, g0, gm, g1);
   icmom = 1.0 / ((KIND == 0) ? rg.c0 : ((KIND <= 2) ? rg.cm : rg.c1));
   // sin(theta) at the three stage radii (sin(theta) r = sin(theta_R) R)
   sn0 = EXT ? sqrt(u * g0.q2) : 0.0;
   snm = EXT ? sqrt(u * gm.q2) : 0.0;
   sn1 = EXT ? sqrt(u * g1.q2) : 0.0;
-  if (KIND == 1 && gc) {
-    gc[0] = rg.c0; gc[1] = rg.cm; gc[2] = rg.c1;
-    gc[3] = rg.hc0; gc[4] = rg.hcm; gc[5] = rg.hc1;
-    gc[6] = icmom;
-    gc[7] = 1.0 / rg.c1;
-    gc[8] = sn0; gc[9] = snm; gc[10] = sn1;
-  }
 }
 
 // ----------------------------------------------------------------- two flavours
@@ -411,7 +395,7 @@ __device__ __forceinline__ void row_setup2(double u, double h, const double* cb,
   const Radial g1{cb[kC2Rad + 6], cb[kC2Rad + 7], cb[kC2Rad + 8], 0.0};
   RowGeo rg;
   double icmom, sn0, snm, sn1;
-  stage_geo<KIND, EXT>(u, h, g0, gm, g1, nullptr, rg, icmom, sn0, snm, sn1);
+  stage_geo<KIND, EXT>(u, h, g0, gm, g1, rg, icmom, sn0, snm, sn1);
   double n[3];
   if (KIND == 1 || KIND == 2 || KIND == 4) {
     nunu_row<3, EXT>(J[0], g0.mu, rg.c0, sn0, cp, sp, n);
@@ -926,13 +910,99 @@ __device__ __forceinline__ Herm3 lin3p(double alpha, const double* P, const doub
                mk(fma(alpha, v[5], fma(ek, P[7], Q[7])), fma(ek, P[8], Q[8]))};
 }
 
+// A three-flavour wavefront's LDS block (doubles): row constants Q, P and the error estimate's
+// Q (27), for packed tails alpha and the species row; FP32 copies of Q and P (18 floats); M1
+// and D as full complex matrices (18 each, the diagonal's imaginary parts zero for the whole
+// launch); the step's q2, lam, mu at the three stage radii.
+constexpr int kL3Alpha = 28, kL3S = 29, kL3F32 = 32, kL3FM = 42, kL3FD = 60, kL3Rad = 78, kL3Size = 88;
+// Kept rows: constants of up to kKeep3 rows that hold for a whole step, kRow3 doubles each:
+// cos(theta) and h / cos(theta) at the three stage radii, 1/cos at rm and r1, sin(theta) at the
+// three radii (extended model); then the row's labels: u, species row, sg, cos and sin of
+// its azimuth.
+constexpr int kKeep3 = 8, kRow3 = 17;
+constexpr int kR3C = 0, kR3H = 3, kR3Icm = 6, kR3Ic1 = 7, kR3Sn = 8, kR3U = 11, kR3S = 12, kR3Sg = 13, kR3Cp = 14,
+              kR3Sp = 15;
+// Labels of rows row0, row0 + nw, ... (gn <= kKeep3 of them, lane l row l).
+template <bool EXT>
+__device__ __forceinline__ void keep_labels3(const StepArgs& a, long long row0, long long nw, int gn, int lane, double* kr) {
+  if (lane < gn) {
+    const long long row = row0 + lane * nw;
+    const long long sj = EXT ? row / a.NP : row;
+    const int s = (int)(sj / a.NU);
+    double* g = kr + lane * kRow3;
+    g[kR3U] = u_of((int)(sj - (long long)s * a.NU), a.NU);
+    g[kR3S] = (double)s;
+    g[kR3Sg] = (s >= (a.NS >> 1)) ? -1.0 : 1.0;
+    if (EXT) {
+      const double* phi = a.tab + (size_t)(kVacRows3 + a.NS) * a.NE;
+      const int p = (int)(row - sj * a.NP);
+      g[kR3Cp] = phi[p];
+      g[kR3Sp] = phi[a.NP + p];
+    }
+  }
+  __asm__ volatile("" ::: "memory");   // the wave's LDS operations complete in program order
+}
+template <bool EXT>
+__device__ __forceinline__ void keep_geo3(const double* rad, double h, int gn, int lane, double* kr) {
+  if (lane < gn) {
+    double* g = kr + lane * kRow3;
+    const Radial g0{rad[0], 0.0, 0.0, 0.0}, gm{rad[3], 0.0, 0.0, 0.0}, g1{rad[6], 0.0, 0.0, 0.0};
+    const double u = g[kR3U];
+    const RowGeo rg = row_geo(u, h, g0, gm, g1);
+    g[kR3C] = rg.c0; g[kR3C + 1] = rg.cm; g[kR3C + 2] = rg.c1;
+    g[kR3H] = rg.hc0; g[kR3H + 1] = rg.hcm; g[kR3H + 2] = rg.hc1;
+    g[kR3Icm] = 1.0 / rg.cm;
+    g[kR3Ic1] = 1.0 / rg.c1;
+    if (EXT) {   // sin(theta) r = sin(theta_R) R
+      g[kR3Sn] = sqrt(u * rad[0]); g[kR3Sn + 1] = sqrt(u * rad[3]); g[kR3Sn + 2] = sqrt(u * rad[6]);
+    }
+  }
+  __asm__ volatile("" ::: "memory");
+}
+// Before every step: its radial profiles and, if the wavefront's nrw rows are all kept, their
+// geometry (run behind the barrier before the step).
+template <bool EXT>
+__device__ __forceinline__ void prep3(const StepArgs& a, const StepGeo& G, int lane, int nrw, double* snn, double* kr) {
+  __asm__ volatile("" ::: "memory");
+  const Radial r[3] = {radial_at(a, G.r0), radial_at(a, G.rm), radial_at(a, G.r1)};
+  double* rad = snn + kL3Rad;
+  if (lane == 0)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      rad[3 * q] = r[q].q2; rad[3 * q + 1] = r[q].lam; rad[3 * q + 2] = r[q].mu;
+    }
+  __asm__ volatile("" ::: "memory");
+  if (nrw <= kKeep3) keep_geo3<EXT>(rad, G.h, nrw, lane, kr);
+}
+// The matrix V0 (vacuum Hamiltonian times E) in full, for the block, and the zero imaginary
+// parts of the wavefront's matrices (then a block barrier).
+__device__ __forceinline__ void put_full(double* F, int a, int b, bool im, double v) {
+  F[(a * 3 + b) * 2 + (im ? 1 : 0)] = v;
+  F[(b * 3 + a) * 2 + (im ? 1 : 0)] = im ? -v : v;
+}
+__device__ __forceinline__ void init3(const StepArgs& a, int lane, double* fv, double* snn) {
+  if (threadIdx.x < 6) {
+    const int q = (int)threadIdx.x - 3;
+    const int ra = (q < 0) ? (int)threadIdx.x : (q == 2 ? 1 : 0), rb = (q < 0) ? (int)threadIdx.x : (q == 0 ? 1 : 2);
+    put_full(fv, ra, rb, true, 0.0);
+    put_full(fv, ra, rb, false, a.v0[threadIdx.x]);
+  }
+  if (lane < 3) {
+    snn[kL3FM + (lane * 3 + lane) * 2 + 1] = 0.0;
+    snn[kL3FD + (lane * 3 + lane) * 2 + 1] = 0.0;
+  }
+}
+
 // Row constants of stage KIND's generator (KIND >= 1): Q to snn[0..8], P to snn[9..17]
 // and, with ADAPT (KIND 4), the error estimate's Q to snn[18..26]; returns alpha (and the
-// error estimate's alpha in alphaE).  J0..J3: the stage moments.  Lane i < 9 computes
-// component i of every 9-real matrix (the same operations as a matrix-at-a-time
-// evaluation, component by component); the commutators read their operands as full
-// complex 3x3 matrices from the wavefront's scratch fl (free before the beam loop), where
-// each lane writes its component and its mirror.
+// error estimate's alpha in alphaE).  J0..J3: the stage moments; g: the row's kept constants;
+// fv: V0 in full.  Lanes i < 9 of each half of the wavefront compute component i of every
+// 9-real matrix (the same operations as a matrix-at-a-time evaluation, component by
+// component), the lower half's the commutator with V0 (P), the upper half's the one with M1
+// (Q); the commutators read their operands as full complex 3x3 matrices from LDS, where
+// each lane writes its component and its mirror.  No lane branches: written with a branch per
+// kind of component and both commutators in the same lanes, the stages with commutators took
+// 2800-3400 cycles here.
 // Component i of the 9-real form: 0..2 the diagonal, 3 + 2t / 4 + 2t re / im of entry t of
 // (0,1), (0,2), (1,2).  nn component of M's component i (the matter part sits on i = 0):
 __device__ __forceinline__ int nn_index(int i) { return (i <= 1) ? i : i - 1; }
@@ -943,100 +1013,63 @@ __device__ __forceinline__ double nunu_comp(const double* J, double mu, double c
   if constexpr (EXT) return mu * ((J[j] - c * J[NC + j]) - sn * (cp * J[2 * NC + j] + sp * J[3 * NC + j]));
   else return mu * (J[j] - c * J[NC + j]);
 }
-// component i of M = lam E_ee + nn (neutrinos) or -(lam E_ee + nn^*) (antineutrinos)
-__device__ __forceinline__ double matter_comp(int an, double lam, double nnv, int i) {
-  const double sg = an ? -1.0 : 1.0;
-  if (i == 0) return sg * (lam + nnv);
-  if (i == 2) return 0.0;
-  return (i >= 4 && (i & 1) == 0) ? nnv : sg * nnv;
-}
-// Write component i of a 9-real Hermitian matrix (value v) into the full complex 3x3
-// matrix F (row-major, re/im pairs), with its conjugate mirror.
-__device__ __forceinline__ void put_full(double* F, int i, double v) {
-  if (i < 3) {
-    F[(i * 3 + i) * 2] = v;
-    F[(i * 3 + i) * 2 + 1] = 0.0;
-  } else {
-    const int t = (i - 3) >> 1, a = (t == 2) ? 1 : 0, b = (t == 0) ? 1 : 2;
-    if ((i & 1) == 1) {   // real part
-      F[(a * 3 + b) * 2] = v;
-      F[(b * 3 + a) * 2] = v;
-    } else {              // imaginary part
-      F[(a * 3 + b) * 2 + 1] = v;
-      F[(b * 3 + a) * 2 + 1] = -v;
-    }
-  }
-}
-// Component i of i[A, B] from the full matrices (X = A B; C_aa = -2 Im X_aa, C_ab =
-// (-(Im X_ab + Im X_ba), Re X_ab - Re X_ba)), as icomm.
-__device__ __forceinline__ double icomm_comp(const double* A, const double* B, int i) {
-  int a, b;
-  if (i < 3) {
-    a = i;
-    b = i;
-  } else {
-    const int t = (i - 3) >> 1;
-    a = (t == 2) ? 1 : 0;
-    b = (t == 0) ? 1 : 2;
-  }
-  auto at = [](const double* F, int r, int c) { return mk(F[(r * 3 + c) * 2], F[(r * 3 + c) * 2 + 1]); };
-  const cplx xab = dot3_mul(at(A, a, 0), at(B, 0, b), at(A, a, 1), at(B, 1, b), at(A, a, 2), at(B, 2, b));
-  if (i < 3) return -2.0 * xab.im;
-  const cplx xba = dot3_mul(at(A, b, 0), at(B, 0, a), at(A, b, 1), at(B, 1, a), at(A, b, 2), at(B, 2, a));
-  if ((i & 1) == 1) return -(xab.im + xba.im);
-  return xab.re - xba.re;
-}
 template <int KIND, bool ADAPT, bool EXT>
-__device__ __forceinline__ double row_lin3(const StepArgs& a, int an, const RowGeo& rg, const Radial& g0,
-                                           const Radial& gm, const Radial& g1, const double* J0,
-                                           const double* J1, const double* J2, const double* J3,
-                                           double sn0, double snm, double sn1, double cp, double sp,
-                                           double* snn, double& alphaE, int lane, double* scr) {
+__device__ __forceinline__ double row_lin3(const double* g, const double* fv, const double* J0, const double* J1,
+                                           const double* J2, const double* J3, double* snn, double& alphaE, int lane) {
   constexpr int NC = 8;
-  const int i = (lane < 9) ? lane : 8;   // lanes 9..63 repeat component 8 and write nothing
+  const int i = min(lane & 31, 8);
+  const bool act = (lane & 31) < 9, upper = lane >= 32;   // other lanes repeat component 8 and write nothing
+  const int q = (i - 3) >> 1;
+  const int ra = (i < 3) ? i : (q == 2 ? 1 : 0), rb = (i < 3) ? i : (q == 0 ? 1 : 2);
+  const bool im = i >= 4 && (i & 1) == 0;
   const int jn = nn_index(i);
+  const double* rad = snn + kL3Rad;
+  const double sg = g[kR3Sg];
+  const double sgi = im ? 1.0 : sg;
+  const double cp = EXT ? g[kR3Cp] : 0.0, sp = EXT ? g[kR3Sp] : 0.0;
+  // component i of M = lam E_ee + nn (neutrinos) or -(lam E_ee + nn^*) (antineutrinos)
+  const auto matter = [&](const double* J, int at) {
+    const double nn = nunu_comp<NC, EXT>(J, rad[3 * at + 2], g[kR3C + at], EXT ? g[kR3Sn + at] : 0.0, cp, sp, jn);
+    const double x = sgi * ((i == 0) ? rad[3 * at + 1] + nn : nn);
+    return (i == 2) ? 0.0 : x;
+  };
   double M1 = 0.0, M2 = 0.0, M3 = 0.0, M4 = 0.0;
-  if (KIND != 3) M1 = matter_comp(an, g0.lam, nunu_comp<NC, EXT>(J0, g0.mu, rg.c0, sn0, cp, sp, jn), i);
-  if (KIND == 2 || KIND == 4) M2 = matter_comp(an, gm.lam, nunu_comp<NC, EXT>(J1, gm.mu, rg.cm, snm, cp, sp, jn), i);
-  if (KIND >= 3) M3 = matter_comp(an, gm.lam, nunu_comp<NC, EXT>(J2, gm.mu, rg.cm, snm, cp, sp, jn), i);
-  if (KIND == 4) M4 = matter_comp(an, g1.lam, nunu_comp<NC, EXT>(J3, g1.mu, rg.c1, sn1, cp, sp, jn), i);
+  if (KIND != 3) M1 = matter(J0, 0);
+  if (KIND == 2 || KIND == 4) M2 = matter(J1, 1);
+  if (KIND >= 3) M3 = matter(J2, 1);
+  if (KIND == 4) M4 = matter(J3, 2);
   double alpha;
   if (KIND == 1 || KIND == 3) {
-    alpha = (KIND == 1) ? 0.5 * rg.hc0 : rg.hcm;
+    alpha = (KIND == 1) ? 0.5 * g[kR3H] : g[kR3H + 1];
     if (lane < 9) snn[i] = alpha * ((KIND == 1) ? M1 : M3);
   } else {
     const double D = ((KIND == 2) ? M2 : M4) - M1;
-    // full matrices: V0 at scr[0..17], M1 at scr[18..35], D at scr[36..53]
-    double* FV = scr;
-    double* FM = scr + 18;
-    double* FD = scr + 36;
-    if (lane < 9) {
-      const double v0 = (i < 3) ? a.v0[i] : (((i & 1) == 1) ? a.v0[3 + ((i - 3) >> 1)] : 0.0);
-      put_full(FV, i, v0);
-      put_full(FM, i, M1);
-      put_full(FD, i, D);
-    }
+    double* FM = snn + kL3FM;
+    double* FD = snn + kL3FD;
+    if (act) put_full(upper ? FM : FD, ra, rb, im, upper ? M1 : D);
     __asm__ volatile("" ::: "memory");   // the wave's LDS operations complete in program order
-    const double R1 = icomm_comp(FV, FD, i), R2 = icomm_comp(FM, FD, i);
+    // component i of i[A, D] (X = A D; C_aa = -2 Im X_aa, C_ab = (-(Im X_ab + Im X_ba),
+    // Re X_ab - Re X_ba)), A = V0 or M1
+    const double* A = upper ? FM : fv;
+    const auto at = [](const double* F, int r, int c) { return mk(F[(r * 3 + c) * 2], F[(r * 3 + c) * 2 + 1]); };
+    const cplx xab = dot3_mul(at(A, ra, 0), at(FD, 0, rb), at(A, ra, 1), at(FD, 1, rb), at(A, ra, 2), at(FD, 2, rb));
+    const cplx xba = dot3_mul(at(A, rb, 0), at(FD, 0, ra), at(A, rb, 1), at(FD, 1, ra), at(A, rb, 2), at(FD, 2, ra));
+    const double R = im ? xab.re - xba.re : -(xab.im + xba.im);
+    const double hc0 = g[kR3H], hcm = g[kR3H + 1], hc1 = g[kR3H + 2];
     __asm__ volatile("" ::: "memory");
     if (KIND == 2) {
-      const double c = (rg.hc0 * rg.hcm) * 0.125;
-      alpha = 0.5 * rg.hcm;
-      if (lane < 9) {
-        snn[9 + i] = c * R1;
-        snn[i] = fma(alpha, M2, c * R2);
-      }
+      const double c = (hc0 * hcm) * 0.125;
+      alpha = 0.5 * hcm;
+      const double P = c * R, Q = fma(alpha, M2, c * R);
+      if (act) snn[upper ? i : 9 + i] = upper ? Q : P;
     } else {
-      const double c = (rg.hc0 * rg.hc1) * (1.0 / 12.0), a2 = 2.0 * rg.hcm;
-      alpha = (((rg.hc0 + a2) + a2) + rg.hc1) * (1.0 / 6.0);
-      alphaE = alpha - rg.hcm;
-      const double S = fma(rg.hc1, M4, fma(a2, M3, fma(a2, M2, rg.hc0 * M1)));
-      const double Qi = fma(S, 1.0 / 6.0, c * R2);
-      if (lane < 9) {
-        snn[9 + i] = c * R1;
-        snn[i] = Qi;
-        if (ADAPT) snn[18 + i] = fma(-rg.hcm, M2, Qi);
-      }
+      const double c = (hc0 * hc1) * (1.0 / 12.0), a2 = 2.0 * hcm;
+      alpha = (((hc0 + a2) + a2) + hc1) * (1.0 / 6.0);
+      alphaE = alpha - hcm;
+      const double S = fma(hc1, M4, fma(a2, M3, fma(a2, M2, hc0 * M1)));
+      const double P = c * R, Q = fma(S, 1.0 / 6.0, c * R);
+      if (act) snn[upper ? i : 9 + i] = upper ? Q : P;
+      if (ADAPT && act && upper) snn[18 + i] = fma(-hcm, M2, Q);
     }
   }
   __asm__ volatile("" ::: "memory");
@@ -1062,43 +1095,24 @@ __device__ __forceinline__ double row_lin3(const StepArgs& a, int an, const RowG
 // the moments keep their bits.  Block barriers: after the row constants (the owner reads
 // its partner's, snp) and before the partner's fold (the handed-over sums).
 template <typename ST, int KIND, bool ADAPT = false, bool EXT = false, bool PK = false>
-__device__ __forceinline__ void row3(const StepArgs& a, const ST* X, ST* Xo, long long row, double h,
-                                     const Radial& g0, const Radial& gm, const Radial& g1,
-                                     const double (*sJ)[EXT ? 32 : 16], const double* tab, double* snn,
-                                     int lane, long long* fl, I128& T, int& err, double& emax,
-                                     const ST* pre = nullptr, double* gc = nullptr, const double* snp = nullptr,
+__device__ __forceinline__ void row3(const StepArgs& a, const ST* X, ST* Xo, long long row, const double* g,
+                                     const double* fv, const double (*sJ)[EXT ? 32 : 16], const double* tab,
+                                     double* snn, int lane, I128& T, int& err, double& emax,
+                                     const ST* pre = nullptr, const double* snp = nullptr, long long* fl = nullptr,
                                      long long* flp = nullptr, bool owner = false) {
   static_assert(!PK || (!ADAPT && !EXT && sizeof(ST) == 8 && KIND >= 1), "packed tails: FP64 fixed steps");
   constexpr int NM = EXT ? 4 : 2;
   const long long plane = a.plane;
   const int NE = a.NE;
-  int s, j;
-  double cp = 0.0, sp = 0.0;
-  if constexpr (EXT) {
-    const long long sj = row / a.NP;
-    const int p = (int)(row - sj * a.NP);
-    s = (int)(sj / a.NU);
-    j = (int)(sj - (long long)s * a.NU);
-    const double* phi = a.tab + (size_t)(kVacRows3 + a.NS) * a.NE;
-    cp = phi[p];
-    sp = phi[a.NP + p];
-  } else {
-    s = (int)(row / a.NU);
-    j = (int)(row - (long long)s * a.NU);
-  }
+  const int s = __builtin_amdgcn_readfirstlane((int)g[kR3S]);
   const int an = (s >= (a.NS >> 1)) ? 1 : 0;   // antiparticle row
-  const double u = u_of(j, a.NU);
-  RowGeo rg;
-  double icmom, sn0, snm, sn1;
-  stage_geo<KIND, EXT>(u, h, g0, gm, g1, gc, rg, icmom, sn0, snm, sn1);
   double alpha = 0.0, alphaE = 0.0;
   if constexpr (KIND >= 1)
-    alpha = row_lin3<KIND, ADAPT, EXT>(a, an, rg, g0, gm, g1, sJ[0], sJ[1], sJ[2], sJ[3], sn0, snm, sn1,
-                                       cp, sp, snn, alphaE, lane, reinterpret_cast<double*>(fl));
+    alpha = row_lin3<KIND, ADAPT, EXT>(g, fv, sJ[0], sJ[1], sJ[2], sJ[3], snn, alphaE, lane);
   if constexpr (PK) {
     if (lane == 0) {
-      snn[28] = alpha;
-      snn[29] = (double)s;
+      snn[kL3Alpha] = alpha;
+      snn[kL3S] = (double)s;
     }
     __syncthreads();   // every row's constants are in place (the owner reads its partner's)
   }
@@ -1195,8 +1209,8 @@ __device__ __forceinline__ void row3(const StepArgs& a, const ST* X, ST* Xo, lon
         if (ton) {
           const int hf = lane >> 5, k = kmain + (lane & 31);
           const double* sl = hf ? snp : snn;
-          const double al = hf ? snp[28] : alpha;
-          const int sh = hf ? (int)snp[29] : s;
+          const double al = hf ? snp[kL3Alpha] : alpha;
+          const int sh = hf ? (int)snp[kL3S] : s;
           const int anl = (sh >= (a.NS >> 1)) ? 1 : 0;
           cplx ps[3] = {mk((double)q[0], (double)q[1]), mk((double)q[2], (double)q[3]),
                         mk((double)q[4], (double)q[5])};
@@ -1253,28 +1267,44 @@ __device__ __forceinline__ void row3(const StepArgs& a, const ST* X, ST* Xo, lon
       mine = i128_add(mine, i128_from(wave_fold<8>(acc, lane)));
     }
   }
-  const double snmom = (KIND == 0) ? sn0 : ((KIND <= 2) ? snm : sn1);
   const double v = (NE <= kSegNE) ? (double)(long long)mine.lo : i128_to_double(mine);
-  close_row<8, NM>(Scales{a.s1, a.s0, a.p2e1, a.p2e0}, lane, mine, v, icmom, T, err, (snmom * icmom) * cp,
-                   (snmom * icmom) * sp);
+  const double icmom = (KIND == 0) ? 1.0 / g[kR3C] : ((KIND <= 2) ? g[kR3Icm] : g[kR3Ic1]);
+  double asc = 0.0, ass = 0.0;
+  if constexpr (EXT) {
+    const double t = g[kR3Sn + ((KIND == 0) ? 0 : ((KIND <= 2) ? 1 : 2))] * icmom;
+    asc = t * g[kR3Cp];
+    ass = t * g[kR3Sp];
+  }
+  close_row<8, NM>(Scales{a.s1, a.s0, a.p2e1, a.p2e0}, lane, mine, v, icmom, T, err, asc, ass);
 }
 
+// Rows gw, gw + nw, ... (nrw of them): kept ones from the table kr, more in groups of kKeep3
+// whose labels and geometry are computed (lane-parallel) in every stage.
+template <bool EXT, typename F>
+__device__ __forceinline__ void each_row3(const StepArgs& a, double h, long long gw, long long nw, int nrw, int lane,
+                                          const double* snn, double* kr, F fn) {
+  for (int r0 = 0; r0 < nrw; r0 += kKeep3) {
+    const int gn = min(nrw - r0, kKeep3);
+    if (nrw > kKeep3) {
+      __asm__ volatile("" ::: "memory");   // the previous group's rows have read their blocks
+      keep_labels3<EXT>(a, gw + r0 * nw, nw, gn, lane, kr);
+      keep_geo3<EXT>(snn + kL3Rad, h, gn, lane, kr);
+    }
+    for (int i = 0; i < gn; ++i) fn(gw + (r0 + i) * nw, kr + i * kRow3, r0 + i == 0);
+  }
+}
 template <typename ST, int KIND, bool ADAPT = false, bool EXT = false, bool PK = false>
-__device__ __forceinline__ void stage3(const StepArgs& a, const StepGeo& G, const ST* X, ST* Xo,
-                                       const double (*sJ)[EXT ? 32 : 16], const double* tab, double* snn,
-                                       long long gw, long long nw, int lane, long long* fl, I128& T,
-                                       int& err, double& emax, const ST* pre = nullptr,
-                                       double* gc = nullptr, const double* snp = nullptr,
-                                       long long* flp = nullptr, bool owner = false) {
-  const Radial g0 = radial_at(a, G.r0), gm = radial_at(a, G.rm), g1 = radial_at(a, G.r1);
-  const long long nrow = (long long)a.NS * a.NU * (EXT ? a.NP : 1);
+__device__ __forceinline__ void stage3(const StepArgs& a, double h, const ST* X, ST* Xo,
+                                       const double (*sJ)[EXT ? 32 : 16], const double* tab, double* snn, double* kr,
+                                       const double* fv, long long gw, long long nw, int nrw, int lane, I128& T,
+                                       int& err, double& emax, const ST* pre = nullptr, const double* snp = nullptr,
+                                       long long* fl = nullptr, long long* flp = nullptr, bool owner = false) {
   if constexpr (PK) {   // one row per wavefront
-    row3<ST, KIND, false, false, true>(a, X, Xo, gw, G.h, g0, gm, g1, sJ, tab, snn, lane, fl, T, err, emax,
-                                       pre, gc, snp, flp, owner);
+    row3<ST, KIND, false, false, true>(a, X, Xo, gw, kr, fv, sJ, tab, snn, lane, T, err, emax, pre, snp, fl, flp, owner);
   } else {
-    for (long long row = gw; row < nrow; row += nw)
-      row3<ST, KIND, ADAPT, EXT>(a, X, Xo, row, G.h, g0, gm, g1, sJ, tab, snn, lane, fl, T, err, emax,
-                                 row == gw ? pre : nullptr, row == gw ? gc : nullptr);
+    each_row3<EXT>(a, h, gw, nw, nrw, lane, snn, kr, [&](long long row, const double* g, bool first) {
+      row3<ST, KIND, ADAPT, EXT>(a, X, Xo, row, g, fv, sJ, tab, snn, lane, T, err, emax, first ? pre : nullptr);
+    });
   }
 }
 // Load the lane's first beam of the wavefront's first row (the next stage starts there),
@@ -1303,10 +1333,9 @@ __device__ __forceinline__ void prefetch_first(const StepArgs& a, const ST* X, l
 // FT: ftab (LDS) holds the vacuum rows and e_k as FP32, eight floats per energy
 // (H_ee, H_mumu, H_tautau, H_emu, H_etau, H_mutau, e_k, 0), read by stages 1-3.
 template <int KIND, bool FT>
-__device__ __forceinline__ void row3m(const StepArgs& a, long long row, const Radial& g0, const Radial& gm,
-                                      const Radial& g1, const RowGeo& rg, double icmom, const double (*sJ)[16],
-                                      const double* tab, const float* ftab, double* snd, float* snn, int lane,
-                                      long long* fl, I128& T, int& err) {
+__device__ __forceinline__ void row3m(const StepArgs& a, long long row, const double* g, const double* fv,
+                                      const double (*sJ)[16], const double* tab, const float* ftab, double* snd,
+                                      int lane, I128& T, int& err) {
 #pragma clang fp contract(fast)
   constexpr int kSeg = 64 * 16;
   const long long plane = a.plane;
@@ -1316,20 +1345,19 @@ __device__ __forceinline__ void row3m(const StepArgs& a, long long row, const Ra
   char* Xp[6];
 #pragma unroll
   for (int c = 0; c < 6; ++c) Xp[c] = (char*)((float*)a.X + c * plane);
-  const int s = (int)(row / a.NU);
+  const int s = __builtin_amdgcn_readfirstlane((int)g[kR3S]);
   const int an = (s >= (a.NS >> 1)) ? 1 : 0;   // antiparticle row
   // generator row constants (FP64, as in the FP64 stepper): snd[0..8] Q, snd[9..17] P;
   // stages 1-3 use FP32 copies in snn, the final update's Theta is summed in FP64
   double alphaE = 0.0;
-  const double alpha = (KIND >= 1)
-      ? row_lin3<(KIND >= 1 ? KIND : 1), false, false>(a, an, rg, g0, gm, g1, sJ[0], sJ[1], sJ[2], sJ[3],
-                                                        0.0, 0.0, 0.0, 0.0, 0.0, snd, alphaE, lane,
-                                                        reinterpret_cast<double*>(fl))
-      : 0.0;
+  const double alpha = (KIND >= 1) ? row_lin3<(KIND >= 1 ? KIND : 1), false, false>(g, fv, sJ[0], sJ[1], sJ[2], sJ[3],
+                                                                                     snd, alphaE, lane)
+                                   : 0.0;
   const float alphaf = (float)alpha;
+  float* snn = (float*)(snd + kL3F32);
   if (KIND >= 1 && KIND <= 3) {
-#pragma unroll
-    for (int i = 0; i < 18; ++i) snn[i] = (float)snd[i];
+    if (lane < 18) snn[lane] = (float)snd[lane];
+    __asm__ volatile("" ::: "memory");
   }
   const double* G = tab + (size_t)(kVacRows3 + s) * NE;
   const long long rb = row * NE;
@@ -1429,6 +1457,7 @@ __device__ __forceinline__ void row3m(const StepArgs& a, long long row, const Ra
     mine = i128_add(mine, i128_from(wave_fold<8>(acc, lane)));
   }
   const double v = (NE <= kSeg) ? (double)(long long)mine.lo : i128_to_double(mine);
+  const double icmom = (KIND == 0) ? 1.0 / g[kR3C] : ((KIND <= 2) ? g[kR3Icm] : g[kR3Ic1]);
   close_row<8>(Scales{a.s1, a.s0, a.p2e1, a.p2e0}, lane, mine, v, icmom, T, err);
 }
 
@@ -1437,20 +1466,12 @@ __device__ __forceinline__ void row3m(const StepArgs& a, long long row, const Ra
 // step (a bound computed from the model's parameters); nearer the neutrinosphere FP32
 // cannot hold the per-step phase and the FP64-arithmetic launch on the FP32 state is used.
 template <int KIND, bool FT>
-__device__ __forceinline__ void stage3m(const StepArgs& a, const StepGeo& G, const double (*sJ)[16],
-                                        const double* tab, const float* ftab, double* snn, long long gw,
-                                        long long nw, int lane, long long* fl, I128& T, int& err,
-                                        double* gc = nullptr) {
-  const Radial g0 = radial_at(a, G.r0), gm = radial_at(a, G.rm), g1 = radial_at(a, G.r1);
-  const long long nrow = (long long)a.NS * a.NU;
-  for (long long row = gw; row < nrow; row += nw) {
-    const int s = (int)(row / a.NU);
-    const int j = (int)(row - (long long)s * a.NU);
-    RowGeo rg;
-    double icmom, sn0, snm, sn1;
-    stage_geo<KIND, false>(u_of(j, a.NU), G.h, g0, gm, g1, row == gw ? gc : nullptr, rg, icmom, sn0, snm, sn1);
-    row3m<KIND, FT>(a, row, g0, gm, g1, rg, icmom, sJ, tab, ftab, snn, (float*)(snn + 32), lane, fl, T, err);
-  }
+__device__ __forceinline__ void stage3m(const StepArgs& a, const double (*sJ)[16], const double* tab, const float* ftab,
+                                        double* snn, double* kr, const double* fv, long long gw, long long nw, int nrw,
+                                        int lane, I128& T, int& err) {
+  each_row3<false>(a, a.h, gw, nw, nrw, lane, snn, kr, [&](long long row, const double* g, bool) {
+    row3m<KIND, FT>(a, row, g, fv, sJ, tab, ftab, snn, lane, T, err);
+  });
 }
 
 // --------------------------------------------------------------- the stepper
@@ -1472,10 +1493,14 @@ k_advance(StepArgs a) {
   constexpr int WPB = BS / 64;
   __shared__ double sJ[4][NV];
   __shared__ RedLds<NV, BS> R;
-  // per wavefront: row constants (mixed: then 32 floats), then the first row's geometry
-  __shared__ double snn_all[WPB][F32 ? 64 : 48];
-  // the two-flavour extended model's rows fold kFoldRowsExt at a time (group2)
-  __shared__ long long sfold[WPB][(NF == 2) ? (EXT ? fold2_words(kFoldRowsExt) : 1) : 256];
+  // per wavefront: stage constants
+  __shared__ double snn_all[WPB][NF == 2 ? kC2Size : kL3Size];
+  // three flavours: each wave's kept rows, and V0
+  __shared__ double skr[NF == 3 ? WPB : 1][NF == 3 ? kKeep3 * kRow3 : 1];
+  __shared__ double sfv[NF == 3 ? 18 : 1];
+  // the two-flavour extended model's rows fold kFoldRowsExt at a time (group2); packed tails
+  // hand sums over
+  __shared__ long long sfold[WPB][(NF == 2) ? (EXT ? fold2_words(kFoldRowsExt) : 1) : (PK ? 256 : 1)];
   __shared__ double s_sct[kSinCosTab];   // sin/cos constants of the two-flavour rotations
   // two flavours: each wave's row-constant table
   __shared__ double srt[NF == 2 ? WPB : 1][NF == 2 ? row_table2(EXT) : 1];
@@ -1508,7 +1533,6 @@ k_advance(StepArgs a) {
     tab = dyn_tab;
   }
   double* snn = snn_all[wid];
-  double* gc = snn + (F32 ? 48 : 32);   // the first row's stage geometry
   long long* fl = sfold[wid];
   const long long step0 = a.step_ctl[0];
   long long nsteps;
@@ -1538,6 +1562,13 @@ k_advance(StepArgs a) {
   }
   const int nrw = wave_rows(gw, nw, nrow3);
   double* rt = srt[NF == 2 ? wid : 0];
+  double* kr = skr[NF == 3 ? wid : 0];
+  if constexpr (NF == 3) {
+    init3(a, lane, sfv, snn);
+    if (nrw <= kKeep3) keep_labels3<EXT>(a, gw, nw, nrw, lane, kr);
+    prep3<EXT>(a, geo_fixed(a, step0), lane, nrw, snn, kr);
+    __syncthreads();
+  }
   if constexpr (NF == 2) {
     if (!EXT) keep_rows2(a, gw, nw, lane, nrw, rt);
     prep2<EXT>(a, geo_fixed(a, step0), lane, nrw, snn, rt);
@@ -1557,8 +1588,8 @@ k_advance(StepArgs a) {
     __syncthreads();
   } else {
     if constexpr (NF == 2) { stage2<0, false, EXT>(a, a.h, (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, nrw, lane, fl, T, err, enone, snn, s_sct, rt); if (!EXT) prefetch_first<3>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
-    else if constexpr (F32) stage3m<0, TLDS>(a, geo_fixed(a, step0), sJ, tab, ftab, snn, gw, nw, lane, fl, T, err);
-    else { stage3<ST, 0, false, EXT>(a, geo_fixed(a, step0), (const ST*)a.X, (ST*)a.X, sJ, tab, snn, gw, nw, lane, fl, T, err, enone); prefetch_first<6>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
+    else if constexpr (F32) stage3m<0, TLDS>(a, sJ, tab, ftab, snn, kr, sfv, gw, nw, nrw, lane, T, err);
+    else { stage3<ST, 0, false, EXT>(a, a.h, (const ST*)a.X, (ST*)a.X, sJ, tab, snn, kr, sfv, gw, nw, nrw, lane, T, err, enone); prefetch_first<6>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
     ok = finish_stage<false, NM>(a, epoch++, T, R, sJ[0]);
   }
   // the adjoint's forward pass records every stage's moments: [step][slot][NV]
@@ -1570,28 +1601,29 @@ k_advance(StepArgs a) {
   for (long long n = step0; ok && n < step0 + nsteps; ++n) {
     T = i128_zero();
     if constexpr (NF == 2) { stage2<1, false, EXT>(a, a.h, (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, nrw, lane, fl, T, err, enone, snn, s_sct, rt, EXT ? nullptr : pre); if (!EXT) prefetch_first<3>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
-    else if constexpr (F32) stage3m<1, TLDS>(a, geo_fixed(a, n), sJ, tab, ftab, snn, gw, nw, lane, fl, T, err, gc);
-    else { stage3<ST, 1, false, EXT, PK>(a, geo_fixed(a, n), (const ST*)a.X, (ST*)a.X, sJ, tab, snn, gw, nw, lane, fl, T, err, enone, pre, gc, snp, flp, owner); prefetch_first<6>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
+    else if constexpr (F32) stage3m<1, TLDS>(a, sJ, tab, ftab, snn, kr, sfv, gw, nw, nrw, lane, T, err);
+    else { stage3<ST, 1, false, EXT, PK>(a, a.h, (const ST*)a.X, (ST*)a.X, sJ, tab, snn, kr, sfv, gw, nw, nrw, lane, T, err, enone, pre, snp, fl, flp, owner); prefetch_first<6>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
     if (!(ok = finish_stage<false, NM>(a, epoch++, T, R, sJ[1]))) break;
     record(n, 1);
     T = i128_zero();
     if constexpr (NF == 2) { stage2<2, false, EXT>(a, a.h, (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, nrw, lane, fl, T, err, enone, snn, s_sct, rt, EXT ? nullptr : pre); if (!EXT) prefetch_first<3>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
-    else if constexpr (F32) stage3m<2, TLDS>(a, geo_fixed(a, n), sJ, tab, ftab, snn, gw, nw, lane, fl, T, err, gc);
-    else { stage3<ST, 2, false, EXT, PK>(a, geo_fixed(a, n), (const ST*)a.X, (ST*)a.X, sJ, tab, snn, gw, nw, lane, fl, T, err, enone, pre, gc, snp, flp, owner); prefetch_first<6>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
+    else if constexpr (F32) stage3m<2, TLDS>(a, sJ, tab, ftab, snn, kr, sfv, gw, nw, nrw, lane, T, err);
+    else { stage3<ST, 2, false, EXT, PK>(a, a.h, (const ST*)a.X, (ST*)a.X, sJ, tab, snn, kr, sfv, gw, nw, nrw, lane, T, err, enone, pre, snp, fl, flp, owner); prefetch_first<6>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
     if (!(ok = finish_stage<false, NM>(a, epoch++, T, R, sJ[2]))) break;
     record(n, 2);
     T = i128_zero();
     if constexpr (NF == 2) { stage2<3, false, EXT>(a, a.h, (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, nrw, lane, fl, T, err, enone, snn, s_sct, rt, EXT ? nullptr : pre); if (!EXT) prefetch_first<3>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
-    else if constexpr (F32) stage3m<3, TLDS>(a, geo_fixed(a, n), sJ, tab, ftab, snn, gw, nw, lane, fl, T, err, gc);
-    else { stage3<ST, 3, false, EXT, PK>(a, geo_fixed(a, n), (const ST*)a.X, (ST*)a.X, sJ, tab, snn, gw, nw, lane, fl, T, err, enone, pre, gc, snp, flp, owner); prefetch_first<6>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
+    else if constexpr (F32) stage3m<3, TLDS>(a, sJ, tab, ftab, snn, kr, sfv, gw, nw, nrw, lane, T, err);
+    else { stage3<ST, 3, false, EXT, PK>(a, a.h, (const ST*)a.X, (ST*)a.X, sJ, tab, snn, kr, sfv, gw, nw, nrw, lane, T, err, enone, pre, snp, fl, flp, owner); prefetch_first<6>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
     if (!(ok = finish_stage<false, NM>(a, epoch++, T, R, sJ[3]))) break;
     record(n, 3);
     T = i128_zero();
     if constexpr (NF == 2) { stage2<4, false, EXT>(a, a.h, (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, nrw, lane, fl, T, err, enone, snn, s_sct, rt, EXT ? nullptr : pre); if (!EXT) prefetch_first<3>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
-    else if constexpr (F32) stage3m<4, TLDS>(a, geo_fixed(a, n), sJ, tab, ftab, snn, gw, nw, lane, fl, T, err, gc);
-    else { stage3<ST, 4, false, EXT, PK>(a, geo_fixed(a, n), (const ST*)a.X, (ST*)a.X, sJ, tab, snn, gw, nw, lane, fl, T, err, enone, pre, gc, snp, flp, owner); prefetch_first<6>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
+    else if constexpr (F32) stage3m<4, TLDS>(a, sJ, tab, ftab, snn, kr, sfv, gw, nw, nrw, lane, T, err);
+    else { stage3<ST, 4, false, EXT, PK>(a, a.h, (const ST*)a.X, (ST*)a.X, sJ, tab, snn, kr, sfv, gw, nw, nrw, lane, T, err, enone, pre, snp, fl, flp, owner); prefetch_first<6>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
     ok = finish_stage<false, NM>(a, epoch++, T, R, sJ[0], [&] {
       if constexpr (NF == 2) prep2<EXT>(a, geo_fixed(a, n + 1), lane, nrw, snn, rt);
+      else prep3<EXT>(a, geo_fixed(a, n + 1), lane, nrw, snn, kr);
     });
     record(n + 1, 0);
   }
@@ -1651,8 +1683,9 @@ __global__ void __launch_bounds__(kBlock) k_adaptive(StepArgs a) {
   __shared__ double sJsave[NV];
   __shared__ double sE[1];
   __shared__ RedLds<NV, kBlock, true> R;
-  __shared__ double snn_all[kBlock / 64][48];   // row constants, then the first row's geometry
-  __shared__ long long sfold[kBlock / 64][(NF == 2) ? 1 : 64];
+  __shared__ double snn_all[kBlock / 64][NF == 2 ? kC2Size : kL3Size];   // stage constants
+  __shared__ double skr[NF == 3 ? kBlock / 64 : 1][NF == 3 ? kKeep3 * kRow3 : 1];
+  __shared__ double sfv[NF == 3 ? 18 : 1];
   __shared__ double s_sct[kSinCosTab];   // sin/cos constants of the two-flavour rotations
   extern __shared__ __align__(16) double dyn_tab[];
   // the wavefront index as a wave-uniform (scalar) value: the row indices, their divisions
@@ -1672,8 +1705,7 @@ __global__ void __launch_bounds__(kBlock) k_adaptive(StepArgs a) {
     tab = dyn_tab;
   }
   double* snn = snn_all[wid];
-  double* gc = snn + 32;   // the first row's stage geometry
-  long long* fl = sfold[wid];
+  double* kr = skr[NF == 3 ? wid : 0];
   long long* ctl = a.step_ctl;
   double r = as_double((unsigned long long)ctl[kCtlR]);
   double h = as_double((unsigned long long)ctl[kCtlH]);
@@ -1689,8 +1721,8 @@ __global__ void __launch_bounds__(kBlock) k_adaptive(StepArgs a) {
   double* rt = srt[NF == 2 ? wid : 0];
   auto stage = [&](auto kind, const StepGeo& G) {
     constexpr int K = decltype(kind)::value;
-    if constexpr (NF == 2) stage2<K, K == 4>(a, G.h, X, Xn, sJ, tab, gw, nw, nrw, lane, fl, T, err, emax, snn, s_sct, rt);
-    else stage3<double, K, K == 4>(a, G, X, Xn, sJ, tab, snn, gw, nw, lane, fl, T, err, emax, nullptr, gc);
+    if constexpr (NF == 2) stage2<K, K == 4>(a, G.h, X, Xn, sJ, tab, gw, nw, nrw, lane, nullptr, T, err, emax, snn, s_sct, rt);
+    else stage3<double, K, K == 4>(a, G.h, X, Xn, sJ, tab, snn, kr, sfv, gw, nw, nrw, lane, T, err, emax);
   };
   using K0 = std::integral_constant<int, 0>;
   using K1 = std::integral_constant<int, 1>;
@@ -1700,6 +1732,11 @@ __global__ void __launch_bounds__(kBlock) k_adaptive(StepArgs a) {
   if constexpr (NF == 2) {
     keep_rows2(a, gw, nw, lane, nrw, rt);
     prep2<false>(a, StepGeo{r, r, r, 0.0}, lane, nrw, snn, rt);
+  } else {
+    init3(a, lane, sfv, snn);
+    if (nrw <= kKeep3) keep_labels3<false>(a, gw, nw, nrw, lane, kr);
+    prep3<false>(a, StepGeo{r, r, r, 0.0}, lane, nrw, snn, kr);
+    __syncthreads();
   }
   stage(K0{}, StepGeo{r, r, r, 0.0});
   bool ok = finish_stage<false, 2>(a, epoch++, T, R, sJ[0]);
@@ -1709,6 +1746,7 @@ __global__ void __launch_bounds__(kBlock) k_adaptive(StepArgs a) {
     const double hs = last ? a.r_end - r : h;
     const StepGeo G{r, r + 0.5 * hs, last ? a.r_end : r + hs, hs};
     if constexpr (NF == 2) prep2<false>(a, G, lane, nrw, snn, rt);
+    else prep3<false>(a, G, lane, nrw, snn, kr);
     T = i128_zero();
     stage(K1{}, G);
     if (!(ok = finish_stage<false, 2>(a, epoch++, T, R, sJ[1]))) break;
