@@ -27,7 +27,7 @@ template <int BS>
 __global__ void k_batch2(BatchArgs a);
 template <int BPT>
 __global__ void k_adjoint2(AdjArgs a);
-template <int NF, bool TLDS>
+template <int NF, bool TLDS, int BS>
 __global__ void k_adaptive(StepArgs a);
 __global__ void k_zero_sync(unsigned int* sync, int keep_status, const unsigned* cancel, int words);
 __global__ void k_zero_u64(unsigned long long* p, long long n);
@@ -152,7 +152,7 @@ struct nb_model {
   hipStream_t stream = nullptr;
   int device = 0, cus = 0, nblocks = 0;
   int cap512 = 0, cap256 = 0;        // resident blocks of the fixed-step kernels at 512 / 256 threads
-  int cap_adaptive = 0;              // resident blocks of the adaptive kernel (512 threads)
+  int bs_adaptive = kBlock, cap_adaptive = 0;  // threads per block and resident blocks of the adaptive kernel
   unsigned* cancel = nullptr;        // this model's cancel word (fine-grained host memory)
   const unsigned* cancel_dev = nullptr;  // its device address
   unsigned long long ticks_per_s = 0;
@@ -581,11 +581,32 @@ static bool f32_tab_in_lds(const nb_model* m) { return !m->batch && f32_lds_byte
 static size_t f32_dyn_lds(const nb_model* m) { return f32_tab_in_lds(m) ? f32_lds_bytes(m) : 0; }
 
 // The adaptive-step kernel of a single FP64 model created with adaptive = 1 (else nullptr).
-static const void* adaptive_kernel(const nb_model* m) {
-  if (m->batch || !m->p.adaptive) return nullptr;
+template <int BS>
+static const void* adaptive_kernel_bs(const nb_model* m) {
   const bool l = tab_in_lds(m);
-  if (m->nf == 2) return l ? (const void*)&k_adaptive<2, true> : (const void*)&k_adaptive<2, false>;
-  return l ? (const void*)&k_adaptive<3, true> : (const void*)&k_adaptive<3, false>;
+  if (m->nf == 2) return l ? (const void*)&k_adaptive<2, true, BS> : (const void*)&k_adaptive<2, false, BS>;
+  return l ? (const void*)&k_adaptive<3, true, BS> : (const void*)&k_adaptive<3, false, BS>;
+}
+static const void* adaptive_kernel(const nb_model* m, int bs) {
+  if (m->batch || !m->p.adaptive) return nullptr;
+  return bs == kBlockSmall ? adaptive_kernel_bs<kBlockSmall>(m) : adaptive_kernel_bs<kBlock>(m);
+}
+// Threads per block of a three-flavour launch (and of adaptive runs) on a device of cus CUs:
+//  * up to 8 rows: 512, one block, which exchanges nothing with others (32 x 4 bins: 14.4 us
+//    per step, two blocks of 256 threads 18);
+//  * up to four rows per CU: 256, so that every wavefront has a SIMD to itself instead of
+//    sharing one while others idle (37 x 40 bins: 18.7 against 22.8 us per step; 100 x 100:
+//    23.0 against 31.1; 400 x 500: 46.8 against 64.6);
+//  * more: 512 (400 x 1000 mixed: 45.9 against 46.4; 1000 x 3000: 433 against 474, mixed 231
+//    against 344), where the block's exchange counts once for twice the wavefronts.
+static int block_of_rows(long long rows, int cus) {
+  return (rows > kBlock / 64 && rows <= (long long)cus * (kBlockSmall / 64)) ? kBlockSmall : kBlock;
+}
+// Adaptive runs of two flavours with more rows than one per SIMD stay at 256 threads (as the
+// fixed steps' default).
+static int adaptive_block(const nb_model* m, int cus) {
+  if (m->nf == 2 && m->rows > kBlock / 64) return kBlockSmall;
+  return block_of_rows(m->rows, cus);
 }
 
 // Packed row tails (k_advance<..., PK = true>): three flavours with FP64 state and
@@ -765,10 +786,10 @@ extern "C" int nb_bind(nb_model* m, void* dev_ws, size_t bytes, void* hip_stream
     if (rc) return rc;
   }
   if (cap[0] < 1) return fail(NB_EHIP, "stepping kernel cannot be resident");
-  if (adaptive_kernel(m)) {
+  const int abs_ = adaptive_block(m, cus);
+  if (adaptive_kernel(m, abs_)) {
     int nba = 0;
-    NB_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nba, adaptive_kernel(m), kBlock,
-                                                         advance_dyn_lds(m)));
+    NB_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nba, adaptive_kernel(m, abs_), abs_, advance_dyn_lds(m)));
     if (nba < 1) return fail(NB_EHIP, "adaptive kernel cannot be resident");
     cap_adaptive = std::min(cus * nba, kMaxBlocks);
     if (m->p.max_blocks > 0) cap_adaptive = std::min(cap_adaptive, (int)m->p.max_blocks);
@@ -829,11 +850,15 @@ extern "C" int nb_bind(nb_model* m, void* dev_ws, size_t bytes, void* hip_stream
   m->cap512 = cap[0];
   m->cap256 = cap[1];
   m->cap_adaptive = cap_adaptive;
+  m->bs_adaptive = abs_;
   // Default shape: two flavours (single, batched or extended) at 256 threads per block
-  // (three wavefronts per SIMD, and small models spread over twice as many CUs: 16 % faster
-  // on the 256-model batch and the 200k model, 9 % on the 60M extended model); three
-  // flavours at 512 (the 256-thread variant measured 19 % slower on the 800k model).
-  if (!m->tuned) m->bs = (m->nf == 2 && m->cap256 > 0) ? kBlockSmall : kBlock;
+  // (three wavefronts per SIMD, and small models spread over twice as many CUs: 200k model
+  // 23.4 against 25.0 us per step, 1024 beams 13.1 against 14.1); three flavours by their rows
+  // (block_of_rows).
+  if (!m->tuned) {
+    m->bs = (m->nf == 2) ? kBlockSmall : block_of_rows(m->rows, cus);
+    if (m->cap256 < 1) m->bs = kBlock;
+  }
   if (capacity(m, m->bs) < 1) m->bs = kBlock;   // a tuned block size this device cannot hold
   if (m->tune_blocks > capacity(m, m->bs)) m->tune_blocks = 0;
   m->nblocks = launch_blocks(m);
@@ -1088,7 +1113,7 @@ extern "C" int nb_run_adaptive(nb_model* m, double tol, double h_max_km, int64_t
                                nb_adaptive_stats* stats) {
   if (!m) return fail(NB_EINVAL, "model is NULL");
   if (!m->ws) return fail(NB_EUNBOUND, "no workspace bound");
-  if (!adaptive_kernel(m)) return fail(NB_EINVAL, "model was not created with adaptive = 1");
+  if (!adaptive_kernel(m, m->bs_adaptive)) return fail(NB_EINVAL, "model was not created with adaptive = 1");
   if (!(tol > 0.0) || !std::isfinite(tol)) return fail(NB_EINVAL, "tol must be > 0");
   if (max_attempts < 1) return fail(NB_EINVAL, "max_attempts must be >= 1");
   if (!std::isfinite(h_max_km)) return fail(NB_EINVAL, "h_max_km must be finite");
@@ -1139,9 +1164,10 @@ extern "C" int nb_run_adaptive(nb_model* m, double tol, double h_max_km, int64_t
   a.max_attempts = max_attempts;
   void* args[] = {&a};
   // one wavefront per row at most, at most the adaptive kernel's resident capacity
-  const int ablocks = (int)std::max<long long>(1, std::min<long long>((m->rows + 7) / 8, m->cap_adaptive));
-  const hipError_t e = hipLaunchKernel(adaptive_kernel(m), dim3(ablocks), dim3(kBlock), args,
-                                      advance_dyn_lds(m), m->stream);
+  const int bs = m->bs_adaptive, wpb = bs / 64;
+  const int ablocks = (int)std::max<long long>(1, std::min<long long>((m->rows + wpb - 1) / wpb, m->cap_adaptive));
+  const hipError_t e =
+      hipLaunchKernel(adaptive_kernel(m, bs), dim3(ablocks), dim3(bs), args, advance_dyn_lds(m), m->stream);
   if (e != hipSuccess) return fail(NB_EHIP, "adaptive launch: %s", hipGetErrorString(e));
   long long out[8];
   NB_HIP(hipMemcpyAsync(out, ctl, sizeof(out), hipMemcpyDeviceToHost, m->stream));

@@ -1675,24 +1675,24 @@ template __global__ void k_advance<3, double, false, false, false, kBlock, true>
 // advance r, double h if E <= tol^2/128 and 2h <= h_max) or reject (keep X and the saved
 // moments of X, halve h).  The last step is shortened to end at r_end.  At the end each
 // wavefront copies its rows back to X if the result sits in the second buffer.
-template <int NF, bool TLDS>
-__global__ void __launch_bounds__(kBlock) k_adaptive(StepArgs a) {
+template <int NF, bool TLDS, int BS>
+__global__ void __launch_bounds__(BS) k_adaptive(StepArgs a) {
   constexpr int NC = (NF == 2) ? 3 : 8;
   constexpr int NV = 2 * NC;
   __shared__ double sJ[4][NV];
   __shared__ double sJsave[NV];
   __shared__ double sE[1];
-  __shared__ RedLds<NV, kBlock, true> R;
-  __shared__ double snn_all[kBlock / 64][NF == 2 ? kC2Size : kL3Size];   // stage constants
-  __shared__ double skr[NF == 3 ? kBlock / 64 : 1][NF == 3 ? kKeep3 * kRow3 : 1];
+  __shared__ RedLds<NV, BS, true> R;
+  __shared__ double snn_all[BS / 64][NF == 2 ? kC2Size : kL3Size];   // stage constants
+  __shared__ double skr[NF == 3 ? BS / 64 : 1][NF == 3 ? kKeep3 * kRow3 : 1];
   __shared__ double sfv[NF == 3 ? 18 : 1];
   __shared__ double s_sct[kSinCosTab];   // sin/cos constants of the two-flavour rotations
   extern __shared__ __align__(16) double dyn_tab[];
   // the wavefront index as a wave-uniform (scalar) value: the row indices, their divisions
   // and the row base offsets derived from it then live in scalar registers
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const long long gw = (long long)blockIdx.x * (kBlock / 64) + wid;
-  const long long nw = (long long)gridDim.x * (kBlock / 64);
+  const long long gw = (long long)blockIdx.x * (BS / 64) + wid;
+  const long long nw = (long long)gridDim.x * (BS / 64);
   if (launch_aborted(a.sync)) return;
   const double* tab = a.tab;
   red_init(R);
@@ -1700,7 +1700,7 @@ __global__ void __launch_bounds__(kBlock) k_adaptive(StepArgs a) {
   __syncthreads();
   if constexpr (TLDS) {
     const int ntab = ((NF == 2) ? 2 : kVacRows3) * a.NE + a.NS * a.NE;
-    for (int i = threadIdx.x; i < ntab; i += kBlock) dyn_tab[i] = a.tab[i];
+    for (int i = threadIdx.x; i < ntab; i += BS) dyn_tab[i] = a.tab[i];
     __syncthreads();
     tab = dyn_tab;
   }
@@ -1717,7 +1717,7 @@ __global__ void __launch_bounds__(kBlock) k_adaptive(StepArgs a) {
   double emax = 0.0;
   I128 T = i128_zero();
   const int nrw = wave_rows(gw, nw, (long long)a.NS * a.NU);
-  __shared__ double srt[NF == 2 ? kBlock / 64 : 1][NF == 2 ? row_table2(false) : 1];
+  __shared__ double srt[NF == 2 ? BS / 64 : 1][NF == 2 ? row_table2(false) : 1];
   double* rt = srt[NF == 2 ? wid : 0];
   auto stage = [&](auto kind, const StepGeo& G) {
     constexpr int K = decltype(kind)::value;
@@ -1808,10 +1808,14 @@ __global__ void __launch_bounds__(kBlock) k_adaptive(StepArgs a) {
   }
 }
 
-template __global__ void k_adaptive<2, true>(StepArgs);
-template __global__ void k_adaptive<2, false>(StepArgs);
-template __global__ void k_adaptive<3, true>(StepArgs);
-template __global__ void k_adaptive<3, false>(StepArgs);
+template __global__ void k_adaptive<2, true, kBlock>(StepArgs);
+template __global__ void k_adaptive<2, false, kBlock>(StepArgs);
+template __global__ void k_adaptive<3, true, kBlock>(StepArgs);
+template __global__ void k_adaptive<3, false, kBlock>(StepArgs);
+template __global__ void k_adaptive<2, true, kBlockSmall>(StepArgs);
+template __global__ void k_adaptive<2, false, kBlockSmall>(StepArgs);
+template __global__ void k_adaptive<3, true, kBlockSmall>(StepArgs);
+template __global__ void k_adaptive<3, false, kBlockSmall>(StepArgs);
 
 // --------------------------------------------------------------- batched models
 // Many independent two-flavour models in one persistent launch (shared step grid).

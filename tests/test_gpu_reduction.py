@@ -59,3 +59,30 @@ def test_row_lengths(nb, oracle, nf, n_energy, kw):
     o = oracle.Model(d)
     o.run()
     np.testing.assert_array_equal(m.get_state().cpu().numpy(), o.get_state())
+
+
+@pytest.mark.parametrize("n_energy,n_u", [(65, 4), (96, 8), (130, 8), (2000, 4)])
+def test_packed_tails_at_512_threads(nb, oracle, n_energy, n_u):
+    """One row per wavefront of 512-thread blocks: the packed-row-tail variant."""
+    d = workloads.small_params(n_flavor=3, n_energy=n_energy, n_u=n_u, n_steps=4)
+    print(f"packed tails: {n_energy} x {n_u}", flush=True)
+    m = nb.Model(d)
+    m.set_tuning(512)
+    m.run()
+    o = oracle.Model(d)
+    o.run()
+    np.testing.assert_array_equal(m.get_state().cpu().numpy(), o.get_state())
+
+
+@pytest.mark.parametrize("nf,n_u", [(2, 4), (2, 5), (3, 4), (3, 5), (3, 512), (3, 513)])
+def test_adaptive_block_sizes(nb, oracle, nf, n_u):
+    """Adaptive runs at the row counts where the threads per block change."""
+    d = workloads.small_params(n_flavor=nf, n_energy=5, n_u=n_u, n_steps=30, r_start_km=600.0,
+                               r_end_km=601.0)
+    print(f"adaptive: {nf} flavours, {2 * n_u} rows", flush=True)
+    m = nb.Model(d, adaptive=True)
+    st = m.run_adaptive(1e-7)
+    o = oracle.Model(d)
+    so = o.run_adaptive(1e-7)
+    assert (st["accepted"], st["rejected"]) == (so["accepted"], so["rejected"])
+    np.testing.assert_array_equal(m.get_state().cpu().numpy(), o.get_state())
