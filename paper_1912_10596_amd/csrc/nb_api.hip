@@ -157,7 +157,7 @@ struct nb_model {
   const unsigned* cancel_dev = nullptr;  // its device address
   unsigned long long ticks_per_s = 0;
   size_t off_X = 0, off_tab = 0, off_sync = 0, off_ctl = 0;
-  size_t off_models = 0, off_waves = 0, off_acc = 0, need = 0;
+  size_t off_models = 0, off_waves = 0, off_counts = 0, off_acc = 0, need = 0;
   size_t off_adj = 0, off_spill = 0, off_jhist = 0, off_dtab = 0, off_aout = 0, off_X2 = 0;
   double* jhist = nullptr;           // set while the adjoint's forward pass records moments
   int adj_blocks = 0, adj_bpt = 0;
@@ -509,7 +509,7 @@ static size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 // (batches) model descriptors | wave row ranges | moment accumulators | (adjoint) its
 // regions | (adaptive) the second state buffer.
 struct Layout {
-  size_t X, tab, sync, ctl, models, waves, acc, adj, spill, jhist, dtab, aout, X2, need;
+  size_t X, tab, sync, ctl, models, waves, counts, acc, adj, spill, jhist, dtab, aout, X2, need;
 };
 
 // The adjoint (single two-flavour model with adjoint_ckpt = K > 0) reserves state slots
@@ -535,13 +535,16 @@ static Layout layout_of(const nb_model* m) {
   o = align256(o + sizeof(long long) * kCtlWords);
   L.models = o;
   L.waves = o;
+  L.counts = o;
   L.acc = o;
   if (m->batch) {
     o = align256(o + sizeof(BatchModel) * (size_t)m->nmodels);
     L.waves = o;
     o = align256(o + sizeof(long long) * ((size_t)kMaxBlocks * (kBlock / 64) + 1));
+    L.counts = o;
+    o = align256(o + sizeof(int) * (size_t)m->nmodels);
     L.acc = o;
-    o = align256(o + sizeof(unsigned long long) * (size_t)kAccSets * m->nmodels * 6 * kAccLimbs);
+    o = align256(o + sizeof(unsigned long long) * (size_t)kAccPerModel * m->nmodels);
   }
   L.adj = L.jhist = L.dtab = L.aout = L.spill = o;
   if (adjoint_enabled(m)) {
@@ -686,7 +689,7 @@ static int clear_sync(nb_model* m, int keep, const unsigned* cancel, int words) 
 }
 static int zero_sync(nb_model* m, int keep, int words) { return clear_sync(m, keep, m->cancel_dev, words); }
 // Words the fixed-step launches of a model use.
-static int step_sync_words(const nb_model* m) { return m->batch ? kSyncArriveEnd : kSyncRedEnd; }
+static int step_sync_words(const nb_model* m) { return m->batch ? kSyncDoneEnd : kSyncRedEnd; }
 
 extern "C" int nb_reset(nb_model* m) {
   if (!m) return fail(NB_EINVAL, "model is NULL");
@@ -744,6 +747,15 @@ static int upload_partition(nb_model* m) {
     }
   }
   for (int i = w + 1; i <= waves; ++i) w0[(size_t)i] = m->rows;
+  // wavefronts that own rows of each model (the count its stages wait for)
+  std::vector<int> count((size_t)m->nmodels, 0);
+  for (int i = 0, k = 0; i < waves; ++i) {
+    if (w0[(size_t)i] >= w0[(size_t)i + 1]) continue;
+    while (w0[(size_t)i] >= m->subs[(size_t)k].row0 + 2LL * m->subs[(size_t)k].NU) ++k;
+    for (int q = k; q < m->nmodels && m->subs[(size_t)q].row0 < w0[(size_t)i + 1]; ++q) ++count[(size_t)q];
+  }
+  NB_HIP(hipMemcpyAsync(m->ws + m->off_counts, count.data(), sizeof(int) * count.size(), hipMemcpyHostToDevice,
+                        m->stream));
   NB_HIP(hipMemcpyAsync(m->ws + m->off_waves, w0.data(), sizeof(long long) * w0.size(),
                         hipMemcpyHostToDevice, m->stream));
   NB_HIP(hipStreamSynchronize(m->stream));
@@ -804,6 +816,7 @@ extern "C" int nb_bind(nb_model* m, void* dev_ws, size_t bytes, void* hip_stream
   m->off_ctl = L.ctl;
   m->off_models = L.models;
   m->off_waves = L.waves;
+  m->off_counts = L.counts;
   m->off_acc = L.acc;
   m->off_adj = L.adj;
   m->off_spill = L.spill;
@@ -938,7 +951,7 @@ static int enqueue_advance(nb_model* m, long long k) {
   const unsigned long long timeout = m->ticks_per_s * 20ull;
   if (m->batch) {
     unsigned long long* acc = acc_words(m);
-    long long nacc = (long long)kAccSets * m->nmodels * 6 * kAccLimbs;
+    long long nacc = (long long)kAccPerModel * m->nmodels;
     void* zz[] = {&acc, &nacc};
     NB_HIP(hipLaunchKernel((const void*)&k_zero_u64, dim3(64), dim3(256), zz, 0, m->stream));
     BatchArgs a{};
@@ -948,6 +961,7 @@ static int enqueue_advance(nb_model* m, long long k) {
     a.models = (const BatchModel*)(m->ws + m->off_models);
     a.nmodels = m->nmodels;
     a.wave_row0 = (const long long*)(m->ws + m->off_waves);
+    a.wave_count = (const int*)(m->ws + m->off_counts);
     a.total_rows = m->rows;
     a.acc = acc;
     a.sync = sync;
@@ -961,6 +975,12 @@ static int enqueue_advance(nb_model* m, long long k) {
     a.renorm = m->p.renorm;
     a.timeout_ticks = timeout;
     a.cancel = m->cancel_dev;
+    // Wavefronts with more rows than they keep (kRowKeep) run for hundreds of microseconds per
+    // stage: free to run ahead, models drift apart over a launch and the last ones end on a
+    // nearly empty device (256 models of 64M beams: 2.53 ms per step against 2.35 with the
+    // blocks meeting after every step).  Small batches gain by not meeting (16 models of
+    // 20-50 x 5-50 bins: 24.9 us per step against 58 with a grid barrier per stage).
+    a.lockstep = m->rows > (long long)kBatchKeep * m->nblocks * (m->bs / 64) ? 1 : 0;
     void* args[] = {&a};
     const hipError_t e =
         hipLaunchKernel(advance_kernel(m, m->bs), dim3(m->nblocks), dim3(m->bs), args, 0, m->stream);
@@ -1059,7 +1079,7 @@ extern "C" int nb_run(nb_model* m) {
 constexpr int kStaticModels = 1024;
 constexpr size_t kStaticSync64 = ((size_t)kSyncWords + 1) / 2;         // sync words, as u64
 constexpr size_t kStaticAccOff = (kStaticSync64 + 31) / 32 * 32;       // 256-byte boundary
-constexpr size_t kStaticWords = kStaticAccOff + (size_t)kAccSets * kStaticModels * 6 * kAccLimbs;
+constexpr size_t kStaticWords = kStaticAccOff + (size_t)kAccPerModel * kStaticModels;
 static __device__ __align__(256) unsigned long long scratch[kStaticWords];
 
 // Device address of this device's copy of scratch, looked up once per device with that

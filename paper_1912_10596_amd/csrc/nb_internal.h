@@ -28,16 +28,17 @@ constexpr int kSyncRedEnd = kSyncPub + 2 * 2 * kRedCopies * kRedStride;
 // Adaptive runs: one tagged 64-bit error word per block, in two regions (even, odd epochs).
 constexpr int kSyncErr = kSyncRedEnd;
 constexpr int kSyncErrEnd = kSyncErr + 2 * 2 * kMaxBlocks;
-// Batches: kFlagCopies copies of the release flag (block b polls copy b % kFlagCopies), each
-// the epoch + 1 of the last release, and one arrival line per block.
-constexpr int kSyncFlag = kSyncErrEnd;
-constexpr int kSyncArrive = kSyncFlag + kFlagCopies * kLineWords;  // [kMaxBlocks] lines
-constexpr int kSyncArriveEnd = kSyncArrive + kMaxBlocks * kLineWords;
+// Batches: the count of blocks that have ended their steps, and the blocks' arrivals at the
+// end of a step, one line per copy, then the copies' published steps.
+constexpr int kSyncDone = kSyncErrEnd;
+constexpr int kSyncStep = kSyncDone + kLineWords;
+constexpr int kSyncStepPub = kSyncStep + kRedCopies * kLineWords;
+constexpr int kSyncDoneEnd = kSyncStepPub + kRedCopies * kLineWords;
 // The adjoint's sums: tagged 64-bit words (every word carries the barrier epoch it belongs
 // to), kFlagCopies copies of the results (block b reads copy b % kFlagCopies) of kTagLines
 // lines each, then one slot of kTagLines lines of partials per block.
 constexpr int kTagLines = 4;
-constexpr int kSyncJTag = kSyncArriveEnd;
+constexpr int kSyncJTag = kSyncDoneEnd;
 constexpr int kSyncPart = kSyncJTag + kFlagCopies * kTagLines * kLineWords;
 constexpr int kSyncWords = kSyncPart + kMaxBlocks * kTagLines * kLineWords;
 constexpr int kTagWords64 = kTagLines * kLineWords / 2;   // 64-bit words per copy or slot
@@ -96,8 +97,13 @@ struct BatchModel {
   double s1, s0, p2e1, p2e0;
 };
 
-constexpr int kAccSets = 6;   // moment accumulator sets, rotated by barrier epoch
-constexpr int kAccLimbs = 3;  // carry-save limbs of 42 bits per 128-bit sum
+// Rows whose constants a two-flavour wavefront keeps through a step.
+constexpr int kBatchKeep = 16;
+// Moment sums of a batch, per model: kAccWords counted accumulators (6 sums of 3 chunks, 4
+// words apart) on lines of their own, and kAccSets published sets of 24 words, rotated by
+// the epoch.
+constexpr int kAccWords = 32, kPubWords = 24, kAccSets = 6;
+constexpr int kAccPerModel = kAccWords + kAccSets * kPubWords;
 
 // Arguments of the batched two-flavour stepping kernel.
 struct BatchArgs {
@@ -108,7 +114,8 @@ struct BatchArgs {
   int nmodels;
   const long long* wave_row0;   // [waves + 1]: each wavefront's contiguous row range
   long long total_rows;
-  unsigned long long* acc;      // [kAccSets][nmodels][6][kAccLimbs]
+  const int* wave_count;        // [nmodels]: wavefronts whose ranges meet the model
+  unsigned long long* acc;      // [nmodels][kAccWords], then [kAccSets][nmodels][kPubWords]
   unsigned int* sync;
   long long* step_ctl;
   long long nsteps, total_steps;
@@ -116,6 +123,7 @@ struct BatchArgs {
   int ne_power, renorm;
   unsigned long long timeout_ticks;
   const unsigned* cancel;
+  int lockstep;                 // 1: the blocks meet after every step
 };
 
 // Arguments of the two-flavour reverse (adjoint) kernel.  Beam b belongs to thread

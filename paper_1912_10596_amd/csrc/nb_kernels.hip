@@ -371,8 +371,9 @@ __device__ __forceinline__ void put_stage2(double* cb, int lane, const Radial& g
 constexpr int kRowS = 23, kRowA = 24;
 constexpr int kRowC = 26;    // doubles per block of a row group's table (25 used)
 // Rows whose constants a wavefront of the bulb model keeps through a step (kRowP doubles
-// each): also cos at the three stage radii, 1/cos at rm and r1, and u.
-constexpr int kRowCos = 25, kRowIcm = 28, kRowIc1 = 29, kRowU = 30, kRowP = 33, kRowKeep = 16;
+// each, an even number, so that pairs are read together): also cos at the three stage radii,
+// 1/cos at rm and r1, and u.
+constexpr int kRowCos = 25, kRowIcm = 28, kRowIc1 = 29, kRowU = 30, kRowP = 34, kRowKeep = kBatchKeep;
 // Stage generator of beam (bx, bz) from its block c = [h/cos, sg lam, nu-nu term] (the
 // arithmetic of gen2: subtracting a term is adding its negative).
 __device__ __forceinline__ void gen2c(double bx, double bz, const double* c, double f[3]) {
@@ -628,7 +629,8 @@ __device__ __forceinline__ void fold_rows2(int lane, long long* fl, int nrows, c
   __asm__ volatile("" ::: "memory");
 }
 
-template <int KIND, bool EXT, int R>
+// RS: doubles per block of the table rt.
+template <int KIND, bool EXT, int R, int RS>
 __device__ __forceinline__ void group2(double* X, long long plane, long long gb0, int NE, int gn,
                                        const double* tab, const double* cb, const double* rt, int renorm,
                                        int lane, long long* fl, I128& T, int& err, const double* sct) {
@@ -649,7 +651,7 @@ __device__ __forceinline__ void group2(double* X, long long plane, long long gb0
   if (lane < nbeam) {
     q0 = X[gb0 + lane]; q1 = X[gb0 + lane + plane]; q2 = X[gb0 + lane + 2 * plane];
     if (PF) {
-      tx = tab[k]; tz = tab[NE + k]; tw = tab[(size_t)(2 + (int)rt[i * kRowC + kRowS]) * NE + k];
+      tx = tab[k]; tz = tab[NE + k]; tw = tab[(size_t)(2 + (int)rt[i * RS + kRowS]) * NE + k];
     }
   }
   unsigned long long acc[3] = {0ull, 0ull, 0ull};
@@ -670,13 +672,13 @@ __device__ __forceinline__ void group2(double* X, long long plane, long long gb0
           k2 -= NE;
           ++i2;
         }
-        tx = tab[k2]; tz = tab[NE + k2]; tw = tab[(size_t)(2 + (int)rt[i2 * kRowC + kRowS]) * NE + k2];
+        tx = tab[k2]; tz = tab[NE + k2]; tw = tab[(size_t)(2 + (int)rt[i2 * RS + kRowS]) * NE + k2];
       }
     }
     __asm__ volatile("" ::: "memory");   // the row constants are re-read from LDS per beam
     unsigned long long x0 = 0ull, x1 = 0ull, x2 = 0ull;
     if (on) {
-      const double* rc = rt + i * kRowC;
+      const double* rc = rt + i * RS;
       const int sr = (int)rc[kRowS];
       if (KIND >= 1) {
         const double bx = PF ? bxc : tab[k], bz = PF ? bzc : tab[NE + k];
@@ -740,7 +742,7 @@ __device__ __forceinline__ void group2(double* X, long long plane, long long gb0
       cnt = 0;
       if constexpr (R == 1) {
         const long long t = wave_fold<3>(ended, lane);
-        const double* rr = rt + r * kRowC;
+        const double* rr = rt + r * RS;
         close_row<3, NM>(sc, lane, i128_from(t), (double)t, rr[20], T, err, rr[21], rr[22]);
         ++r;
       } else {
@@ -848,7 +850,7 @@ __device__ __forceinline__ void stage2(const StepArgs& a, double h, const double
       }
       __asm__ volatile("" ::: "memory");
       if (!ADAPT && NE <= kGroupMaxNE) {
-        group2<KIND, true, kFoldRowsExt>(Xo, plane, row * NE, NE, gn, tab, cb, rt, renorm, lane, fl, T, err, sct);
+        group2<KIND, true, kFoldRowsExt, kRowC>(Xo, plane, row * NE, NE, gn, tab, cb, rt, renorm, lane, fl, T, err, sct);
         row += gn;
       } else {
         for (int i = 0; i < gn; ++i, ++row)
@@ -1820,145 +1822,222 @@ template __global__ void k_adaptive<3, false, kBlockSmall>(StepArgs);
 // --------------------------------------------------------------- batched models
 // Many independent two-flavour models in one persistent launch (shared step grid).
 // Each wavefront owns a contiguous, cost-balanced range of the concatenated rows, so it
-// meets only a few models per stage.  Its per-model moment totals are added, as three
-// 42-bit limbs, to per-model integer accumulators with device atomics (exact, so the
-// result is the same integer as the single-model reduction); a reader rebuilds the
-// 128-bit sum from the limbs.  Accumulator sets rotate with the barrier epoch: set e % 6
-// collects epoch e, and set (e + 1) % 6 -- last read during epoch e - 1 -- is cleared
-// during epoch e.
-constexpr unsigned long long kMask42 = (1ull << 42) - 1ull;
+// meets only a few models per stage.  Models are independent, so there is no grid barrier:
+// a stage of a model waits only for the wavefronts that own rows of that model.
+//
+// Per model and epoch (barrier index) the wavefronts' exact 128-bit totals meet as in the
+// single-model reduction, one level up: 6 sums of 3 chunks of 32 bits (the last signed and
+// biased by 2^31; a total is below 2^93), each added with one atomic to a counted word (50
+// bits of running sum, 14 bits of count: at most 2^14 wavefronts); the wavefront whose add
+// completes the model's count publishes the running sum under a 14-bit epoch tag, and readers
+// take differences of consecutive epochs.  Six published sets rotate: the final update of a
+// step still reads the sums of stage 1 and those before it, five epochs back, and set
+// e % 6 is rewritten at epoch e only after every wavefront of the model has added for e, that
+// is after all it read up to its stage e.  A wavefront's add for e follows its reads for e - 1
+// of every model, and waits point only to earlier epochs, so they cannot form a cycle.
+// A grid barrier with arrival lines gathered by one block, a release flag and a read of
+// the accumulators took 14 us per stage for 16 small models, of which the beams are 1 us.
+constexpr unsigned long long kTag14 = 16383ull;
 
-__device__ __forceinline__ void acc_add(unsigned long long* slot, const I128& v) {
-  const unsigned long long l0 = v.lo & kMask42;
-  const unsigned long long l1 = ((v.lo >> 42) | ((unsigned long long)v.hi << 22)) & kMask42;
-  const unsigned long long l2 = (unsigned long long)(v.hi >> 20);
-  __hip_atomic_fetch_add(slot + 0, l0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_fetch_add(slot + 1, l1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_fetch_add(slot + 2, l2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ unsigned long long* batch_pub(const BatchArgs& a, unsigned epoch, int m) {
+  return a.acc + (size_t)a.nmodels * kAccWords + ((size_t)(epoch % kAccSets) * a.nmodels + m) * kPubWords;
 }
-__device__ __forceinline__ I128 acc_read(const unsigned long long* slot) {
-  const unsigned long long s0 = __hip_atomic_load(slot + 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const unsigned long long s1 = __hip_atomic_load(slot + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const long long s2 = (long long)__hip_atomic_load(slot + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  I128 t = I128{s0, 0ll};
-  t = i128_add(t, I128{s1 << 42, (long long)(s1 >> 22)});
-  t = i128_add(t, I128{0ull, s2 << 20});
-  return t;
+// Add this wavefront's totals T of model m (lanes of fold_comp, fold_moment) for the epoch;
+// n: the model's wavefronts.  sx: 12 words of the wavefront's LDS.
+__device__ __forceinline__ void batch_publish(const BatchArgs& a, int m, unsigned n, unsigned epoch, const I128& T,
+                                              int lane, unsigned long long* sx) {
+  const int mo = fold_moment<3>(lane), co = fold_comp<3>(lane);
+  __asm__ volatile("" ::: "memory");   // the wave's LDS operations complete in program order
+  if (mo < 2 && co < 3) {
+    sx[2 * (mo * 3 + co)] = T.lo;
+    sx[2 * (mo * 3 + co) + 1] = (unsigned long long)T.hi;
+  }
+  __asm__ volatile("" ::: "memory");
+  const int v = lane >> 2, l = lane & 3;
+  if (lane < 24 && l < 3) {
+    const unsigned long long w = sx[2 * v + (l == 2 ? 1 : 0)];
+    const unsigned c = (l == 1) ? (unsigned)(w >> 32) : ((l == 2) ? (unsigned)w + 0x80000000u : (unsigned)w);
+    const unsigned long long add = ((unsigned long long)c << 14) + 1ull, n0 = (unsigned long long)epoch * n;
+    const unsigned long long sum = __hip_atomic_fetch_add(a.acc + (size_t)m * kAccWords + lane, add, __ATOMIC_RELAXED,
+                                                          __HIP_MEMORY_SCOPE_AGENT) + add;
+    if ((((unsigned)sum - (unsigned)n0) & (unsigned)kTag14) == (n & (unsigned)kTag14))
+      __hip_atomic_store(batch_pub(a, epoch, m) + lane, ((sum - n0 - n) & ~kTag14) | ((epoch + 1u) & kTag14),
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
 }
-__device__ __forceinline__ unsigned long long* acc_slot(const BatchArgs& a, unsigned epoch, int m) {
-  return a.acc + ((size_t)(epoch % kAccSets) * a.nmodels + m) * 6 * kAccLimbs;
-}
-
-// Flags-only grid barrier (the sums are already in the accumulators, added with
-// agent-scope atomics before the workgroup barrier inside the arrival).
-__device__ bool grid_barrier(const BatchArgs& a, unsigned epoch) {
-  const unsigned want = epoch + 1u;
-  if (blockIdx.x != 0) return arrive_and_wait(a.sync, a.cancel, a.timeout_ticks, want);
-  if (!wait_arrivals(a.sync, a.cancel, a.timeout_ticks, want)) return false;
-  release_grid(a.sync, want);
+// The moments J^(1..KIND) of model m for stage KIND of epoch `epoch` (NEWEST: only the last)
+// into Jv.  Returns false if the wait was abandoned (time limit or abort).
+template <int KIND, bool NEWEST>
+__device__ __forceinline__ bool batch_moments(const BatchArgs& a, int m, unsigned n, unsigned epoch, double p2e0,
+                                              double p2e1, int lane, double (*Jv)[6]) {
+  constexpr int J0 = NEWEST ? KIND - 1 : 0;
+  const int v = lane >> 2, l = lane & 3;
+  const bool on = lane < 24 && l < 3;
+  // words of the sums of epochs epoch - KIND - 1 + J0 (the difference's base; before epoch 0
+  // a set not yet written), ..., epoch - 1
+  unsigned long long w[KIND + 1 - J0];
+#pragma unroll
+  for (int i = 0; i <= KIND - J0; ++i) w[i] = 0ull;
+  if (on)
+#pragma unroll
+    for (int i = 0; i < KIND - J0; ++i)
+      w[i] = __hip_atomic_load(batch_pub(a, epoch + (unsigned)(kAccSets - (KIND + 1 - J0 - i)), m) + lane, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+  int ok = 1;
+  if (on) {
+    const unsigned long long* q = batch_pub(a, epoch - 1u, m) + lane;
+    const unsigned long long tag = epoch & kTag14, t0 = wall_clock64();
+    for (unsigned it = 1;; ++it) {
+      const unsigned long long x = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      w[KIND - J0] = x;
+      if ((x & kTag14) == tag) break;
+      if ((it & 31u) == 0u && give_up(a.sync, a.cancel, t0, a.timeout_ticks, it)) {
+        ok = 0;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+  }
+  if (__any(!ok)) return false;
+  __asm__ volatile("" ::: "memory");
+#pragma unroll
+  for (int i = J0; i < KIND; ++i) {
+    // (the fields are differences modulo 2^50; the last chunk less its bias is signed)
+    unsigned long long d = ((w[i + 1 - J0] & ~kTag14) - (w[i - J0] & ~kTag14)) >> 14;
+    if (l == 2) d -= (unsigned long long)n << 31;
+    const unsigned long long c1 = dpp_u64<0x55>(d), c2 = dpp_u64<0xAA>(d);   // lanes 1, 2 of each four
+    const I128 tot = i128_add(i128_add(I128{d, 0ll}, I128{c1 << 32, (long long)(c1 >> 32)}), I128{0ull, (long long)c2});
+    if (on && l == 0) Jv[i][v] = i128_to_double(tot) * (v < 3 ? p2e0 : p2e1);
+  }
+  __asm__ volatile("" ::: "memory");
   return true;
 }
 
+// All blocks meet (a.lockstep): counted arrivals per die, published by the block that
+// completes them, polled by every block.  i: the number of earlier meetings of the launch.
+__device__ __forceinline__ bool batch_meet(const BatchArgs& a, unsigned i) {
+  const int tid = threadIdx.x;
+  int ok = 1;
+  __syncthreads();
+  if (tid == 0) {
+    const unsigned c = blockIdx.x % kRedCopies, n = (gridDim.x + (kRedCopies - 1) - c) / kRedCopies;
+    if (__hip_atomic_fetch_add(a.sync + kSyncStep + c * kLineWords, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u ==
+        (i + 1u) * n)
+      __hip_atomic_store(a.sync + kSyncStepPub + c * kLineWords, i + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (tid < kRedCopies && tid < (int)gridDim.x) {
+    const unsigned long long t0 = wall_clock64();
+    for (unsigned it = 1;; ++it) {
+      if (__hip_atomic_load(a.sync + kSyncStepPub + tid * kLineWords, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= i + 1u)
+        break;
+      if ((it & 31u) == 0u && give_up(a.sync, a.cancel, t0, a.timeout_ticks, it)) {
+        ok = 0;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+  }
+  return !__syncthreads_or(!ok);
+}
+
+// A wavefront's part of the batch: its rows, the first model it meets and, where all its rows
+// are of that model and at most kRowKeep, kept = their number: such a wavefront keeps its
+// rows' constants (keep_geo2, keep_nunu2) like those of the bulb model.
+struct BatchWave {
+  long long r0, r1;
+  int m0, kept;
+};
+// A value that is the same in every lane, as a scalar.
+__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ long long uni(long long x) {
+  return (long long)(((unsigned long long)(unsigned)uni((int)(x >> 32)) << 32) | (unsigned)uni((int)x));
+}
 // Rows are taken in groups of up to kGroup rows of one model: lane l first computes the
 // constants of the group's row l (row_setup2, the arithmetic every lane of the row would
-// otherwise repeat) into the wave's table rt, then the rows run one after the other.
+// otherwise repeat) into the wave's table rt, then the group's beams are streamed (group2).
 constexpr int kGroup = 16;
-template <int KIND>
-__device__ void batch_stage(const BatchArgs& a, long long n, unsigned epoch, long long r0w,
-                            long long r1w, int lane, double (*Jv)[6], double* cb, double* rt,
-                            const double* sct, int& err) {
+__device__ __forceinline__ void batch_radii(const BatchArgs& a, long long n, const BatchModel* md, int lane, double* cb) {
   const double r0 = a.rs + (double)n * a.h;
   const double rm = r0 + 0.5 * a.h;
   const double r1 = a.rs + (double)(n + 1) * a.h;
-  // the moment component of the lane's total (J0 | J1), or -1
-  const int tv = (fold_moment<3>(lane) < 2 && fold_comp<3>(lane) < 3) ? fold_moment<3>(lane) * 3 + fold_comp<3>(lane) : -1;
-  // epoch of the slot holding J^(i+1) of this step: epoch - KIND + i
-  int m = -1;
-  long long mrow0 = 0, mrow1 = 0, mbeam0 = 0, mtab0 = 0;
-  int mNE = 0, mNU = 1;
+  const double lam0 = md->lam0;
+  __asm__ volatile("" ::: "memory");
+  put_stage2(cb, lane, radial(a.R, a.ne_power, lam0, r0), radial(a.R, a.ne_power, lam0, rm),
+             radial(a.R, a.ne_power, lam0, r1), Scales{md->s1, md->s0, md->p2e1, md->p2e0});
+}
+// Before a step: radial profiles and geometry of a keeping wavefront.
+__device__ __forceinline__ void batch_prep(const BatchArgs& a, long long n, const BatchWave& W, int lane, double* cb,
+                                           double* rt) {
+  if (!W.kept) return;
+  batch_radii(a, n, a.models + W.m0, lane, cb);
+  keep_geo2(cb, a.h, lane, W.kept, rt);
+}
+template <int KIND>
+__device__ __forceinline__ bool batch_stage(const BatchArgs& a, long long n, unsigned epoch, const BatchWave& W, int lane,
+                                            double (*Jv)[6], double* cb, double* rt, unsigned long long* sx,
+                                            const double* sct, int& err) {
   const double* J[4] = {Jv[0], Jv[1], Jv[2], Jv[3]};   // this wave's LDS block
-  I128 T = i128_zero();
-  for (long long row = r0w; row < r1w;) {
-    if (m < 0 || row >= mrow1) {
-      if (m >= 0 && tv >= 0) acc_add(acc_slot(a, epoch, m) + tv * kAccLimbs, T);
-      T = i128_zero();
-      if (m < 0) {                      // first model of the range: binary search
-        int lo = 0, hi = a.nmodels - 1;
-        while (lo < hi) {
-          const int mid = (lo + hi + 1) >> 1;
-          if (a.models[mid].row0 <= row) lo = mid; else hi = mid - 1;
-        }
-        m = lo;
-      } else {
-        while (row >= a.models[m].row0 + 2LL * a.models[m].NU) ++m;
-      }
-      const BatchModel* md = a.models + m;
-      mrow0 = md->row0;
-      mNE = md->NE;
-      mNU = md->NU;
-      mrow1 = mrow0 + 2LL * mNU;
-      mbeam0 = md->beam0;
-      mtab0 = md->tab0;
-      const double lam0 = md->lam0;
-      const Scales sc{md->s1, md->s0, md->p2e1, md->p2e0};
-      put_stage2(cb, lane, radial(a.R, a.ne_power, lam0, r0), radial(a.R, a.ne_power, lam0, rm),
-                 radial(a.R, a.ne_power, lam0, r1), sc);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const bool need = (i == 0) ? (KIND == 1 || KIND == 2 || KIND == 4)
-                                   : (i == 1 ? (KIND == 2 || KIND == 4) : (i == 2 ? KIND >= 3 : KIND == 4));
-        if (!need) continue;
-        const unsigned long long* sl = acc_slot(a, epoch - (unsigned)KIND + (unsigned)i, m);
-#pragma unroll
-        for (int v = 0; v < 6; ++v)
-          Jv[i][v] = i128_to_double(acc_read(sl + v * kAccLimbs)) * (v < 3 ? sc.p2e0 : sc.p2e1);
-      }
-    }
-    const long long gend = min(min(r1w, mrow1), row + (long long)kGroup);
-    const int gn = (int)(gend - row);
-    __asm__ volatile("" ::: "memory");   // the previous group's rows have read their blocks
-    if (lane < gn) {
-      const int lr = (int)(row + lane - mrow0);
-      const int s = lr / mNU;
-      const int j = lr - s * mNU;
-      row_setup2<KIND, false>(u_of(j, mNU), a.h, cb, J, 0.0, 0.0, s, s ? -1.0 : 1.0, rt + lane * kRowC);
-    }
-    __asm__ volatile("" ::: "memory");
-    if (mNE <= kGroupMaxNE) {
-      group2<KIND, false, kFoldRowsBatch>(a.X, a.plane, mbeam0 + (row - mrow0) * mNE, mNE, gn, a.tab + mtab0, cb, rt,
-                          a.renorm, lane, nullptr, T, err, sct);
-      row += gn;
+  double enone = 0.0;
+  int m = W.m0;
+  for (long long row = W.r0; row < W.r1; ++m) {   // the models the range meets
+    const BatchModel* md = a.models + m;
+    const long long mrow0 = uni(md->row0), mbeam0 = uni(md->beam0);
+    const int mNE = uni(md->NE), mNU = uni(md->NU);
+    const unsigned nw = (unsigned)uni(a.wave_count[m]);
+    const long long mend = min(W.r1, mrow0 + 2LL * mNU);
+    const double* tab = a.tab + uni(md->tab0);
+    I128 T = i128_zero();
+    if (W.kept) {
+      if constexpr (KIND >= 1)
+        if (!batch_moments<KIND, true>(a, m, nw, epoch, cb[kC2Sc + 3], cb[kC2Sc + 2], lane, Jv)) return false;
+      keep_nunu2<KIND>(cb, Jv, lane, W.kept, rt);
     } else {
-      for (int i = 0; i < gn; ++i, ++row) {
-        double enone = 0.0;
-        row2<KIND>(a.X, a.X, a.plane, mbeam0 + (row - mrow0) * mNE, mNE, a.tab + mtab0, cb, rt + i * kRowC, a.renorm,
-                   lane, T, err, enone, sct);
-      }
+      batch_radii(a, n, md, lane, cb);
+      if constexpr (KIND >= 1)
+        if (!batch_moments<KIND, false>(a, m, nw, epoch, cb[kC2Sc + 3], cb[kC2Sc + 2], lane, Jv)) return false;
     }
+    while (row < mend) {
+      const int gn = (int)min(mend - row, (long long)kGroup);
+      if (!W.kept) {
+        __asm__ volatile("" ::: "memory");   // the previous group's rows have read their blocks
+        if (lane < gn) {
+          const int lr = (int)(row + lane - mrow0);
+          const int s = lr / mNU;
+          const int j = lr - s * mNU;
+          row_setup2<KIND, false>(u_of(j, mNU), a.h, cb, J, 0.0, 0.0, s, s ? -1.0 : 1.0, rt + lane * kRowP);
+        }
+        __asm__ volatile("" ::: "memory");
+      }
+      const long long gb0 = mbeam0 + (row - mrow0) * mNE;
+      if (mNE <= kGroupMaxNE) {
+        group2<KIND, false, kFoldRowsBatch, kRowP>(a.X, a.plane, gb0, mNE, gn, tab, cb, rt, a.renorm, lane, nullptr, T,
+                                                   err, sct);
+      } else {
+        for (int i = 0; i < gn; ++i)
+          row2<KIND>(a.X, a.X, a.plane, gb0 + (long long)i * mNE, mNE, tab, cb, rt + i * kRowP, a.renorm, lane, T, err,
+                     enone, sct);
+      }
+      row += gn;
+    }
+    batch_publish(a, m, nw, epoch, T, lane, sx);
   }
-  if (m >= 0 && tv >= 0) acc_add(acc_slot(a, epoch, m) + tv * kAccLimbs, T);
-  // clear the set the next epoch will collect into
-  if (blockIdx.x == 0) {
-    unsigned long long* z = a.acc + (size_t)((epoch + 1u) % kAccSets) * a.nmodels * 6 * kAccLimbs;
-    for (int i = threadIdx.x; i < a.nmodels * 6 * kAccLimbs; i += blockDim.x)
-      __hip_atomic_store(z + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  return true;
 }
 
-// Four wavefronts per SIMD (128 VGPRs; the row groups' set-up spills about 230 bytes per
+// Four wavefronts per SIMD (128 VGPRs; the row groups' set-up spills about 200 bytes per
 // lane, outside the chunk loop): the rows of a batch are short (50-400 energies), so a wave
 // spends much of its time on row set-up and the first load of each row, which more
-// wavefronts hide.  Measured on the 256-model batch: 4.35 (two wavefronts per SIMD) -> 4.20
-// (four, 512 threads, 224-byte spill) -> 3.52 (three, 256 threads) -> 3.19 ms per step
-// (four, 256 threads, with the wavefront index scalar); with the lane-parallel row groups,
-// the chunks streamed across rows and the table prefetch 2.53 ms (three wavefronts per SIMD
-// then measure 2.65).
+// wavefronts hide.  Measured on the 256-model batch before the chunks were streamed across
+// rows: 4.35 ms per step at two wavefronts per SIMD, 3.52 at three, 3.19 at four; after it
+// 2.65 at three and 2.53 at four.
 template <int BS>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) k_batch2(BatchArgs a) {
   __shared__ double sJw[BS / 64][4][6];
   __shared__ double scb[BS / 64][kC2Size];
-  __shared__ double srt[BS / 64][kGroup * kRowC];   // each wave's row-constant table
+  __shared__ unsigned long long sxw[BS / 64][12];
+  __shared__ double srt[BS / 64][kRowKeep * kRowP];   // each wave's row-constant table
   __shared__ double s_sct[kSinCosTab];   // sin/cos constants of the rotations
+  static_assert(kGroup <= kRowKeep, "one table for kept rows and groups");
   if (launch_aborted(a.sync)) return;
   if (threadIdx.x == 0) sincos_coefs(s_sct);
   __syncthreads();
@@ -1966,28 +2045,58 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
   // and the row base offsets derived from it then live in scalar registers
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   double (*Jv)[6] = sJw[wid];
+  double *cb = scb[wid], *rt = srt[wid];
+  unsigned long long* sx = sxw[wid];
   const long long w = (long long)blockIdx.x * (BS / 64) + wid;
-  const long long r0w = min(max(a.wave_row0[w], 0LL), a.total_rows);
-  const long long r1w = min(max(a.wave_row0[w + 1], r0w), a.total_rows);
-  const long long step0 = *a.step_ctl;
+  BatchWave W;
+  W.r0 = min(max(uni(a.wave_row0[w]), 0LL), a.total_rows);
+  W.r1 = min(max(uni(a.wave_row0[w + 1]), W.r0), a.total_rows);
+  W.m0 = 0;
+  W.kept = 0;
+  if (W.r0 < W.r1) {
+    int lo = 0, hi = a.nmodels - 1;   // the first row's model
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (a.models[mid].row0 <= W.r0) lo = mid; else hi = mid - 1;
+    }
+    W.m0 = uni(lo);
+    const BatchModel* md = a.models + W.m0;
+    if (W.r1 <= uni(md->row0) + 2LL * uni(md->NU) && W.r1 - W.r0 <= kRowKeep) {
+      W.kept = (int)(W.r1 - W.r0);
+      if (lane < W.kept) {
+        const int lr = (int)(W.r0 + lane - md->row0), s = lr / md->NU;
+        rt[lane * kRowP + kRowU] = u_of(lr - s * md->NU, md->NU);
+        rt[lane * kRowP + kRowS] = (double)s;
+        rt[lane * kRowP + kRowA] = s ? -1.0 : 1.0;   // two tracked species: row s is anti iff s = 1
+      }
+    }
+  }
+  const long long step0 = uni(*a.step_ctl);
   const long long nsteps = max(0LL, min(a.nsteps, a.total_steps - step0));
   unsigned epoch = 0;
   int err = 0;
-  bool ok;
-  batch_stage<0>(a, step0, epoch, r0w, r1w, lane, Jv, scb[wid], srt[wid], s_sct, err);
-  ok = grid_barrier(a, epoch++);
+  batch_prep(a, step0, W, lane, cb, rt);
+  bool ok = batch_stage<0>(a, step0, epoch++, W, lane, Jv, cb, rt, sx, s_sct, err);
   for (long long n = step0; ok && n < step0 + nsteps; ++n) {
-    batch_stage<1>(a, n, epoch, r0w, r1w, lane, Jv, scb[wid], srt[wid], s_sct, err);
-    if (!(ok = grid_barrier(a, epoch++))) break;
-    batch_stage<2>(a, n, epoch, r0w, r1w, lane, Jv, scb[wid], srt[wid], s_sct, err);
-    if (!(ok = grid_barrier(a, epoch++))) break;
-    batch_stage<3>(a, n, epoch, r0w, r1w, lane, Jv, scb[wid], srt[wid], s_sct, err);
-    if (!(ok = grid_barrier(a, epoch++))) break;
-    batch_stage<4>(a, n, epoch, r0w, r1w, lane, Jv, scb[wid], srt[wid], s_sct, err);
-    ok = grid_barrier(a, epoch++);
+    ok = batch_stage<1>(a, n, epoch++, W, lane, Jv, cb, rt, sx, s_sct, err) &&
+         batch_stage<2>(a, n, epoch++, W, lane, Jv, cb, rt, sx, s_sct, err) &&
+         batch_stage<3>(a, n, epoch++, W, lane, Jv, cb, rt, sx, s_sct, err) &&
+         batch_stage<4>(a, n, epoch++, W, lane, Jv, cb, rt, sx, s_sct, err);
+    // (a.lockstep is uniform over the grid, ok is not: a wavefront that gave up still meets the
+    // others of its block, which read the abort word at their next wait)
+    if (a.lockstep) {
+      const bool met = batch_meet(a, (unsigned)(n - step0));
+      ok = ok && met;
+      if (__syncthreads_or(!ok)) ok = false;
+    }
+    batch_prep(a, n + 1, W, lane, cb, rt);   // while the models' other wavefronts finish
   }
   if (err) __hip_atomic_fetch_or(a.sync + kSyncStatus, (unsigned)err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (ok && blockIdx.x == 0 && threadIdx.x == 0) *a.step_ctl = step0 + nsteps;
+  // the block that ends last moves the step counter (every block read it at its start); a
+  // block that gave up does not count, and the counter stays
+  if (!__syncthreads_or(!ok) && threadIdx.x == 0 &&
+      __hip_atomic_fetch_add(a.sync + kSyncDone, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1)
+    *a.step_ctl = step0 + nsteps;
 }
 template __global__ void k_batch2<kBlock>(BatchArgs);
 template __global__ void k_batch2<kBlockSmall>(BatchArgs);

@@ -25,15 +25,12 @@ __device__ __forceinline__ Radial radial(double R, int ne_power, double lam0, do
 __device__ __forceinline__ double as_double(unsigned long long u) { return __longlong_as_double((long long)u); }
 __device__ __forceinline__ unsigned long long as_bits(double d) { return (unsigned long long)__double_as_longlong(d); }
 
-// Grid barriers.  Within one launch a beam's state is touched only by the wavefront that
-// owns its row, so the only data that crosses blocks are the block partials, the reduced
-// moments and the barrier words -- and every one of those is written and read with
-// agent-scope atomics, which are coherent at the device level without L2 write-back or
-// invalidation.  Ordering comes from the protocol itself: a block's partial stores
-// complete before its arrival word is stored (the workgroup barrier in between waits for
-// all of the block's outstanding memory operations), and a waiter issues its loads of the
-// published data only after it has read the word that announces them.  So the barrier
-// needs no cache maintenance at all: the state written in the same stage stays in L2.
+// Waits.  Within one launch a beam's state is touched only by the wavefront that owns its
+// row, so the only data that cross blocks are moment sums -- and every one of those is
+// written and read with agent-scope atomics, which are coherent at the device level without
+// L2 write-back or invalidation, in words that carry the epoch they belong to, so a reader
+// knows from the word itself whether it is current.  No cache maintenance is needed: the
+// state written in the same stage stays in L2.
 
 // Checked every 32nd poll (it) of a wait: true if another block has aborted, or if this
 // wait, begun at t0, has passed the launch's time limit (then it sets the abort word and
@@ -60,64 +57,6 @@ __device__ __forceinline__ bool give_up(unsigned* sync, const unsigned* cancel, 
 __device__ __forceinline__ bool launch_aborted(const unsigned* sync) {
   return __syncthreads_or(threadIdx.x == 0 &&
                           __hip_atomic_load(sync + kSyncAbort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u);
-}
-
-// Poll *w (relaxed) until it reaches want; gives up when another block has aborted or the
-// launch's time limit passes (then it sets the abort word and status bit 1).  The abort
-// word and the clock are read only every 32nd poll, so a poll costs one load round trip.
-__device__ __forceinline__ bool poll_until(unsigned* sync, const unsigned* cancel,
-                                           unsigned long long timeout_ticks, unsigned* w, unsigned want) {
-  const unsigned long long t0 = wall_clock64();
-  for (unsigned it = 1;; ++it) {
-    if (__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= want) return true;
-    if ((it & 31u) == 0u && give_up(sync, cancel, t0, timeout_ticks, it)) return false;
-    __builtin_amdgcn_s_sleep(1);
-  }
-}
-// Block 0 of a barrier (all its threads call this): the first wavefront polls every other
-// block's arrival word, all of a lane's words per round so that their loads overlap.
-// Returns false on give-up.
-__device__ __forceinline__ bool wait_arrivals(unsigned* sync, const unsigned* cancel,
-                                              unsigned long long timeout_ticks, unsigned want) {
-  int ok = 1;
-  if (threadIdx.x < 64) {
-    const unsigned long long t0 = wall_clock64();
-    for (unsigned it = 1;; ++it) {
-      unsigned lowest = 0xffffffffu;
-      for (unsigned b = 1 + threadIdx.x; b < gridDim.x; b += 64)
-        lowest = min(lowest, __hip_atomic_load(sync + kSyncArrive + b * kLineWords, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT));
-      if (lowest >= want) break;
-      if ((it & 31u) == 0u && give_up(sync, cancel, t0, timeout_ticks, it)) {
-        ok = 0;
-        break;
-      }
-      __builtin_amdgcn_s_sleep(1);
-    }
-  }
-  return !__syncthreads_or(!ok);
-}
-// A non-zero block arrives (all its threads call this, after their partial stores) and
-// waits for block 0's release flag.  Returns false on give-up.
-__device__ __forceinline__ bool arrive_and_wait(unsigned* sync, const unsigned* cancel,
-                                                unsigned long long timeout_ticks, unsigned want) {
-  __shared__ int s_ok;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __hip_atomic_store(sync + kSyncArrive + blockIdx.x * kLineWords, want, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-    s_ok = poll_until(sync, cancel, timeout_ticks, sync + kSyncFlag + (blockIdx.x % kFlagCopies) * kLineWords,
-                      want) ? 1 : 0;
-  }
-  __syncthreads();
-  return s_ok != 0;
-}
-// Block 0 releases the grid (all its threads call this, after their result stores).
-__device__ __forceinline__ void release_grid(unsigned* sync, unsigned want) {
-  __syncthreads();
-  if (threadIdx.x < kFlagCopies)
-    __hip_atomic_store(sync + kSyncFlag + threadIdx.x * kLineWords, want, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Geometry of one emission bin u at the three stage radii of a step.

@@ -86,3 +86,23 @@ def test_adaptive_block_sizes(nb, oracle, nf, n_u):
     so = o.run_adaptive(1e-7)
     assert (st["accepted"], st["rejected"]) == (so["accepted"], so["rejected"])
     np.testing.assert_array_equal(m.get_state().cpu().numpy(), o.get_state())
+
+
+@pytest.mark.parametrize("bs,blocks,steps", [(256, 0, 4200), (256, 1, 30), (256, 3, 30), (512, 1, 30)])
+def test_batch_models_wait_for_their_own_rows(nb, oracle, bs, blocks, steps):
+    """Batches in one launch: a wavefront per row, past 16384 epochs (the 14-bit tags and counts
+    wrap); wavefronts with more rows than they keep, of several models (blocks meet after
+    every step)."""
+    ds = [workloads.small_params(n_energy=ne, n_u=nu, n_steps=steps, r_start_km=500.0,
+                                 r_end_km=500.0 + 0.01 * steps, lum_erg_s=[le, 1e51, 2e51])
+          for ne, nu, le in ((5, 3, 1e51), (70, 1, 2e51), (3, 40, 1.5e51), (64, 2, 3e51), (9, 11, 1e51))]
+    print(f"batch: {bs} threads, {blocks} blocks, {steps} steps", flush=True)
+    m = nb.Model(ds)
+    m.set_tuning(bs, blocks)
+    m.run()
+    got = m.get_state().cpu().numpy()
+    off = m.offsets()
+    for i, d in enumerate(ds):
+        o = oracle.Model(d)
+        o.run()
+        np.testing.assert_array_equal(got[:, off[i]:off[i + 1]], o.get_state())
