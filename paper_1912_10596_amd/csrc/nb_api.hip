@@ -25,7 +25,7 @@ template <int NF, typename ST, bool TLDS, bool F32, bool EXT, int BS, bool PK>
 __global__ void k_advance(StepArgs a);
 template <int BS>
 __global__ void k_batch2(BatchArgs a);
-template <int BPT>
+template <int BPT, int BS>
 __global__ void k_adjoint2(AdjArgs a);
 template <int NF, bool TLDS, int BS>
 __global__ void k_adaptive(StepArgs a);
@@ -160,7 +160,7 @@ struct nb_model {
   size_t off_models = 0, off_waves = 0, off_counts = 0, off_acc = 0, need = 0;
   size_t off_adj = 0, off_spill = 0, off_jhist = 0, off_dtab = 0, off_aout = 0, off_X2 = 0;
   double* jhist = nullptr;           // set while the adjoint's forward pass records moments
-  int adj_blocks = 0, adj_bpt = 0;
+  int adj_blocks = 0, adj_bpt = 0, adj_bs = kBlock;   // adj_bpt -1: spill mode
   long long* pinned = nullptr;       // [0] status, [1] step, [8..12] adjoint gradients
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
@@ -612,6 +612,15 @@ static int adaptive_block(const nb_model* m, int cus) {
   return block_of_rows(m->rows, cus);
 }
 
+// The reverse kernel at bpt beams per thread (-1: spill mode) and bs threads per block.
+static const void* adjoint_kernel(int bpt, int bs) {
+  if (bs == kBlockSmall) return (const void*)&k_adjoint2<1, kBlockSmall>;
+  return bpt == 1 ? (const void*)&k_adjoint2<1, kBlock>
+       : bpt == 2 ? (const void*)&k_adjoint2<2, kBlock>
+       : bpt == 4 ? (const void*)&k_adjoint2<4, kBlock>
+                  : (const void*)&k_adjoint2<0, kBlock>;
+}
+
 // Packed row tails (k_advance<..., PK = true>): three flavours with FP64 state and
 // arithmetic, the bulb model, 512 threads, one row per wavefront of a launch of nblocks
 // blocks, N_E = 64 m + t with 1 <= t <= 32 and N_E <= 2048.  The kernel ends with a range
@@ -828,31 +837,27 @@ extern "C" int nb_bind(nb_model* m, void* dev_ws, size_t bytes, void* hip_stream
   m->adj_bpt = 0;
   m->adj_blocks = 0;
   if (adjoint_enabled(m)) {
-    // smallest beams-per-thread variant whose resident grid covers every beam; beyond four
-    // beams per resident thread, the spill variant (adjoint registers in the workspace) on
-    // the full resident grid
-    static const int bpts[3] = {1, 2, 4};
-    static const void* fns[3] = {(const void*)&k_adjoint2<1>, (const void*)&k_adjoint2<2>,
-                                 (const void*)&k_adjoint2<4>};
-    for (int i = 0; i < 3 && !m->adj_bpt; ++i) {
+    // up to one wavefront per SIMD: 256-thread blocks, one beam per thread (4096 beams: each
+    // wavefront has a SIMD to itself, where 512-thread blocks put two on one and leave CUs
+    // idle); else the smallest beams-per-thread variant at 512 threads whose resident grid
+    // covers every beam; beyond four beams per resident thread, the spill variant (adjoint
+    // registers in the workspace) on the full resident grid
+    struct Shape { int bpt, bs; };
+    static const Shape shapes[4] = {{1, kBlockSmall}, {1, kBlock}, {2, kBlock}, {4, kBlock}};
+    for (int i = 0; i < 5 && !m->adj_bpt; ++i) {
+      const Shape sh = i < 4 ? shapes[i] : Shape{-1, kBlock};   // -1: spill mode
       int per = 0;
-      NB_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fns[i], kBlock, 0));
-      int blocks = std::min(cus * per, kMaxBlocks);
+      NB_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, adjoint_kernel(sh.bpt, sh.bs), sh.bs, 0));
+      if (i == 4 && per < 1) return fail(NB_EHIP, "adjoint kernel cannot be resident");
+      int blocks = std::min(sh.bs == kBlockSmall ? cus * std::min(per, 1) : cus * per, kAdjMaxBlocks);
       if (m->p.max_blocks > 0) blocks = std::min(blocks, (int)m->p.max_blocks);
-      const long long need_blocks = (m->nb + (long long)bpts[i] * kBlock - 1) / ((long long)bpts[i] * kBlock);
-      if (per >= 1 && need_blocks <= blocks) {
-        m->adj_bpt = bpts[i];
-        m->adj_blocks = (int)std::max<long long>(1, need_blocks);
+      const long long per_block = (long long)std::max(1, sh.bpt) * sh.bs;
+      const long long need_blocks = (m->nb + per_block - 1) / per_block;
+      if (i == 4 || (per >= 1 && need_blocks <= blocks)) {
+        m->adj_bpt = sh.bpt;
+        m->adj_bs = sh.bs;
+        m->adj_blocks = std::max(1, i == 4 ? blocks : (int)need_blocks);
       }
-    }
-    if (!m->adj_bpt) {
-      int per = 0;
-      NB_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, (const void*)&k_adjoint2<0>, kBlock, 0));
-      if (per < 1) return fail(NB_EHIP, "adjoint kernel cannot be resident");
-      int blocks = std::min(cus * per, kMaxBlocks);
-      if (m->p.max_blocks > 0) blocks = std::min(blocks, (int)m->p.max_blocks);
-      m->adj_bpt = -1;   // spill mode
-      m->adj_blocks = std::max(1, blocks);
     }
   }
   m->ws = (char*)dev_ws;
@@ -1775,11 +1780,8 @@ extern "C" int nb_adjoint(nb_model* m, const double* dev_dl_dpee, double* grad_o
   a.timeout_ticks = m->ticks_per_s * 20ull;
   a.cancel = m->cancel_dev;
   void* args[] = {&a};
-  const void* fn = m->adj_bpt == 1 ? (const void*)&k_adjoint2<1>
-                 : m->adj_bpt == 2 ? (const void*)&k_adjoint2<2>
-                 : m->adj_bpt == 4 ? (const void*)&k_adjoint2<4>
-                                   : (const void*)&k_adjoint2<0>;
-  const hipError_t e = hipLaunchKernel(fn, dim3(m->adj_blocks), dim3(kBlock), args, 0, m->stream);
+  const hipError_t e = hipLaunchKernel(adjoint_kernel(m->adj_bpt, m->adj_bs), dim3(m->adj_blocks), dim3(m->adj_bs), args, 0,
+                                      m->stream);
   if (e != hipSuccess) return fail(NB_EHIP, "adjoint launch: %s", hipGetErrorString(e));
   const long long before = m->step;
   int rc = check_status(m);

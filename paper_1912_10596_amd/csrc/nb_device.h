@@ -124,6 +124,25 @@ __device__ __forceinline__ double div_by_sqrt(double a, double g, double h) {
   return div_by_rcp(a, g, rcp_step(g, h + h));
 }
 
+// -------------------------------------------------------------- lanes of a wavefront
+// The value of another lane of the same row of 16 (all lanes active): quad permutations for
+// lanes i ^ 1 and i ^ 2, the mirror of 8 lanes for 7 - i, a rotation by 8.
+template <int CTRL>
+__device__ __forceinline__ unsigned long long dpp_u64(unsigned long long x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)x, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(x >> 32), CTRL, 0xf, 0xf, true);
+  return ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo;
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppRor8 = 0x128;
+// Sum over 8 consecutive lanes, in every one of them.
+__device__ __forceinline__ unsigned long long sum8(unsigned long long x) {
+  x += dpp_u64<kDppXor1>(x);
+  x += dpp_u64<kDppXor2>(x);
+  x += dpp_u64<kDppHalfMirror>(x);
+  return x;
+}
+
+
 // ------------------------------------------------------------- fixed point
 // 128-bit two's complement integer held as two 64-bit halves.
 struct I128 {
@@ -178,18 +197,6 @@ constexpr unsigned long long kFixMagic = 0x4338000000000000ull;
 __device__ __forceinline__ unsigned long long fix_bits(double v, double ws) {
   return (unsigned long long)__double_as_longlong(fma(v, ws, 0x1.8p52));
 }
-// Butterfly sum over the 64 lanes of a wavefront; every lane gets the total.
-__device__ __forceinline__ I128 wave_sum(I128 a) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    I128 o;
-    o.lo = __shfl_xor(a.lo, off, 64);
-    o.hi = __shfl_xor(a.hi, off, 64);
-    a = i128_add(a, o);
-  }
-  return a;
-}
-
 // ------------------------------------------------------------------ complex
 struct cplx {
   double re, im;

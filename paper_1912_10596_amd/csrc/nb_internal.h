@@ -12,7 +12,6 @@ constexpr int kMaxBlocks = 2048;  // upper bound on blocks of one stepping launc
 // block writes or polls sits on a 128-byte line of its own or in one of the reduction
 // regions below.
 constexpr int kLineWords = 32;
-constexpr int kFlagCopies = 8;
 constexpr int kSyncAbort = 1 * kLineWords;   // set when any block gives up waiting
 constexpr int kSyncStatus = 2 * kLineWords;  // bit 0: fixed-point range error, bit 1: barrier timeout,
                                              // bit 2: cancelled by the host, bit 3: renormalisation
@@ -35,13 +34,15 @@ constexpr int kSyncStep = kSyncDone + kLineWords;
 constexpr int kSyncStepPub = kSyncStep + kRedCopies * kLineWords;
 constexpr int kSyncDoneEnd = kSyncStepPub + kRedCopies * kLineWords;
 // The adjoint's sums: tagged 64-bit words (every word carries the barrier epoch it belongs
-// to), kFlagCopies copies of the results (block b reads copy b % kFlagCopies) of kTagLines
-// lines each, then one slot of kTagLines lines of partials per block.
+// to): in two regions (even, odd epochs) the sums of the 8 dies, kTagLines lines each, then
+// one slot of kTagLines lines of partials per block.
 constexpr int kTagLines = 4;
 constexpr int kSyncJTag = kSyncDoneEnd;
-constexpr int kSyncPart = kSyncJTag + kFlagCopies * kTagLines * kLineWords;
+constexpr int kSyncPart = kSyncJTag + 2 * 8 * kTagLines * kLineWords;
 constexpr int kSyncWords = kSyncPart + kMaxBlocks * kTagLines * kLineWords;
 constexpr int kTagWords64 = kTagLines * kLineWords / 2;   // 64-bit words per copy or slot
+constexpr int kAdjDieBlocks = 64;                         // most adjoint blocks of one die
+constexpr int kAdjMaxBlocks = 8 * kAdjDieBlocks;
 
 constexpr int kVacRows3 = 7;    // 3f table rows before the weights: 6 vacuum entries and e_k
 constexpr int kBlock = 512;       // threads per block: the most a stepping launch uses (8 waves),

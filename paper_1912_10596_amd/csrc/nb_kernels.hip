@@ -63,21 +63,6 @@ __device__ __forceinline__ unsigned long long chunk_field(const I128& x, int k) 
   const unsigned long long hi = (x.lo >> 47) | ((unsigned long long)x.hi << 17);
   return (k ? hi + (1ull << 46) : x.lo) & kMask47;
 }
-// Sum over 8 consecutive lanes (all active), in every one of them: lane i ^ 1, i ^ 2, 7 - i.
-template <int CTRL>
-__device__ __forceinline__ unsigned long long dpp_u64(unsigned long long x) {
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)x, CTRL, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(x >> 32), CTRL, 0xf, 0xf, true);
-  return ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo;
-}
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppRor8 = 0x128;
-__device__ __forceinline__ unsigned long long sum8(unsigned long long x) {
-  x += dpp_u64<kDppXor1>(x);
-  x += dpp_u64<kDppXor2>(x);
-  x += dpp_u64<kDppHalfMirror>(x);
-  return x;
-}
-
 template <int NC>
 __device__ __forceinline__ int fold_comp(int lane);     // lane layout of the moment totals, below
 template <int NC>

@@ -74,6 +74,20 @@ __device__ __forceinline__ RowGeo row_geo(double u, double h, const Radial& g0, 
   r.hc1 = h / r.c1;
   return r;
 }
+// The same values from the in-range forms: 0 < 1 - u q2 <= 1, at least 1 / (2 N_u).
+__device__ __forceinline__ void row_cos(double u, double h, double q2, double& c, double& hc) {
+  double half;
+  c = sqrt_in_range(1.0 - u * q2, half);
+  hc = div_by_sqrt(h, c, half);
+}
+__device__ __forceinline__ RowGeo row_geo_in_range(double u, double h, const Radial& g0, const Radial& gm,
+                                                   const Radial& g1) {
+  RowGeo r;
+  row_cos(u, h, g0.q2, r.c0, r.hc0);
+  row_cos(u, h, gm.q2, r.cm, r.hcm);
+  row_cos(u, h, g1.q2, r.c1, r.hc1);
+  return r;
+}
 __device__ __forceinline__ double u_of(int j, int NU) { return ((double)j + 0.5) / (double)NU; }
 // The neutrino-neutrino term mu (J0 - c J1) of a row: the same for every energy bin.
 template <int NC>

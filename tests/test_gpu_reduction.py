@@ -106,3 +106,24 @@ def test_batch_models_wait_for_their_own_rows(nb, oracle, bs, blocks, steps):
         o = oracle.Model(d)
         o.run()
         np.testing.assert_array_equal(got[:, off[i]:off[i + 1]], o.get_state())
+
+
+@pytest.mark.parametrize("n_energy,n_u", [(8, 16), (8, 17), (64, 16), (64, 17), (64, 18), (128, 256), (129, 256),
+                                          (512, 257), (1024, 257)])
+def test_adjoint_grid_sizes(nb, oracle, n_energy, n_u):
+    """The adjoint's sums at one block, at most eight, more than eight and many blocks, and at the
+    beam counts where the block size and the beams per thread change; parameters and
+    tolerance of the adjoint's own oracle test."""
+    import torch
+    d = workloads.small_params(n_flavor=2, n_energy=n_energy, n_u=n_u, n_steps=5, r_start_km=60.0,
+                               r_end_km=61.5, n0_cm3=1e31, lum_erg_s=[3e50, 2e50, 1e50], theta=[0.5, 0.0, 0.0])
+    print(f"adjoint: {2 * n_energy * n_u} beams", flush=True)
+    o = oracle.Model(d)
+    c = np.random.default_rng(5).uniform(-1.0, 1.0, o.nb) / o.nb
+    _, go, sbo = o.adjoint(3, c, want_state_bar=True)
+    m = nb.Model(d, adjoint_ckpt=3)
+    g, sb = m.adjoint(torch.as_tensor(c, device="cuda"), want_state_bar=True)
+    np.testing.assert_allclose(g, go, rtol=1e-9, atol=0)
+    np.testing.assert_allclose(sb.cpu().numpy(), sbo, rtol=1e-9, atol=1e-9 * np.abs(sbo).max())
+    m.reset()
+    np.testing.assert_array_equal(m.adjoint(torch.as_tensor(c, device="cuda")), g)
