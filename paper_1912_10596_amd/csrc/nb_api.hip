@@ -29,17 +29,19 @@ template <int BPT, int BS>
 __global__ void k_adjoint2(AdjArgs a);
 template <int NF, bool TLDS, int BS>
 __global__ void k_adaptive(StepArgs a);
-__global__ void k_zero_sync(unsigned int* sync, int keep_status, const unsigned* cancel, int words);
-__global__ void k_zero_u64(unsigned long long* p, long long n);
+__global__ void k_zero_sync(unsigned int* sync, int keep_status, const unsigned* cancel, int words,
+                            unsigned long long* acc, long long nacc);
 __global__ void k_set_step(long long* step_ctl, long long step);
 __global__ void k_status_out(const unsigned int* sync, const long long* step_ctl, long long* host);
 __global__ void k_set_target(long long* step_ctl, long long k, long long total);
 template <typename ST>
-__global__ void k_init(ST* X, long long nb, long long plane, int nsc, long long per_species, int nfl);
+__global__ void k_init(ST* X, long long nb, long long plane, int nsc, long long per_species, int nfl,
+                       long long* step_ctl);
 template <typename ST>
 __global__ void k_read_pee(const ST* X, long long nb, long long plane, int nsc, double* out);
 template <typename ST>
-__global__ void k_state_xfer(ST* X, long long nb, long long plane, int nsc, double* buf, int dir);
+__global__ void k_state_xfer(ST* X, long long nb, long long plane, int nsc, double* buf, int dir, long long* step_ctl,
+                             long long step);
 }  // namespace nb
 
 using namespace nb;
@@ -161,7 +163,8 @@ struct nb_model {
   size_t off_adj = 0, off_spill = 0, off_jhist = 0, off_dtab = 0, off_aout = 0, off_X2 = 0;
   double* jhist = nullptr;           // set while the adjoint's forward pass records moments
   int adj_blocks = 0, adj_bpt = 0, adj_bs = kBlock;   // adj_bpt -1: spill mode
-  long long* pinned = nullptr;       // [0] status, [1] step, [8..12] adjoint gradients
+  long long* pinned = nullptr;       // [0] status (-1: not reported), [1] step, [8..12] adjoint gradients
+  bool sync_dirty = false;           // the reduction words need a clear before a stepping launch
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
   long long graph_steps = 0;
@@ -687,18 +690,21 @@ static int set_device_step(nb_model* m, long long step) {
   return NB_OK;
 }
 
-// Clear the first `words` barrier words (the part the next launch uses), optionally keeping
-// the status word (a kernel: capturable).
+// Clear the first `words` barrier words (the part the next launch uses) and a batch's
+// accumulators, optionally keeping the status word (a kernel: capturable).
 static int clear_sync(nb_model* m, int keep, const unsigned* cancel, int words) {
   unsigned int* sync = sync_words(m);
-  void* zargs[] = {&sync, &keep, &cancel, &words};
-  NB_HIP(hipLaunchKernel((const void*)&k_zero_sync, dim3((unsigned)((words + 1023) / 1024)), dim3(256), zargs, 0,
-                         m->stream));
+  unsigned long long* acc = acc_words(m);
+  long long nacc = m->batch ? (long long)kAccPerModel * m->nmodels : 0;
+  void* zargs[] = {&sync, &keep, &cancel, &words, &acc, &nacc};
+  const long long n = std::max<long long>(words, nacc);
+  NB_HIP(hipLaunchKernel((const void*)&k_zero_sync, dim3((unsigned)std::min<long long>((n + 1023) / 1024, 256)), dim3(256),
+                         zargs, 0, m->stream));
   return NB_OK;
 }
 static int zero_sync(nb_model* m, int keep, int words) { return clear_sync(m, keep, m->cancel_dev, words); }
 // Words the fixed-step launches of a model use.
-static int step_sync_words(const nb_model* m) { return m->batch ? kSyncDoneEnd : kSyncRedEnd; }
+static int step_sync_words(const nb_model* m) { return m->batch ? kSyncStepEnd : kSyncRedEnd; }
 
 extern "C" int nb_reset(nb_model* m) {
   if (!m) return fail(NB_EINVAL, "model is NULL");
@@ -711,11 +717,10 @@ extern "C" int nb_reset(nb_model* m) {
   const Sub& s0 = m->subs[0];
   long long per_species = m->batch ? m->nb : s0.NE * s0.NU * s0.NP;
   int nfl = m->batch ? 1 : s0.NS / 2;
-  void* args[] = {&X, &nb_, &plane, &nsc, &per_species, &nfl};
+  long long* ctl = (long long*)(m->ws + m->off_ctl);
+  void* args[] = {&X, &nb_, &plane, &nsc, &per_species, &nfl, &ctl};
   int rc = launch_1d(state_fp32(m) ? (const void*)&k_init<float> : (const void*)&k_init<double>,
                      m->nb, args, m->stream);
-  if (rc) return rc;
-  rc = set_device_step(m, 0);
   if (rc) return rc;
   m->step = 0;
   return NB_OK;
@@ -905,26 +910,39 @@ extern "C" int nb_bind(nb_model* m, void* dev_ws, size_t bytes, void* hip_stream
   }
   const int rc = clear_sync(m, 0, nullptr, kSyncWords);
   if (rc) return rc;
+  m->sync_dirty = false;
   NB_HIP(hipStreamSynchronize(m->stream));
   return nb_reset(m);
 }
 
-// Read and clear the kernels' status word and read back the device step counter (only
-// outside graph capture).
-static int check_status(nb_model* m) {
+// Before launches whose status check_status reads: no report yet.
+static void expect_report(nb_model* m) { __atomic_store_n(&m->pinned[0], -1ll, __ATOMIC_SEQ_CST); }
+
+// Wait for the stream, read and clear the kernels' status word and read back the device step
+// counter (only outside graph capture).  reports: the last launch reports both itself when
+// it ends well; otherwise (and if it did not) a kernel copies them.
+static int check_status(nb_model* m, bool reports) {
   if (capturing(m->stream)) return NB_OK;
   unsigned int* sync = sync_words(m);
-  const long long* ctl = (const long long*)(m->ws + m->off_ctl);
-  long long* host = m->pinned;
-  void* sargs[] = {&sync, &ctl, &host};
-  NB_HIP(hipLaunchKernel((const void*)&k_status_out, dim3(1), dim3(1), sargs, 0, m->stream));
-  NB_HIP(hipStreamSynchronize(m->stream));
+  if (reports) NB_HIP(hipStreamSynchronize(m->stream));
+  if (!reports || __atomic_load_n(&m->pinned[0], __ATOMIC_SEQ_CST) < 0) {
+    const long long* ctl = (const long long*)(m->ws + m->off_ctl);
+    long long* host = m->pinned;
+    void* sargs[] = {&sync, &ctl, &host};
+    NB_HIP(hipLaunchKernel((const void*)&k_status_out, dim3(1), dim3(1), sargs, 0, m->stream));
+    NB_HIP(hipStreamSynchronize(m->stream));
+    if (reports && m->pinned[0] == 0) {   // a launch that ended early always leaves a status bit
+      m->sync_dirty = true;
+      return fail(NB_EHIP, "stepping launch did not end");
+    }
+  }
   const unsigned st = (unsigned)(m->pinned[0] & 0xffffffffll);
   m->step = m->pinned[1];
   if (st) {
     const int rc = clear_sync(m, 0, nullptr, kSyncWords);
     if (rc) return rc;
     NB_HIP(hipStreamSynchronize(m->stream));
+    if (!m->sync_static) m->sync_dirty = false;
     if (st & 4u) return fail(NB_ETIMEOUT, "cancelled by the host (nb_cancel)");
     if (st & 2u) return fail(NB_ETIMEOUT, "grid barrier time limit exceeded");
     if (st & 8u)
@@ -948,17 +966,21 @@ static long long launch_chunk(const nb_model* m) {
 // cost 15-18 us more per call, and processes that had made cooperative launches crashed in
 // the runtime's exit handler under rocprofv3 (ordinary launches exit cleanly).
 //
-// Enqueue one stepping launch of k steps (from the device step counter) on the stream.
-static int enqueue_advance(nb_model* m, long long k) {
+// Enqueue one stepping launch of k steps (from the device step counter) on the stream.  A
+// single model's launch that ends well clears the reduction words after itself, so only
+// batches, launches after an adaptive run and captured launches (whose predecessors'
+// status the library may not have seen) have a clear before them.  report: the launch
+// writes its status to the pinned words.
+static int enqueue_advance(nb_model* m, long long k, bool report) {
   unsigned int* sync = sync_words(m);
-  int rc0 = zero_sync(m, 1, step_sync_words(m));
-  if (rc0) return rc0;
+  if (m->batch || (m->sync_dirty && !m->sync_static) || capturing(m->stream)) {
+    const int rc = zero_sync(m, 1, step_sync_words(m));
+    if (rc) return rc;
+    if (!m->sync_static && !capturing(m->stream)) m->sync_dirty = false;
+  }
   const unsigned long long timeout = m->ticks_per_s * 20ull;
   if (m->batch) {
     unsigned long long* acc = acc_words(m);
-    long long nacc = (long long)kAccPerModel * m->nmodels;
-    void* zz[] = {&acc, &nacc};
-    NB_HIP(hipLaunchKernel((const void*)&k_zero_u64, dim3(64), dim3(256), zz, 0, m->stream));
     BatchArgs a{};
     a.X = (double*)(m->ws + m->off_X);
     a.plane = m->plane;
@@ -985,6 +1007,7 @@ static int enqueue_advance(nb_model* m, long long k) {
     // nearly empty device (256 models of 64M beams: 2.53 ms per step against 2.35 with the
     // blocks meeting after every step).  Small batches gain by not meeting (16 models of
     // 20-50 x 5-50 bins: 24.9 us per step against 58 with a grid barrier per stage).
+    a.host = report ? m->pinned : nullptr;
     a.lockstep = m->rows > (long long)kBatchKeep * m->nblocks * (m->bs / 64) ? 1 : 0;
     void* args[] = {&a};
     const hipError_t e =
@@ -1025,7 +1048,10 @@ static int enqueue_advance(nb_model* m, long long k) {
     if (e != hipSuccess) return fail(NB_EHIP, "stepping launch: %s", hipGetErrorString(e));
     return NB_OK;
   };
-  if (!advance_kernel_f32(m, m->bs)) return launch(advance_kernel(m, m->bs), advance_dyn_lds(m));
+  if (!advance_kernel_f32(m, m->bs)) {
+    a.host = report ? m->pinned : nullptr;
+    return launch(advance_kernel(m, m->bs), advance_dyn_lds(m));
+  }
   // Mixed precision: FP64-arithmetic steps before fp32_from, FP32-arithmetic steps after,
   // as two windowed launches sharing one target of k steps from the device counter.
   {
@@ -1039,8 +1065,7 @@ static int enqueue_advance(nb_model* m, long long k) {
   a.win_hi = s.fp32_from;
   int rc = launch(advance_kernel(m, m->bs), advance_dyn_lds(m));
   if (rc) return rc;
-  rc = zero_sync(m, 1, kSyncRedEnd);
-  if (rc) return rc;
+  a.host = report ? m->pinned : nullptr;   // the second launch's status covers both
   a.win_lo = s.fp32_from;
   a.win_hi = m->p.n_steps;
   return launch(advance_kernel_f32(m, m->bs), f32_dyn_lds(m));
@@ -1050,12 +1075,14 @@ static int advance(nb_model* m, long long n) {
   const long long chunk = launch_chunk(m);
   while (n > 0) {
     const long long k = std::min(n, chunk);
-    int rc = enqueue_advance(m, k);
+    const bool cap = capturing(m->stream);
+    if (!cap) expect_report(m);
+    int rc = enqueue_advance(m, k, !cap);
     if (rc) return rc;
     n -= k;
-    if (capturing(m->stream)) continue;
+    if (cap) continue;
     const long long before = m->step;
-    rc = check_status(m);
+    rc = check_status(m, true);
     if (rc) return rc;
     if (m->step != before + k) return fail(NB_EHIP, "device step counter out of step");
   }
@@ -1156,6 +1183,7 @@ extern "C" int nb_run_adaptive(nb_model* m, double tol, double h_max_km, int64_t
   NB_HIP(hipMemcpyAsync(ctl, init, sizeof(init), hipMemcpyHostToDevice, m->stream));
   int rc = zero_sync(m, 1, kSyncErrEnd);
   if (rc) return rc;
+  m->sync_dirty = true;   // the adaptive kernel leaves its sums
   StepArgs a{};
   a.X = m->ws + m->off_X;
   a.X2 = m->ws + m->off_X2;
@@ -1196,7 +1224,7 @@ extern "C" int nb_run_adaptive(nb_model* m, double tol, double h_max_km, int64_t
   if (e != hipSuccess) return fail(NB_EHIP, "adaptive launch: %s", hipGetErrorString(e));
   long long out[8];
   NB_HIP(hipMemcpyAsync(out, ctl, sizeof(out), hipMemcpyDeviceToHost, m->stream));
-  rc = check_status(m);
+  rc = check_status(m, false);
   if (rc) return rc;
   if (stats) {
     stats->accepted = out[kCtlAcc];
@@ -1222,7 +1250,7 @@ extern "C" int nb_graph_capture(nb_model* m, int64_t n_steps) {
   if (!m->stream) return fail(NB_EINVAL, "graph capture needs a non-default stream");
   drop_graph(m);
   NB_HIP(hipStreamBeginCapture(m->stream, hipStreamCaptureModeThreadLocal));
-  int rc = enqueue_advance(m, n_steps);
+  int rc = enqueue_advance(m, n_steps, true);
   hipGraph_t g = nullptr;
   hipError_t e = hipStreamEndCapture(m->stream, &g);
   if (rc) {
@@ -1257,8 +1285,9 @@ extern "C" int nb_graph_launch(nb_model* m) {
   if (m->graph_blocks > cap)
     return fail(NB_EINVAL, "captured grid of %d blocks of %d threads exceeds the resident capacity %d",
                 m->graph_blocks, m->graph_bs, cap);
+  expect_report(m);
   NB_HIP(hipGraphLaunch(m->graph_exec, m->stream));
-  return check_status(m);
+  return check_status(m, true);
 }
 
 extern "C" int nb_cancel(nb_model* m, int32_t on) {
@@ -1649,11 +1678,12 @@ extern "C" int nb_read_pee(const nb_model* m, double* dev_out) {
   return NB_OK;
 }
 
-static int xfer(nb_model* m, double* buf, int dir) {
+static int xfer(nb_model* m, double* buf, int dir, long long step = 0) {
   void* X = m->ws + m->off_X;
   long long nb_ = m->nb, plane = m->plane;
   int nsc = m->nsc;
-  void* args[] = {&X, &nb_, &plane, &nsc, &buf, &dir};
+  long long* ctl = (long long*)(m->ws + m->off_ctl);
+  void* args[] = {&X, &nb_, &plane, &nsc, &buf, &dir, &ctl, &step};
   return launch_1d(state_fp32(m) ? (const void*)&k_state_xfer<float> : (const void*)&k_state_xfer<double>,
                    m->nb, args, m->stream);
 }
@@ -1702,9 +1732,8 @@ extern "C" int nb_set_state(nb_model* m, const double* src, int64_t step, int on
   if (!m->ws) return fail(NB_EUNBOUND, "no workspace bound");
   if (step < 0 || step > m->p.n_steps) return fail(NB_EINVAL, "step out of range");
   if (capturing(m->stream)) return fail(NB_EINVAL, "state exchange cannot be captured");
-  int rc = on_device ? xfer(m, const_cast<double*>(src), 1) : host_xfer(m, const_cast<double*>(src), 1);
-  if (rc) return rc;
-  rc = set_device_step(m, step);
+  int rc = on_device ? xfer(m, const_cast<double*>(src), 1, step) : host_xfer(m, const_cast<double*>(src), 1);
+  if (!rc && !on_device) rc = set_device_step(m, step);
   if (rc) return rc;
   NB_HIP(hipStreamSynchronize(m->stream));
   m->step = step;
@@ -1784,7 +1813,7 @@ extern "C" int nb_adjoint(nb_model* m, const double* dev_dl_dpee, double* grad_o
                                       m->stream);
   if (e != hipSuccess) return fail(NB_EHIP, "adjoint launch: %s", hipGetErrorString(e));
   const long long before = m->step;
-  int rc = check_status(m);
+  int rc = check_status(m, false);
   if (rc) return rc;
   if (m->step != before) return fail(NB_EHIP, "device step counter moved during the reverse pass");
   double* host = (double*)(m->pinned + 8);

@@ -21,23 +21,23 @@ constexpr int kSyncStatus = 2 * kLineWords;  // bit 0: fixed-point range error, 
 // Block b adds to copy b % kRedCopies (consecutive blocks go to the 8 dies in turn, so a
 // copy is added to from one die); a copy's words start on a line of their own.
 constexpr int kRedCopies = 8, kRedStride = 64;
+constexpr int kSyncDone = 3 * kLineWords;     // blocks that have ended the launch
 constexpr int kSyncRed = 4 * kLineWords;
 constexpr int kSyncPub = kSyncRed + 2 * kRedCopies * kRedStride;
 constexpr int kSyncRedEnd = kSyncPub + 2 * 2 * kRedCopies * kRedStride;
 // Adaptive runs: one tagged 64-bit error word per block, in two regions (even, odd epochs).
 constexpr int kSyncErr = kSyncRedEnd;
 constexpr int kSyncErrEnd = kSyncErr + 2 * 2 * kMaxBlocks;
-// Batches: the count of blocks that have ended their steps, and the blocks' arrivals at the
-// end of a step, one line per copy, then the copies' published steps.
-constexpr int kSyncDone = kSyncErrEnd;
-constexpr int kSyncStep = kSyncDone + kLineWords;
+// Batches: the blocks' arrivals at the end of a step, one line per copy, then the copies'
+// published steps.
+constexpr int kSyncStep = kSyncErrEnd;
 constexpr int kSyncStepPub = kSyncStep + kRedCopies * kLineWords;
-constexpr int kSyncDoneEnd = kSyncStepPub + kRedCopies * kLineWords;
+constexpr int kSyncStepEnd = kSyncStepPub + kRedCopies * kLineWords;
 // The adjoint's sums: tagged 64-bit words (every word carries the barrier epoch it belongs
 // to): in two regions (even, odd epochs) the sums of the 8 dies, kTagLines lines each, then
 // one slot of kTagLines lines of partials per block.
 constexpr int kTagLines = 4;
-constexpr int kSyncJTag = kSyncDoneEnd;
+constexpr int kSyncJTag = kSyncStepEnd;
 constexpr int kSyncPart = kSyncJTag + 2 * 8 * kTagLines * kLineWords;
 constexpr int kSyncWords = kSyncPart + kMaxBlocks * kTagLines * kLineWords;
 constexpr int kTagWords64 = kTagLines * kLineWords / 2;   // 64-bit words per copy or slot
@@ -70,6 +70,8 @@ struct StepArgs {
   double v0[6];            // 3f: the vacuum Hamiltonian times E (entries of bin k = e_k v0)
   unsigned long long timeout_ticks;
   const unsigned* cancel;  // the model's cancel word (fine-grained host memory), or nullptr
+  long long* host;         // pinned host words [status, step] a launch that ends well writes, or
+                           // nullptr
   double* Jhist;           // nullptr, or [step][4][2*NC]: every stage's moments (adjoint tape)
   int use_window;          // 0: advance min(nsteps, total - step) steps; 1: the window below
   long long win_lo, win_hi;// windowed launch: only steps in [win_lo, win_hi), up to step_ctl[1]
@@ -125,6 +127,7 @@ struct BatchArgs {
   unsigned long long timeout_ticks;
   const unsigned* cancel;
   int lockstep;                 // 1: the blocks meet after every step
+  long long* host;              // as StepArgs
 };
 
 // Arguments of the two-flavour reverse (adjoint) kernel.  Beam b belongs to thread

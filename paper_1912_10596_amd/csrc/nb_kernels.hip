@@ -1499,7 +1499,7 @@ k_advance(StepArgs a) {
   const long long nw = (long long)gridDim.x * WPB;
   const double* tab = a.tab;
   const float* ftab = nullptr;
-  if (launch_aborted(a.sync)) return;
+  if (launch_aborted(a.sync, a.cancel)) return;
   red_init(R);
   if (NF == 2 && threadIdx.x == 0) sincos_coefs(s_sct);
   __syncthreads();
@@ -1529,7 +1529,10 @@ k_advance(StepArgs a) {
   } else {
     nsteps = max(0LL, min(a.nsteps, a.total_steps - step0));
   }
-  if (a.use_window && nsteps == 0) return;   // uniform over the grid: nothing to do
+  if (a.use_window && nsteps == 0) {   // uniform over the grid: nothing to do
+    if (a.host && blockIdx.x == 0 && threadIdx.x == 0) put_host(a.host, a.sync, step0);
+    return;
+  }
   unsigned epoch = 0;
   int err = 0;
   bool ok = true;
@@ -1614,15 +1617,19 @@ k_advance(StepArgs a) {
     });
     record(n + 1, 0);
   }
-  if (err) __hip_atomic_fetch_or(a.sync + kSyncStatus, (unsigned)err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  // every block read the start step before the first barrier; block 0 passes the last, and
-  // leaves the moments of the new state for the next launch
-  if (ok && blockIdx.x == 0) {
+  // the block that ends last (all have passed the last barrier and read its sums, and read
+  // the start step before the first) moves the step counter, leaves the moments of the new
+  // state for the next launch, clears the reduction words for it (so that no clear need
+  // precede it) and reports to the host
+  if (launch_ends(a.sync, err, ok)) {
     if (threadIdx.x < NV) a.step_ctl[kCtlMom + threadIdx.x] = (long long)as_bits(sJ[0][threadIdx.x]);
+    for (int i = threadIdx.x; i < kSyncRedEnd - kSyncRed; i += BS) a.sync[kSyncRed + i] = 0u;
     if (threadIdx.x == 0) {
+      a.sync[kSyncDone] = 0u;
       a.step_ctl[0] = step0 + nsteps;
       a.step_ctl[kCtlMTag] = step0 + nsteps;
       a.step_ctl[kCtlMKind] = kind;
+      if (a.host) put_host(a.host, a.sync, step0 + nsteps);
     }
   }
 }
@@ -2076,21 +2083,16 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
     }
     batch_prep(a, n + 1, W, lane, cb, rt);   // while the models' other wavefronts finish
   }
-  if (err) __hip_atomic_fetch_or(a.sync + kSyncStatus, (unsigned)err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  // the block that ends last moves the step counter (every block read it at its start); a
-  // block that gave up does not count, and the counter stays
-  if (!__syncthreads_or(!ok) && threadIdx.x == 0 &&
-      __hip_atomic_fetch_add(a.sync + kSyncDone, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1)
+  // the block that ends last moves the step counter (every block read it at its start)
+  if (launch_ends(a.sync, err, ok) && threadIdx.x == 0) {
     *a.step_ctl = step0 + nsteps;
+    if (a.host) put_host(a.host, a.sync, step0 + nsteps);
+  }
 }
 template __global__ void k_batch2<kBlock>(BatchArgs);
 template __global__ void k_batch2<kBlockSmall>(BatchArgs);
 
 // ----------------------------------------------------------------- small kernels
-__global__ void k_zero_u64(unsigned long long* p, long long n) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
-    p[i] = 0ull;
-}
 // The state was set or reset: the step, and no moments left for the next launch.
 __global__ void k_set_step(long long* step_ctl, long long step) {
   step_ctl[0] = step;
@@ -2107,11 +2109,14 @@ __global__ void k_set_target(long long* step_ctl, long long k, long long total) 
   step_ctl[1] = min(step_ctl[0] + k, total);
 }
 
-// Clear the first `words` barrier and reduction words (those the launch uses) before a
-// persistent launch (keep_status: keep the status bits of earlier launches of the same call).  If the host has set the model's
+// Clear the first `words` barrier and reduction words (those the launch uses), and nacc
+// accumulators at acc (batches), before a persistent launch (keep_status: keep the status bits of earlier launches of the same call).  If the host has set the model's
 // cancel word (fine-grained host memory; nullptr: none), the abort word is set instead of
 // cleared, with status bit 2, so that the next persistent launch returns at once.
-__global__ void k_zero_sync(unsigned int* sync, int keep_status, const unsigned* cancel, int words) {
+__global__ void k_zero_sync(unsigned int* sync, int keep_status, const unsigned* cancel, int words,
+                            unsigned long long* acc, long long nacc) {
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < nacc; i += (long long)gridDim.x * blockDim.x)
+    acc[i] = 0ull;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < words; i += gridDim.x * blockDim.x) {
     if (i == kSyncStatus) continue;   // written with the abort word
     if (i == kSyncAbort) {
@@ -2130,8 +2135,13 @@ __global__ void k_zero_sync(unsigned int* sync, int keep_status, const unsigned*
 // flavour s % nfl (nfl = 1 when only electron-born beams are tracked); 2f: P = (0, 0, +-1),
 // 3f: psi = the unit vector of that flavour.
 template <typename ST>
-__global__ void k_init(ST* X, long long nb, long long plane, int nsc, long long per_species, int nfl) {
+__global__ void k_init(ST* X, long long nb, long long plane, int nsc, long long per_species, int nfl,
+                       long long* step_ctl) {
   const long long b = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (b == 0) {   // step 0, no moments left for the next launch
+    step_ctl[0] = 0;
+    step_ctl[kCtlMTag] = -1;
+  }
   if (b >= nb) return;
   const int fl = (int)((b / per_species) % nfl);
   for (int c = 0; c < nsc; ++c) {
@@ -2141,8 +2151,8 @@ __global__ void k_init(ST* X, long long nb, long long plane, int nsc, long long 
     X[b + c * plane] = v;
   }
 }
-template __global__ void k_init<double>(double*, long long, long long, int, long long, int);
-template __global__ void k_init<float>(float*, long long, long long, int, long long, int);
+template __global__ void k_init<double>(double*, long long, long long, int, long long, int, long long*);
+template __global__ void k_init<float>(float*, long long, long long, int, long long, int, long long*);
 
 template <typename ST>
 __global__ void k_read_pee(const ST* X, long long nb, long long plane, int nsc, double* out) {
@@ -2158,17 +2168,23 @@ __global__ void k_read_pee(const ST* X, long long nb, long long plane, int nsc, 
 template __global__ void k_read_pee<double>(const double*, long long, long long, int, double*);
 template __global__ void k_read_pee<float>(const float*, long long, long long, int, double*);
 
-// State exchange with FP64 [comp][beam] planes (dir 0: state -> out, 1: in -> state).
+// State exchange with FP64 [comp][beam] planes (dir 0: state -> out, 1: in -> state, and the
+// step counter, as k_set_step).
 template <typename ST>
-__global__ void k_state_xfer(ST* X, long long nb, long long plane, int nsc, double* buf, int dir) {
+__global__ void k_state_xfer(ST* X, long long nb, long long plane, int nsc, double* buf, int dir, long long* step_ctl,
+                             long long step) {
   const long long b = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (dir == 1 && b == 0) {
+    step_ctl[0] = step;
+    step_ctl[kCtlMTag] = -1;
+  }
   if (b >= nb) return;
   for (int c = 0; c < nsc; ++c) {
     if (dir == 0) buf[c * nb + b] = (double)X[b + c * plane];
     else X[b + c * plane] = (ST)buf[c * nb + b];
   }
 }
-template __global__ void k_state_xfer<double>(double*, long long, long long, int, double*, int);
-template __global__ void k_state_xfer<float>(float*, long long, long long, int, double*, int);
+template __global__ void k_state_xfer<double>(double*, long long, long long, int, double*, int, long long*, long long);
+template __global__ void k_state_xfer<float>(float*, long long, long long, int, double*, int, long long*, long long);
 
 }  // namespace nb

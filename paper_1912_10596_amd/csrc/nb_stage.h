@@ -53,10 +53,42 @@ __device__ __forceinline__ bool give_up(unsigned* sync, const unsigned* cancel, 
 // Read at the start of a persistent launch (all threads of the block call this; thread 0
 // reads, the block shares its answer): the abort word, set before the launch by the
 // sync-word clear when the host had cancelled the model (every block then returns at once,
-// leaving the state as it was), or during it by a block that gave up.
-__device__ __forceinline__ bool launch_aborted(const unsigned* sync) {
+// leaving the state as it was), or during it by a block that gave up.  cancel (launches that
+// no clear precedes): block 0 also reads the host's cancel word; if it is set, that block
+// sets the abort word and status bit 2 and returns, and the others find the abort word at
+// their first wait, before any state is stored.
+__device__ __forceinline__ bool launch_aborted(unsigned* sync, const unsigned* cancel = nullptr) {
+  int ab = 0;
+  if (threadIdx.x == 0) {
+    const unsigned c = (cancel && blockIdx.x == 0)
+                           ? __hip_atomic_load(cancel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) : 0u;
+    ab = __hip_atomic_load(sync + kSyncAbort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
+    if (c && !ab) {
+      __hip_atomic_store(sync + kSyncAbort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_fetch_or(sync + kSyncStatus, 4u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      ab = 1;
+    }
+  }
+  return __syncthreads_or(ab);
+}
+// The status word and the step counter into pinned host memory.
+__device__ __forceinline__ void put_host(long long* host, const unsigned* sync, long long step) {
+  const unsigned st = __hip_atomic_load(sync + kSyncStatus, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(host + 1, step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(host, (long long)st, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+// End of a launch (all threads of the block call this): the block's status bits err are added
+// to the status word; true in the block that ends last, if no block gave up (one that did
+// does not count).  Every other block has then read and written all it shares.
+__device__ __forceinline__ bool launch_ends(unsigned* sync, int err, bool ok) {
+  if (err) {
+    __hip_atomic_fetch_or(sync + kSyncStatus, (unsigned)err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");   // before the block counts itself
+  }
+  if (__syncthreads_or(!ok)) return false;
   return __syncthreads_or(threadIdx.x == 0 &&
-                          __hip_atomic_load(sync + kSyncAbort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u);
+                          __hip_atomic_fetch_add(sync + kSyncDone, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                              gridDim.x - 1u);
 }
 
 // Geometry of one emission bin u at the three stage radii of a step.
