@@ -36,6 +36,8 @@ struct Rot {
   double v0, v1, v2, c;  // sin(t/2) x/t, cos(t/2)
   double ja, jb;
 };
+// SK: as sincos_nb.
+template <bool SK>
 __device__ __forceinline__ Rot make_rot(double x0, double x1, double x2) {
   Rot r;
   r.x0 = x0;
@@ -48,7 +50,7 @@ __device__ __forceinline__ Rot make_rot(double x0, double x1, double x2) {
     t = sqrt(t2);
     ih = (t > 0.0) ? 0.5 / t : 0.0;
   }
-  sincos_nb(0.5 * t, s, c);
+  sincos_nb<SK>(0.5 * t, s, c);
   const double k = div_by_sqrt(s, t, ih);   // 0 for t = 0
   r.v0 = x0 * k;
   r.v1 = x1 * k;
@@ -328,6 +330,7 @@ __device__ __forceinline__ void beam_grads(const AdjArgs& a, AdjBeam& q, double 
 
 // Recompute beam b's states over a segment of len steps from its checkpoint with the
 // recorded moments (the stepping kernel's arithmetic, hence its bits) into the tape.
+template <bool SK>
 __device__ __forceinline__ void recompute_segment(const AdjArgs& a, const AdjBeam& q, long long b, long long seg,
                                                   long long s0, long long len) {
   const long long plane = a.plane;
@@ -363,7 +366,7 @@ __device__ __forceinline__ void recompute_segment(const AdjArgs& a, const AdjBea
     const double t0 = (((f1[0] + 2.0 * f2[0]) + 2.0 * f3[0]) + f4[0]) * (1.0 / 6.0) - cr0 * (1.0 / 12.0);
     const double t1 = (((f1[1] + 2.0 * f2[1]) + 2.0 * f3[1]) + f4[1]) * (1.0 / 6.0) - cr1 * (1.0 / 12.0);
     const double t2 = (((f1[2] + 2.0 * f2[2]) + 2.0 * f3[2]) + f4[2]) * (1.0 / 6.0) - cr2 * (1.0 / 12.0);
-    rotate2(t0, t1, t2, P0, P1, P2);
+    rotate2<false, SK>(t0, t1, t2, P0, P1, P2);
     if (a.renorm) {   // as the forward stepper: one Newton step for 1/sqrt from 1
       const double nrm2 = (P0 * P0 + P1 * P1) + P2 * P2;
       const double inv = fma(-0.5, nrm2, 1.5);
@@ -388,6 +391,7 @@ __device__ __forceinline__ void load_step(const AdjArgs& a, AdjBeam& B, long lon
 }
 
 // A: P_{n+1} = R(Theta) P_n / |.|  ->  Theta-bar, f4-bar
+template <bool SK>
 __device__ __forceinline__ void phase_a(int renorm, AdjBeam& B, const double (*sJ)[6], const Radial& g0,
                                         const Radial& gm, const Radial& g1, double (&red)[6], double& gn0) {
   double f1[3], f2[3], f3[3], f4[3], cr[3];
@@ -400,7 +404,7 @@ __device__ __forceinline__ void phase_a(int renorm, AdjBeam& B, const double (*s
 #pragma unroll
   for (int c = 0; c < 3; ++c)
     th[c] = (((f1[c] + 2.0 * f2[c]) + 2.0 * f3[c]) + f4[c]) * (1.0 / 6.0) - cr[c] * (1.0 / 12.0);
-  const Rot R = make_rot(th[0], th[1], th[2]);
+  const Rot R = make_rot<SK>(th[0], th[1], th[2]);
   double Pp[3];
   rot_fwd(R, B.P[0], B.P[1], B.P[2], Pp[0], Pp[1], Pp[2]);
   double Ppb[3] = {B.Pb[0], B.Pb[1], B.Pb[2]};
@@ -429,11 +433,12 @@ __device__ __forceinline__ void phase_a(int renorm, AdjBeam& B, const double (*s
   b_bar(B, Bb, B.c1, g1, red, gn0);
 }
 // B: Y4 = R(f3) P  ->  f3-bar
+template <bool SK>
 __device__ __forceinline__ void phase_b(AdjBeam& B, const double (*sJ)[6], const double* Jb,
                                         const Radial& gm, double (&red)[6], double& gn0) {
   double f3[3], Y[3], Yb[3], om[3], f3b[3];
   stage_f(B, sJ[2], gm, B.cm, B.hcm, f3);
-  const Rot R = make_rot(f3[0], f3[1], f3[2]);
+  const Rot R = make_rot<SK>(f3[0], f3[1], f3[2]);
   rot_fwd(R, B.P[0], B.P[1], B.P[2], Y[0], Y[1], Y[2]);
   m_bar(B, Jb, B.c1, Y, Yb);
   rot_inv_add(R, Yb[0], Yb[1], Yb[2], B.Pb);
@@ -445,13 +450,14 @@ __device__ __forceinline__ void phase_b(AdjBeam& B, const double (*sJ)[6], const
   b_bar(B, Bb, B.cm, gm, red, gn0);
 }
 // C: Y3 = R(Om) P, Om = f2/2 - (f1 x f2)/8  ->  f2-bar, f1-bar
+template <bool SK>
 __device__ __forceinline__ void phase_c(AdjBeam& B, const double (*sJ)[6], const double* Jb,
                                         const Radial& g0, const Radial& gm, double (&red)[6], double& gn0) {
   double f1[3], f2[3], cr[3], Y[3], Yb[3], om[3], ob[3], a1[3], a2[3], f2b[3];
   stage_f(B, sJ[0], g0, B.c0, B.hc0, f1);
   stage_f(B, sJ[1], gm, B.cm, B.hcm, f2);
   cross(f1, f2, cr);
-  const Rot R = make_rot(0.5 * f2[0] - 0.125 * cr[0], 0.5 * f2[1] - 0.125 * cr[1],
+  const Rot R = make_rot<SK>(0.5 * f2[0] - 0.125 * cr[0], 0.5 * f2[1] - 0.125 * cr[1],
                          0.5 * f2[2] - 0.125 * cr[2]);
   rot_fwd(R, B.P[0], B.P[1], B.P[2], Y[0], Y[1], Y[2]);
   m_bar(B, Jb, B.cm, Y, Yb);
@@ -469,11 +475,12 @@ __device__ __forceinline__ void phase_c(AdjBeam& B, const double (*sJ)[6], const
   b_bar(B, Bb, B.cm, gm, red, gn0);
 }
 // D: Y2 = R(f1/2) P  ->  f1-bar complete
+template <bool SK>
 __device__ __forceinline__ void phase_d(AdjBeam& B, const double (*sJ)[6], const double* Jb,
                                         const Radial& g0, double (&red)[6], double& gn0) {
   double f1[3], Y[3], Yb[3], om[3], ob[3];
   stage_f(B, sJ[0], g0, B.c0, B.hc0, f1);
-  const Rot R = make_rot(0.5 * f1[0], 0.5 * f1[1], 0.5 * f1[2]);
+  const Rot R = make_rot<SK>(0.5 * f1[0], 0.5 * f1[1], 0.5 * f1[2]);
   rot_fwd(R, B.P[0], B.P[1], B.P[2], Y[0], Y[1], Y[2]);
   m_bar(B, Jb, B.cm, Y, Yb);
   rot_inv_add(R, Yb[0], Yb[1], Yb[2], B.Pb);
@@ -522,6 +529,9 @@ __device__ __forceinline__ void adj_store(const AdjArgs& a, const AdjBeam& B, lo
 // r0 of step n is r1 of step n - 1), and the recorded moments of the step go to LDS.
 template <int BPT, int BS>
 __global__ void __launch_bounds__(BS) k_adjoint2(AdjArgs a) {
+  // one wavefront per SIMD has registers for the literals and no other wavefront's vector
+  // instructions to issue the moves beside
+  constexpr bool kSK = BPT != 1 || BS != kBlockSmall;
   __shared__ double sJ[2][24];
   __shared__ SumLds L;
   constexpr int NQ = BPT > 0 ? BPT : 1;
@@ -570,11 +580,11 @@ __global__ void __launch_bounds__(BS) k_adjoint2(AdjArgs a) {
     if constexpr (BPT > 0) {
 #pragma unroll
       for (int i = 0; i < BPT; ++i)
-        if (q[i].on) recompute_segment(a, q[i], gt + i * nthr, seg, s0, len);
+        if (q[i].on) recompute_segment<kSK>(a, q[i], gt + i * nthr, seg, s0, len);
     } else {
       for (long long b = gt; b < a.nb; b += nthr) {
         beam_init(a, b, true, q[0]);
-        recompute_segment(a, q[0], b, seg, s0, len);
+        recompute_segment<kSK>(a, q[0], b, seg, s0, len);
       }
     }
     // -- reverse steps of the segment
@@ -607,16 +617,16 @@ __global__ void __launch_bounds__(BS) k_adjoint2(AdjArgs a) {
       };
 #pragma unroll
       for (int c = 0; c < 6; ++c) red[c] = 0.0;
-      each([&](AdjBeam& B) { phase_a(renorm, B, J, g0, gm, g1, red, gn0); }, t, g0, gm, g1);
+      each([&](AdjBeam& B) { phase_a<kSK>(renorm, B, J, g0, gm, g1, red, gn0); }, t, g0, gm, g1);
       if (!(ok = grid_sum<6, BS>(a, epoch++, red, L))) break;
       moments(g1.mu);
-      each([&](AdjBeam& B) { phase_b(B, J, Jb, gm, red, gn0); }, t, g0, gm, g1);
+      each([&](AdjBeam& B) { phase_b<kSK>(B, J, Jb, gm, red, gn0); }, t, g0, gm, g1);
       if (!(ok = grid_sum<6, BS>(a, epoch++, red, L))) break;
       moments(gm.mu);
-      each([&](AdjBeam& B) { phase_c(B, J, Jb, g0, gm, red, gn0); }, t, g0, gm, g1);
+      each([&](AdjBeam& B) { phase_c<kSK>(B, J, Jb, g0, gm, red, gn0); }, t, g0, gm, g1);
       if (!(ok = grid_sum<6, BS>(a, epoch++, red, L))) break;
       moments(gm.mu);
-      each([&](AdjBeam& B) { phase_d(B, J, Jb, g0, red, gn0); }, t, g0, gm, g1);
+      each([&](AdjBeam& B) { phase_d<kSK>(B, J, Jb, g0, red, gn0); }, t, g0, gm, g1);
       double PN[NQ][3], c0n[NQ], cmn[NQ], h0n[NQ], hmn[NQ];
       Radial gn = g0, gnm = g0;
       ok = grid_sum<6, BS>(a, epoch++, red, L, [&] {

@@ -21,6 +21,16 @@ constexpr double kTwo64 = 18446744073709551616.0;
 // sin and cos of one argument.  Reduction x = k pi/2 + r with k the nearest integer to 2x/pi and a
 // three-part split of pi/2 (each part applied with one fma); then Taylor series of sin
 // (to r^17) and cos (to r^18) by Horner in r^2; the quadrant k mod 4 picks signs.
+// SK: the constants of the series are put into scalar registers at their use (two scalar moves
+// each, which issue beside other wavefronts' vector instructions).  Left to itself the
+// compiler does that in the three-flavour kernels, but in the two-flavour ones it copies each
+// constant from vector registers into its fma (17 of 96 instructions, 20-60 registers spilled).
+template <bool SK>
+__device__ __forceinline__ double fma_const(double a, double b, double k) {
+  if constexpr (SK) __asm__ volatile("" : "+s"(k));
+  return fma(a, b, k);
+}
+template <bool SK = false>
 __device__ __forceinline__ void sincos_nb(double x, double& sn, double& cs) {
   // k = the exact product x 2/pi rounded once to the nearest integer: the fma adds
   // 1.5 2^52 and rounds in a binade of unit spacing, so t - 1.5 2^52 = k and the low bits
@@ -31,24 +41,22 @@ __device__ __forceinline__ void sincos_nb(double x, double& sn, double& cs) {
   r = fma(-k, 0x1.1a62633145c07p-54, r);
   r = fma(-k, -0x1.f1976b7ed8fbcp-110, r);
   const double r2 = r * r;
-  double ps = 1.0 / 355687428096000.0;
-  ps = fma(ps, r2, -1.0 / 1307674368000.0);
-  ps = fma(ps, r2, 1.0 / 6227020800.0);
-  ps = fma(ps, r2, -1.0 / 39916800.0);
-  ps = fma(ps, r2, 1.0 / 362880.0);
-  ps = fma(ps, r2, -1.0 / 5040.0);
-  ps = fma(ps, r2, 1.0 / 120.0);
-  ps = fma(ps, r2, -1.0 / 6.0);
+  double ps = fma_const<SK>(1.0 / 355687428096000.0, r2, -1.0 / 1307674368000.0);
+  ps = fma_const<SK>(ps, r2, 1.0 / 6227020800.0);
+  ps = fma_const<SK>(ps, r2, -1.0 / 39916800.0);
+  ps = fma_const<SK>(ps, r2, 1.0 / 362880.0);
+  ps = fma_const<SK>(ps, r2, -1.0 / 5040.0);
+  ps = fma_const<SK>(ps, r2, 1.0 / 120.0);
+  ps = fma_const<SK>(ps, r2, -1.0 / 6.0);
   const double s = fma(r2 * r, ps, r);
-  double pc = -1.0 / 6402373705728000.0;
-  pc = fma(pc, r2, 1.0 / 20922789888000.0);
-  pc = fma(pc, r2, -1.0 / 87178291200.0);
-  pc = fma(pc, r2, 1.0 / 479001600.0);
-  pc = fma(pc, r2, -1.0 / 3628800.0);
-  pc = fma(pc, r2, 1.0 / 40320.0);
-  pc = fma(pc, r2, -1.0 / 720.0);
-  pc = fma(pc, r2, 1.0 / 24.0);
-  pc = fma(pc, r2, -0.5);
+  double pc = fma_const<SK>(-1.0 / 6402373705728000.0, r2, 1.0 / 20922789888000.0);
+  pc = fma_const<SK>(pc, r2, -1.0 / 87178291200.0);
+  pc = fma_const<SK>(pc, r2, 1.0 / 479001600.0);
+  pc = fma_const<SK>(pc, r2, -1.0 / 3628800.0);
+  pc = fma_const<SK>(pc, r2, 1.0 / 40320.0);
+  pc = fma_const<SK>(pc, r2, -1.0 / 720.0);
+  pc = fma_const<SK>(pc, r2, 1.0 / 24.0);
+  pc = fma_const<SK>(pc, r2, -0.5);
   const double c = fma(r2, pc, 1.0);
   const int quad = (int)(__double_as_longlong(t) & 3);
   const double a = (quad & 1) ? c : s;    // |sin| candidate
@@ -57,8 +65,10 @@ __device__ __forceinline__ void sincos_nb(double x, double& sn, double& cs) {
   cs = ((quad + 1) & 2) ? -b : b;
 }
 
-// The same sin/cos with its constants read from a table (for instance in LDS, so that a
-// kernel short of registers does not hold them in VGPRs): c = the values sincos_coefs writes.
+// The same sin/cos with its constants read from a table in LDS: c = the values sincos_coefs
+// writes.  For kernels that run few wavefronts on a SIMD, where scalar moves lie in the
+// chain: stepping 1024 beams takes 13.3 us per step with the table and 13.8 with SK, but a batch of
+// 16 small models 28.9 with it and 26.2 with SK, the 200k-beam gradient 6.76 and 6.52 ms.
 constexpr int kSinCosTab = 21;
 __device__ __forceinline__ void sincos_coefs(double* c) {
   c[0] = 0x1.45f306dc9c883p-1; c[1] = 0x1.921fb54442d18p+0; c[2] = 0x1.1a62633145c07p-54;
@@ -348,8 +358,8 @@ __device__ __forceinline__ void exp3_apply(const Herm3& K, cplx psi[3]) {
 
 // Bloch-vector rotation about x by |x| (two flavours): unit quaternion
 // (cos|x|/2, sin(|x|/2) x/|x|), P' = P + w t + v x t with t = 2 v x P.  TAB: the sin/cos
-// constants are read from tab (sincos_coefs) instead of immediates.
-template <bool TAB = false>
+// constants are read from tab (sincos_coefs).
+template <bool TAB = false, bool SK = true>
 __device__ __forceinline__ void rotate2(const double x0, const double x1, const double x2,
                                         double& P0, double& P1, double& P2,
                                         const double* tab = nullptr) {
@@ -362,7 +372,7 @@ __device__ __forceinline__ void rotate2(const double x0, const double x1, const 
     ih = 0.5 / th;
   }
   if constexpr (TAB) sincos_tab(0.5 * th, tab, s, c);
-  else sincos_nb(0.5 * th, s, c);
+  else sincos_nb<SK>(0.5 * th, s, c);
   const double k = div_by_sqrt(s, th, ih);
   const double v0 = x0 * k, v1 = x1 * k, v2 = x2 * k;
   double t0 = v1 * P2 - v2 * P1;

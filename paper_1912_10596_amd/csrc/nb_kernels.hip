@@ -457,8 +457,8 @@ __device__ __forceinline__ void keep_nunu2(const double* cb, const double (*sJ)[
 // ADAPT (final update only): the new state goes to Xo instead of X, and emax keeps the
 // largest embedded error estimate |Theta - f2|^2 of the lane's beams.
 // EXT: extended bulb model.  pre: the lane's first beam, if it was loaded before.
-// sct: the block's sin/cos constants (sincos_coefs, in LDS).
-template <int KIND, bool ADAPT = false, bool EXT = false>
+// TAB: sin/cos constants from sct, the block's table in LDS (sincos_coefs).
+template <int KIND, bool TAB, bool ADAPT = false, bool EXT = false>
 __device__ __forceinline__ void row2(const double* X, double* Xo, long long plane, long long rb, int NE,
                                      const double* tab, const double* cb, const double* rc, int renorm, int lane,
                                      I128& T, int& err, double& emax, const double* sct,
@@ -491,17 +491,17 @@ __device__ __forceinline__ void row2(const double* X, double* Xo, long long plan
         double f1[3], f2[3], f3[3], f4[3];
         if (KIND != 3) gen2c(bx, bz, rc + 0, f1);
         if (KIND == 1) {
-          rotate2<true>(0.5 * f1[0], 0.5 * f1[1], 0.5 * f1[2], P0, P1, P2, sct);
+          rotate2<TAB>(0.5 * f1[0], 0.5 * f1[1], 0.5 * f1[2], P0, P1, P2, sct);
         } else if (KIND == 2) {
           gen2c(bx, bz, rc + 5, f2);
           const double cr0 = f1[1] * f2[2] - f1[2] * f2[1];
           const double cr1 = f1[2] * f2[0] - f1[0] * f2[2];
           const double cr2 = f1[0] * f2[1] - f1[1] * f2[0];
-          rotate2<true>(0.5 * f2[0] - 0.125 * cr0, 0.5 * f2[1] - 0.125 * cr1, 0.5 * f2[2] - 0.125 * cr2,
+          rotate2<TAB>(0.5 * f2[0] - 0.125 * cr0, 0.5 * f2[1] - 0.125 * cr1, 0.5 * f2[2] - 0.125 * cr2,
                   P0, P1, P2, sct);
         } else if (KIND == 3) {
           gen2c(bx, bz, rc + 10, f3);
-          rotate2<true>(f3[0], f3[1], f3[2], P0, P1, P2, sct);
+          rotate2<TAB>(f3[0], f3[1], f3[2], P0, P1, P2, sct);
         } else {
           gen2c(bx, bz, rc + 5, f2);
           gen2c(bx, bz, rc + 10, f3);
@@ -517,7 +517,7 @@ __device__ __forceinline__ void row2(const double* X, double* Xo, long long plan
             const double e = (d0 * d0 + d1 * d1) + d2 * d2;
             emax = (e > emax) ? e : emax;
           }
-          rotate2<true>(t0, t1, t2, P0, P1, P2, sct);
+          rotate2<TAB>(t0, t1, t2, P0, P1, P2, sct);
           if (renorm) {
             const double nrm2 = (P0 * P0 + P1 * P1) + P2 * P2;
             if (!(fabs(nrm2 - 1.0) <= kRenormTol)) err |= 8;
@@ -618,7 +618,7 @@ __device__ __forceinline__ void fold_rows2(int lane, long long* fl, int nrows, c
 template <int KIND, bool EXT, int R, int RS>
 __device__ __forceinline__ void group2(double* X, long long plane, long long gb0, int NE, int gn,
                                        const double* tab, const double* cb, const double* rt, int renorm,
-                                       int lane, long long* fl, I128& T, int& err, const double* sct) {
+                                       int lane, long long* fl, I128& T, int& err) {
   constexpr int NM = EXT ? 4 : 2;
   constexpr int NCR = 3 * R, S = fold2_stride(R);   // R > 1
   const Scales sc{cb[kC2Sc + 0], cb[kC2Sc + 1], cb[kC2Sc + 2], cb[kC2Sc + 3]};
@@ -626,6 +626,23 @@ __device__ __forceinline__ void group2(double* X, long long plane, long long gb0
   const int nchunk = (nbeam + 63) >> 6;
   int i = lane / NE;                 // the lane's row and energy in the current chunk
   int k = lane - i * NE;
+  const int irow = 64 / NE, krow = 64 - irow * NE;   // a chunk further: irow rows, krow energies
+  // a plane's base is uniform and the group's byte offsets fit 32 bits (at most kGroup rows of
+  // kGroupMaxNE energies): one offset register serves all planes, and the next beam is found
+  // without a loop over lanes (256-model batch 2.92 -> 2.75 ms per step, extended 20M beams
+  // 858 -> 843 us, against 64-bit addresses and a loop that stepped k row by row)
+  char *X0 = reinterpret_cast<char*>(X + gb0), *X1 = reinterpret_cast<char*>(X + gb0 + plane),
+       *X2 = reinterpret_cast<char*>(X + gb0 + 2 * plane);
+  const auto at = [](char* base, unsigned off) -> double& { return *reinterpret_cast<double*>(base + off); };
+  // (PF: two species, so row 2 or 3 of the tables)
+  const auto load_tab = [&](int row, int e, double& x, double& z, double& w) {
+    const unsigned off = 8u * (unsigned)e;
+    const unsigned woff = off + (rt[row * RS + kRowS] != 0.0 ? 8u * (unsigned)NE : 0u);
+    char* t = reinterpret_cast<char*>(const_cast<double*>(tab));
+    x = at(t, off);
+    z = at(t + 8 * (size_t)NE, off);
+    w = at(t + 16 * (size_t)NE, woff);
+  };
   double q0 = 0.0, q1 = 0.0, q2 = 0.0;
   // PF (batches): the energy tables of a batch's models stay in HBM, so the lane's table
   // values (vacuum terms and weight) for its beam in the next chunk are loaded with that
@@ -634,10 +651,9 @@ __device__ __forceinline__ void group2(double* X, long long plane, long long gb0
   constexpr bool PF = !EXT;
   double tx = 0.0, tz = 0.0, tw = 0.0;
   if (lane < nbeam) {
-    q0 = X[gb0 + lane]; q1 = X[gb0 + lane + plane]; q2 = X[gb0 + lane + 2 * plane];
-    if (PF) {
-      tx = tab[k]; tz = tab[NE + k]; tw = tab[(size_t)(2 + (int)rt[i * RS + kRowS]) * NE + k];
-    }
+    const unsigned off = 8u * (unsigned)lane;
+    q0 = at(X0, off); q1 = at(X1, off); q2 = at(X2, off);
+    if (PF) load_tab(i, k, tx, tz, tw);
   }
   unsigned long long acc[3] = {0ull, 0ull, 0ull};
   unsigned long long cnt = 0;        // contributions in acc (each carries kFixMagic)
@@ -649,16 +665,15 @@ __device__ __forceinline__ void group2(double* X, long long plane, long long gb0
     const bool on = f < nbeam;
     double P0 = q0, P1 = q1, P2 = q2;
     const double bxc = tx, bzc = tz, wsc = tw;
-    if (f + 64 < nbeam) {    // prefetch the lane's next beam
-      q0 = X[gb0 + f + 64]; q1 = X[gb0 + f + 64 + plane]; q2 = X[gb0 + f + 64 + 2 * plane];
-      if (PF) {
-        int k2 = k + 64, i2 = i;
-        while (k2 >= NE) {
-          k2 -= NE;
-          ++i2;
-        }
-        tx = tab[k2]; tz = tab[NE + k2]; tw = tab[(size_t)(2 + (int)rt[i2 * RS + kRowS]) * NE + k2];
-      }
+    const unsigned off = 8u * (unsigned)f;
+    int kn = k + krow, in = i + irow;   // the lane's beam in the next chunk
+    if (kn >= NE) {
+      kn -= NE;
+      ++in;
+    }
+    if (f + 64 < nbeam) {    // prefetch it
+      q0 = at(X0 + 512, off); q1 = at(X1 + 512, off); q2 = at(X2 + 512, off);
+      if (PF) load_tab(in, kn, tx, tz, tw);
     }
     __asm__ volatile("" ::: "memory");   // the row constants are re-read from LDS per beam
     unsigned long long x0 = 0ull, x1 = 0ull, x2 = 0ull;
@@ -670,17 +685,17 @@ __device__ __forceinline__ void group2(double* X, long long plane, long long gb0
         double f1[3], f2[3], f3[3], f4[3];
         if (KIND != 3) gen2c(bx, bz, rc + 0, f1);
         if (KIND == 1) {
-          rotate2<true>(0.5 * f1[0], 0.5 * f1[1], 0.5 * f1[2], P0, P1, P2, sct);
+          rotate2(0.5 * f1[0], 0.5 * f1[1], 0.5 * f1[2], P0, P1, P2);
         } else if (KIND == 2) {
           gen2c(bx, bz, rc + 5, f2);
           const double cr0 = f1[1] * f2[2] - f1[2] * f2[1];
           const double cr1 = f1[2] * f2[0] - f1[0] * f2[2];
           const double cr2 = f1[0] * f2[1] - f1[1] * f2[0];
-          rotate2<true>(0.5 * f2[0] - 0.125 * cr0, 0.5 * f2[1] - 0.125 * cr1, 0.5 * f2[2] - 0.125 * cr2,
-                        P0, P1, P2, sct);
+          rotate2(0.5 * f2[0] - 0.125 * cr0, 0.5 * f2[1] - 0.125 * cr1, 0.5 * f2[2] - 0.125 * cr2,
+                        P0, P1, P2);
         } else if (KIND == 3) {
           gen2c(bx, bz, rc + 10, f3);
-          rotate2<true>(f3[0], f3[1], f3[2], P0, P1, P2, sct);
+          rotate2(f3[0], f3[1], f3[2], P0, P1, P2);
         } else {
           gen2c(bx, bz, rc + 5, f2);
           gen2c(bx, bz, rc + 10, f3);
@@ -691,7 +706,7 @@ __device__ __forceinline__ void group2(double* X, long long plane, long long gb0
           const double t0 = (((f1[0] + 2.0 * f2[0]) + 2.0 * f3[0]) + f4[0]) * (1.0 / 6.0) - cr0 * (1.0 / 12.0);
           const double t1 = (((f1[1] + 2.0 * f2[1]) + 2.0 * f3[1]) + f4[1]) * (1.0 / 6.0) - cr1 * (1.0 / 12.0);
           const double t2 = (((f1[2] + 2.0 * f2[2]) + 2.0 * f3[2]) + f4[2]) * (1.0 / 6.0) - cr2 * (1.0 / 12.0);
-          rotate2<true>(t0, t1, t2, P0, P1, P2, sct);
+          rotate2(t0, t1, t2, P0, P1, P2);
           if (renorm) {
             const double nrm2 = (P0 * P0 + P1 * P1) + P2 * P2;
             if (!(fabs(nrm2 - 1.0) <= kRenormTol)) err |= 8;
@@ -700,9 +715,9 @@ __device__ __forceinline__ void group2(double* X, long long plane, long long gb0
             P1 = P1 * inv;
             P2 = P2 * inv;
           }
-          X[gb0 + f] = P0;
-          X[gb0 + f + plane] = P1;
-          X[gb0 + f + 2 * plane] = P2;
+          at(X0, off) = P0;
+          at(X1, off) = P1;
+          at(X2, off) = P2;
         }
       }
       // rho~: rho for neutrinos, -rho^* (Bloch (-x, y, -z)) for antineutrinos
@@ -746,11 +761,8 @@ __device__ __forceinline__ void group2(double* X, long long plane, long long gb0
       acc[0] += x0; acc[1] += x1; acc[2] += x2;
       ++cnt;
     }
-    k += 64;                 // the lane's beam in the next chunk
-    while (k >= NE) {
-      k -= NE;
-      ++i;
-    }
+    k = kn;
+    i = in;
   }
   if constexpr (R == 1) return;
   if (ns) fold_rows2<R, NM>(lane, fl, ns, rt + (r - ns) * kRowC, sc, Tq, err);
@@ -835,18 +847,18 @@ __device__ __forceinline__ void stage2(const StepArgs& a, double h, const double
       }
       __asm__ volatile("" ::: "memory");
       if (!ADAPT && NE <= kGroupMaxNE) {
-        group2<KIND, true, kFoldRowsExt, kRowC>(Xo, plane, row * NE, NE, gn, tab, cb, rt, renorm, lane, fl, T, err, sct);
+        group2<KIND, true, kFoldRowsExt, kRowC>(Xo, plane, row * NE, NE, gn, tab, cb, rt, renorm, lane, fl, T, err);
         row += gn;
       } else {
         for (int i = 0; i < gn; ++i, ++row)
-          row2<KIND, ADAPT, true>(X, Xo, plane, row * NE, NE, tab, cb, rt + i * kRowC, renorm, lane, T, err, emax,
-                                  sct);
+          row2<KIND, false, ADAPT, true>(X, Xo, plane, row * NE, NE, tab, cb, rt + i * kRowC, renorm, lane, T, err, emax,
+                                         nullptr);
       }
     }
   } else if (nrw <= kRowKeep) {
     keep_nunu2<KIND>(cb, sJ, lane, nrw, rt);
     for (int i = 0; i < nrw; ++i)
-      row2<KIND, ADAPT>(X, Xo, plane, (gw + i * nw) * NE, NE, tab, cb, rt + i * kRowP, renorm, lane, T, err, emax,
+      row2<KIND, true, ADAPT>(X, Xo, plane, (gw + i * nw) * NE, NE, tab, cb, rt + i * kRowP, renorm, lane, T, err, emax,
                         sct, i == 0 ? pre : nullptr);
   } else {
     for (int r0 = 0; r0 < nrw; r0 += kRowKeep) {
@@ -860,7 +872,7 @@ __device__ __forceinline__ void stage2(const StepArgs& a, double h, const double
       }
       __asm__ volatile("" ::: "memory");
       for (int i = 0; i < gn; ++i)
-        row2<KIND, ADAPT>(X, Xo, plane, (gw + (r0 + i) * nw) * NE, NE, tab, cb, rt + i * kRowP, renorm, lane, T, err,
+        row2<KIND, true, ADAPT>(X, Xo, plane, (gw + (r0 + i) * nw) * NE, NE, tab, cb, rt + i * kRowP, renorm, lane, T, err,
                           emax, sct, r0 + i == 0 ? pre : nullptr);
     }
   }
@@ -1966,8 +1978,7 @@ __device__ __forceinline__ void batch_prep(const BatchArgs& a, long long n, cons
 }
 template <int KIND>
 __device__ __forceinline__ bool batch_stage(const BatchArgs& a, long long n, unsigned epoch, const BatchWave& W, int lane,
-                                            double (*Jv)[6], double* cb, double* rt, unsigned long long* sx,
-                                            const double* sct, int& err) {
+                                            double (*Jv)[6], double* cb, double* rt, unsigned long long* sx, int& err) {
   const double* J[4] = {Jv[0], Jv[1], Jv[2], Jv[3]};   // this wave's LDS block
   double enone = 0.0;
   int m = W.m0;
@@ -2003,11 +2014,11 @@ __device__ __forceinline__ bool batch_stage(const BatchArgs& a, long long n, uns
       const long long gb0 = mbeam0 + (row - mrow0) * mNE;
       if (mNE <= kGroupMaxNE) {
         group2<KIND, false, kFoldRowsBatch, kRowP>(a.X, a.plane, gb0, mNE, gn, tab, cb, rt, a.renorm, lane, nullptr, T,
-                                                   err, sct);
+                                                   err);
       } else {
         for (int i = 0; i < gn; ++i)
-          row2<KIND>(a.X, a.X, a.plane, gb0 + (long long)i * mNE, mNE, tab, cb, rt + i * kRowP, a.renorm, lane, T, err,
-                     enone, sct);
+          row2<KIND, false>(a.X, a.X, a.plane, gb0 + (long long)i * mNE, mNE, tab, cb, rt + i * kRowP, a.renorm, lane, T, err,
+                            enone, nullptr);
       }
       row += gn;
     }
@@ -2028,11 +2039,8 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
   __shared__ double scb[BS / 64][kC2Size];
   __shared__ unsigned long long sxw[BS / 64][12];
   __shared__ double srt[BS / 64][kRowKeep * kRowP];   // each wave's row-constant table
-  __shared__ double s_sct[kSinCosTab];   // sin/cos constants of the rotations
   static_assert(kGroup <= kRowKeep, "one table for kept rows and groups");
   if (launch_aborted(a.sync)) return;
-  if (threadIdx.x == 0) sincos_coefs(s_sct);
-  __syncthreads();
   // the wavefront index as a wave-uniform (scalar) value: the row indices, their divisions
   // and the row base offsets derived from it then live in scalar registers
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -2068,12 +2076,12 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
   unsigned epoch = 0;
   int err = 0;
   batch_prep(a, step0, W, lane, cb, rt);
-  bool ok = batch_stage<0>(a, step0, epoch++, W, lane, Jv, cb, rt, sx, s_sct, err);
+  bool ok = batch_stage<0>(a, step0, epoch++, W, lane, Jv, cb, rt, sx, err);
   for (long long n = step0; ok && n < step0 + nsteps; ++n) {
-    ok = batch_stage<1>(a, n, epoch++, W, lane, Jv, cb, rt, sx, s_sct, err) &&
-         batch_stage<2>(a, n, epoch++, W, lane, Jv, cb, rt, sx, s_sct, err) &&
-         batch_stage<3>(a, n, epoch++, W, lane, Jv, cb, rt, sx, s_sct, err) &&
-         batch_stage<4>(a, n, epoch++, W, lane, Jv, cb, rt, sx, s_sct, err);
+    ok = batch_stage<1>(a, n, epoch++, W, lane, Jv, cb, rt, sx, err) &&
+         batch_stage<2>(a, n, epoch++, W, lane, Jv, cb, rt, sx, err) &&
+         batch_stage<3>(a, n, epoch++, W, lane, Jv, cb, rt, sx, err) &&
+         batch_stage<4>(a, n, epoch++, W, lane, Jv, cb, rt, sx, err);
     // (a.lockstep is uniform over the grid, ok is not: a wavefront that gave up still meets the
     // others of its block, which read the abort word at their next wait)
     if (a.lockstep) {

@@ -127,3 +127,26 @@ def test_adjoint_grid_sizes(nb, oracle, n_energy, n_u):
     np.testing.assert_allclose(sb.cpu().numpy(), sbo, rtol=1e-9, atol=1e-9 * np.abs(sbo).max())
     m.reset()
     np.testing.assert_array_equal(m.adjoint(torch.as_tensor(c, device="cuda")), g)
+
+
+@pytest.mark.parametrize("n_energy", [1, 21, 32, 63, 64, 65, 127, 128, 129, 1984, 1985])
+@pytest.mark.parametrize("n_phi", [0, 2])
+def test_row_groups_across_chunks(nb, oracle, n_energy, n_phi):
+    """Rows streamed in groups, where a lane's next beam lies 64 beams further: rows that divide a
+    64-lane chunk, fill it, or end one short of or one past it, and the longest row that is
+    grouped.  n_phi = 0: a batch of two such models on one block (many rows to a wavefront);
+    otherwise the extended model."""
+    n_u = 4 if n_energy > 1000 else 37
+    ds = [workloads.small_params(n_flavor=2, n_energy=n_energy, n_u=n_u + i, n_steps=3, r_start_km=100.0,
+                                 r_end_km=100.1, n0_cm3=1e32, n_phi=n_phi) for i in range(1 if n_phi else 2)]
+    print(f"row groups: {n_energy} energies, n_phi {n_phi}", flush=True)
+    m = nb.Model(ds[0] if n_phi else ds)
+    m.set_tuning(256, 1)
+    m.run()
+    got = m.get_state().cpu().numpy()
+    at = 0
+    for d in ds:
+        o = oracle.Model(d)
+        o.run()
+        np.testing.assert_array_equal(got[:, at:at + o.nb], o.get_state())
+        at += o.nb
