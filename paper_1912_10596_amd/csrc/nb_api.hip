@@ -776,20 +776,36 @@ static int upload_partition(nb_model* m) {
   return NB_OK;
 }
 
+// Blocks of bs threads of kernel fn that a CU holds at once with dyn bytes of dynamic LDS.  A
+// CU's 160 KB of LDS are given to blocks in units of 1280 bytes, to which the runtime's
+// occupancy query does not round: three blocks of 53984 bytes (two flavours, 1070 energies)
+// count as resident there, but take 43 of the 128 units each, and a grid of three per CU
+// waits at its first barrier for blocks that cannot start.
+static constexpr int kLdsUnit = 1280, kLdsUnits = 160 * 1024 / kLdsUnit;
+static int blocks_per_cu(const void* fn, int bs, size_t dyn, int* per) {
+  hipFuncAttributes at{};
+  NB_HIP(hipFuncGetAttributes(&at, fn));
+  NB_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(per, fn, bs, dyn));
+  const long long units = ((long long)(at.sharedSizeBytes + dyn) + kLdsUnit - 1) / kLdsUnit;
+  if (units > 0) *per = (int)std::min<long long>(*per, kLdsUnits / units);
+  return NB_OK;
+}
+
 // Resident blocks of the model's fixed-step kernels at bs threads per block: the least
 // per-CU occupancy over the kernels its launches use (with their dynamic LDS) times the CUs,
 // at most kMaxBlocks and p.max_blocks; 0 if one of them cannot be resident at that size.
 static int fixed_step_capacity(const nb_model* m, int cus, int bs, int* out) {
   int per = 0;
-  NB_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, advance_kernel(m, bs), bs, advance_dyn_lds(m)));
+  int rc = blocks_per_cu(advance_kernel(m, bs), bs, advance_dyn_lds(m), &per);
+  if (rc) return rc;
   if (bs == kBlock && !m->batch && m->nf == 3 && !state_fp32(m) && m->p.n_phi == 0) {
     int ppk = 0;   // the packed-tail variant may take any of these launches
-    NB_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&ppk, packed_kernel(m), bs, advance_dyn_lds(m)));
+    if ((rc = blocks_per_cu(packed_kernel(m), bs, advance_dyn_lds(m), &ppk))) return rc;
     per = std::min(per, ppk);
   }
   if (advance_kernel_f32(m, bs)) {
     int p32 = 0;
-    NB_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&p32, advance_kernel_f32(m, bs), bs, f32_dyn_lds(m)));
+    if ((rc = blocks_per_cu(advance_kernel_f32(m, bs), bs, f32_dyn_lds(m), &p32))) return rc;
     per = std::min(per, p32);
   }
   int cap = std::min(cus * per, kMaxBlocks);
@@ -815,7 +831,8 @@ extern "C" int nb_bind(nb_model* m, void* dev_ws, size_t bytes, void* hip_stream
   const int abs_ = adaptive_block(m, cus);
   if (adaptive_kernel(m, abs_)) {
     int nba = 0;
-    NB_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nba, adaptive_kernel(m, abs_), abs_, advance_dyn_lds(m)));
+    const int rc = blocks_per_cu(adaptive_kernel(m, abs_), abs_, advance_dyn_lds(m), &nba);
+    if (rc) return rc;
     if (nba < 1) return fail(NB_EHIP, "adaptive kernel cannot be resident");
     cap_adaptive = std::min(cus * nba, kMaxBlocks);
     if (m->p.max_blocks > 0) cap_adaptive = std::min(cap_adaptive, (int)m->p.max_blocks);
@@ -852,7 +869,8 @@ extern "C" int nb_bind(nb_model* m, void* dev_ws, size_t bytes, void* hip_stream
     for (int i = 0; i < 5 && !m->adj_bpt; ++i) {
       const Shape sh = i < 4 ? shapes[i] : Shape{-1, kBlock};   // -1: spill mode
       int per = 0;
-      NB_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, adjoint_kernel(sh.bpt, sh.bs), sh.bs, 0));
+      const int rc = blocks_per_cu(adjoint_kernel(sh.bpt, sh.bs), sh.bs, 0, &per);
+      if (rc) return rc;
       if (i == 4 && per < 1) return fail(NB_EHIP, "adjoint kernel cannot be resident");
       int blocks = std::min(sh.bs == kBlockSmall ? cus * std::min(per, 1) : cus * per, kAdjMaxBlocks);
       if (m->p.max_blocks > 0) blocks = std::min(blocks, (int)m->p.max_blocks);

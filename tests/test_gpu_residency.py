@@ -1,0 +1,41 @@
+"""Grids of the full resident capacity at table sizes where a block's LDS, rounded up to the units it
+is given out in, decides how many blocks a CU holds: every block of the launch is resident
+(the grid barriers complete), and the bits are those of a grid of one block per CU."""
+import numpy as np
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def nb():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no HIP device visible")
+    import paper_1912_10596_amd as nb
+    nb.lib()
+    return nb
+
+
+# more rows than two 256-thread blocks per CU have wavefronts (2048), so that a third block per
+# CU is launched wherever one counts as resident
+CASES = [("2f", dict(n_flavor=2, n_energy=ne, n_u=1100)) for ne in (1063, 1070, 1089, 1090, 1943, 1944)] + \
+        [("2f-all", dict(n_flavor=2, n_energy=ne, n_u=550, track_all=1)) for ne in (709, 715, 727)] + \
+        [("2f-ext", dict(n_flavor=2, n_energy=ne, n_u=120, n_phi=10)) for ne in (248, 260, 276)] + \
+        [("2f-ext-all", dict(n_flavor=2, n_energy=ne, n_u=60, n_phi=10, track_all=1)) for ne in (175,)]
+
+
+@pytest.mark.parametrize("name,kw", CASES, ids=[f"{c[0]}-{c[1]['n_energy']}" for c in CASES])
+def test_full_grids_are_resident(nb, name, kw):
+    d = workloads.small_params(n_steps=2, **kw)
+    m = nb.Model(d)
+    got = {}
+    for blocks in (0, 256):
+        m.set_tuning(256, blocks)
+        print(f"{name} {kw['n_energy']} energies: {m.get_tuning()['blocks']} blocks of 256", flush=True)
+        m.reset()
+        m.run()
+        got[blocks] = m.get_state().cpu().numpy()
+    np.testing.assert_array_equal(got[0], got[256])
