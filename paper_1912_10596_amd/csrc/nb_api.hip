@@ -154,6 +154,7 @@ struct nb_model {
   hipStream_t stream = nullptr;
   int device = 0, cus = 0, nblocks = 0;
   int cap512 = 0, cap256 = 0;        // resident blocks of the fixed-step kernels at 512 / 256 threads
+  bool lds512 = true, lds256 = true; // the fixed-step kernels of that size may stage the energy tables in LDS
   int bs_adaptive = kBlock, cap_adaptive = 0;  // threads per block and resident blocks of the adaptive kernel
   unsigned* cancel = nullptr;        // this model's cancel word (fine-grained host memory)
   const unsigned* cancel_dev = nullptr;  // its device address
@@ -569,13 +570,17 @@ static Layout layout_of(const nb_model* m) {
 
 extern "C" size_t nb_workspace_bytes(const nb_model* m) { return m ? layout_of(m).need : 0; }
 
-// Energy tables are staged in LDS when they fit in this many bytes per block (the
-// stepping kernels' static LDS is about 50 KB; a CU holds 160 KB and runs one block).
+// Energy tables are staged in LDS when they fit in this many bytes per block and a block of
+// the kernel that stages them fits a CU's 160 KB beside its own arrays (11-38 KB; extended
+// two-flavour stepper 46 KB at 256 threads and 89 KB at 512, so that tables above 75 KB, for
+// instance 2360 energies, stay in memory at 512): nb_bind asks for each block size.
 static constexpr size_t kTabLdsMax = 96 * 1024;
 
 static size_t tab_bytes(const nb_model* m) { return sizeof(double) * m->tab.size(); }
 static bool tab_in_lds(const nb_model* m) { return !m->batch && tab_bytes(m) <= kTabLdsMax; }
-static size_t advance_dyn_lds(const nb_model* m) { return tab_in_lds(m) ? tab_bytes(m) : 0; }
+static bool tab_in_lds(const nb_model* m, int bs) { return tab_in_lds(m) && (bs == kBlockSmall ? m->lds256 : m->lds512); }
+static size_t advance_dyn_lds(const nb_model* m, int bs) { return tab_in_lds(m, bs) ? tab_bytes(m) : 0; }
+static size_t adaptive_dyn_lds(const nb_model* m) { return tab_in_lds(m) ? tab_bytes(m) : 0; }
 // The FP32-arithmetic kernel stages the table and, from the next 16-byte boundary, an FP32
 // copy of the vacuum rows and e_k (eight floats per energy) when both fit in this many
 // bytes (with its static LDS, below the 160 KB of a CU).
@@ -635,14 +640,14 @@ static bool packed_tails(const nb_model* m, int nblocks) {
          (ne % 64) <= 32;
 }
 static const void* packed_kernel(const nb_model* m) {
-  return tab_in_lds(m) ? (const void*)&k_advance<3, double, true, false, false, kBlock, true>
-                       : (const void*)&k_advance<3, double, false, false, false, kBlock, true>;
+  return tab_in_lds(m, kBlock) ? (const void*)&k_advance<3, double, true, false, false, kBlock, true>
+                               : (const void*)&k_advance<3, double, false, false, false, kBlock, true>;
 }
 // The fixed-step kernel of a model at bs threads per block (512 or 256).
 template <int BS>
 static const void* advance_kernel_bs(const nb_model* m) {
   if (m->batch) return (const void*)&k_batch2<BS>;
-  const bool l = tab_in_lds(m);
+  const bool l = tab_in_lds(m, BS);
   if (m->nf == 2)
     return m->p.n_phi > 0
                ? (l ? (const void*)&k_advance<2, double, true, false, true, BS, false> : (const void*)&k_advance<2, double, false, false, true, BS, false>)
@@ -796,11 +801,11 @@ static int blocks_per_cu(const void* fn, int bs, size_t dyn, int* per) {
 // at most kMaxBlocks and p.max_blocks; 0 if one of them cannot be resident at that size.
 static int fixed_step_capacity(const nb_model* m, int cus, int bs, int* out) {
   int per = 0;
-  int rc = blocks_per_cu(advance_kernel(m, bs), bs, advance_dyn_lds(m), &per);
+  int rc = blocks_per_cu(advance_kernel(m, bs), bs, advance_dyn_lds(m, bs), &per);
   if (rc) return rc;
   if (bs == kBlock && !m->batch && m->nf == 3 && !state_fp32(m) && m->p.n_phi == 0) {
     int ppk = 0;   // the packed-tail variant may take any of these launches
-    if ((rc = blocks_per_cu(packed_kernel(m), bs, advance_dyn_lds(m), &ppk))) return rc;
+    if ((rc = blocks_per_cu(packed_kernel(m), bs, advance_dyn_lds(m, bs), &ppk))) return rc;
     per = std::min(per, ppk);
   }
   if (advance_kernel_f32(m, bs)) {
@@ -824,14 +829,21 @@ extern "C" int nb_bind(nb_model* m, void* dev_ws, size_t bytes, void* hip_stream
   NB_HIP(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev));
   int cap[2] = {0, 0}, cap_adaptive = 0;
   for (int i = 0; i < 2; ++i) {
-    int rc = fixed_step_capacity(m, cus, i == 0 ? kBlock : kBlockSmall, &cap[i]);
+    const int bs = i == 0 ? kBlock : kBlockSmall;
+    bool& lds = i == 0 ? m->lds512 : m->lds256;
+    lds = true;
+    int rc = fixed_step_capacity(m, cus, bs, &cap[i]);
+    if (!rc && cap[i] < 1 && tab_in_lds(m, bs)) {   // not beside the kernel's own arrays
+      lds = false;
+      rc = fixed_step_capacity(m, cus, bs, &cap[i]);
+    }
     if (rc) return rc;
   }
   if (cap[0] < 1) return fail(NB_EHIP, "stepping kernel cannot be resident");
   const int abs_ = adaptive_block(m, cus);
   if (adaptive_kernel(m, abs_)) {
     int nba = 0;
-    const int rc = blocks_per_cu(adaptive_kernel(m, abs_), abs_, advance_dyn_lds(m), &nba);
+    const int rc = blocks_per_cu(adaptive_kernel(m, abs_), abs_, adaptive_dyn_lds(m), &nba);
     if (rc) return rc;
     if (nba < 1) return fail(NB_EHIP, "adaptive kernel cannot be resident");
     cap_adaptive = std::min(cus * nba, kMaxBlocks);
@@ -1068,7 +1080,7 @@ static int enqueue_advance(nb_model* m, long long k, bool report) {
   };
   if (!advance_kernel_f32(m, m->bs)) {
     a.host = report ? m->pinned : nullptr;
-    return launch(advance_kernel(m, m->bs), advance_dyn_lds(m));
+    return launch(advance_kernel(m, m->bs), advance_dyn_lds(m, m->bs));
   }
   // Mixed precision: FP64-arithmetic steps before fp32_from, FP32-arithmetic steps after,
   // as two windowed launches sharing one target of k steps from the device counter.
@@ -1081,7 +1093,7 @@ static int enqueue_advance(nb_model* m, long long k, bool report) {
   a.use_window = 1;
   a.win_lo = 0;
   a.win_hi = s.fp32_from;
-  int rc = launch(advance_kernel(m, m->bs), advance_dyn_lds(m));
+  int rc = launch(advance_kernel(m, m->bs), advance_dyn_lds(m, m->bs));
   if (rc) return rc;
   a.host = report ? m->pinned : nullptr;   // the second launch's status covers both
   a.win_lo = s.fp32_from;
@@ -1238,7 +1250,7 @@ extern "C" int nb_run_adaptive(nb_model* m, double tol, double h_max_km, int64_t
   const int bs = m->bs_adaptive, wpb = bs / 64;
   const int ablocks = (int)std::max<long long>(1, std::min<long long>((m->rows + wpb - 1) / wpb, m->cap_adaptive));
   const hipError_t e =
-      hipLaunchKernel(adaptive_kernel(m, bs), dim3(ablocks), dim3(bs), args, advance_dyn_lds(m), m->stream);
+      hipLaunchKernel(adaptive_kernel(m, bs), dim3(ablocks), dim3(bs), args, adaptive_dyn_lds(m), m->stream);
   if (e != hipSuccess) return fail(NB_EHIP, "adaptive launch: %s", hipGetErrorString(e));
   long long out[8];
   NB_HIP(hipMemcpyAsync(out, ctl, sizeof(out), hipMemcpyDeviceToHost, m->stream));
