@@ -39,3 +39,29 @@ def test_full_grids_are_resident(nb, name, kw):
         m.run()
         got[blocks] = m.get_state().cpu().numpy()
     np.testing.assert_array_equal(got[0], got[256])
+
+
+# rows of their own wavefronts: grids bounded by LDS (one block per CU at either size) or by
+# max_blocks hold more at 512 threads; others keep 256
+BLOCKS = [(dict(n_flavor=2, n_energy=1943, n_u=600), 256), (dict(n_flavor=2, n_energy=1944, n_u=512), 256),
+          (dict(n_flavor=2, n_energy=1944, n_u=513), 512), (dict(n_flavor=2, n_energy=1350, n_u=300, track_all=1), 512),
+          (dict(n_flavor=2, n_energy=1200, n_u=60, n_phi=9), 512),
+          (dict(n_flavor=2, n_energy=20, n_u=40, max_blocks=20), 256),
+          (dict(n_flavor=2, n_energy=20, n_u=41, max_blocks=20), 512),
+          (dict(n_flavor=3, n_energy=20, n_u=40, max_blocks=20), 256),
+          (dict(n_flavor=3, n_energy=20, n_u=41, max_blocks=20), 512),
+          (dict(n_flavor=3, n_energy=20, n_u=512), 256), (dict(n_flavor=3, n_energy=20, n_u=513), 512)]
+
+
+@pytest.mark.parametrize("kw,bs", BLOCKS, ids=["-".join(f"{k}{v}" for k, v in c[0].items()) for c in BLOCKS])
+def test_default_block_size(nb, kw, bs):
+    d = workloads.small_params(n_steps=2, **kw)
+    m = nb.Model(d)
+    print(kw, m.get_tuning(), flush=True)
+    assert m.get_tuning()["block_threads"] == bs
+    m.run()
+    want = m.get_state().cpu().numpy()
+    m.set_tuning(768 - bs)
+    m.reset()
+    m.run()
+    np.testing.assert_array_equal(m.get_state().cpu().numpy(), want)
