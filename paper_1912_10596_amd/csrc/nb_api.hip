@@ -602,7 +602,7 @@ static const void* adaptive_kernel(const nb_model* m, int bs) {
   if (m->batch || !m->p.adaptive) return nullptr;
   return bs == kBlockSmall ? adaptive_kernel_bs<kBlockSmall>(m) : adaptive_kernel_bs<kBlock>(m);
 }
-// Threads per block of a three-flavour launch (and of adaptive runs) on a device of cus CUs:
+// Threads per block of a three-flavour launch on a device of cus CUs:
 //  * up to 8 rows: 512, one block, which exchanges nothing with others (32 x 4 bins: 14.4 us
 //    per step, two blocks of 256 threads 18);
 //  * up to four rows per CU: 256, so that every wavefront has a SIMD to itself instead of
@@ -622,13 +622,6 @@ static int pick_block(bool prefer256, long long rows, int cap512, int cap256) {
   const auto waves = [&](int bs, int cap) { return std::min<long long>(rows, (long long)cap * (bs / 64)); };
   return prefer256 && waves(kBlockSmall, cap256) >= waves(kBlock, cap512) ? kBlockSmall : kBlock;
 }
-// Adaptive runs of two flavours with more rows than one per SIMD stay at 256 threads (as the
-// fixed steps' default).
-static int adaptive_block(const nb_model* m, int cus) {
-  if (m->nf == 2 && m->rows > kBlock / 64) return kBlockSmall;
-  return block_of_rows(m->rows, cus);
-}
-
 // The reverse kernel at bpt beams per thread (-1: spill mode) and bs threads per block.
 static const void* adjoint_kernel(int bpt, int bs) {
   if (bs == kBlockSmall) return (const void*)&k_adjoint2<1, kBlockSmall>;
@@ -849,14 +842,27 @@ extern "C" int nb_bind(nb_model* m, void* dev_ws, size_t bytes, void* hip_stream
     if (rc) return rc;
   }
   if (cap[0] < 1) return fail(NB_EHIP, "stepping kernel cannot be resident");
-  const int abs_ = adaptive_block(m, cus);
-  if (adaptive_kernel(m, abs_)) {
-    int nba = 0;
-    const int rc = blocks_per_cu(adaptive_kernel(m, abs_), abs_, adaptive_dyn_lds(m), &nba);
-    if (rc) return rc;
-    if (nba < 1) return fail(NB_EHIP, "adaptive kernel cannot be resident");
-    cap_adaptive = std::min(cus * nba, kMaxBlocks);
-    if (m->p.max_blocks > 0) cap_adaptive = std::min(cap_adaptive, (int)m->p.max_blocks);
+  // Adaptive runs: as the fixed steps, but up to 8 rows in one block of 512 threads at two
+  // flavours too.  Two flavours, ms per run at 256 and 512 threads: 100 x 12 bins 1.67 and 1.97,
+  // 100 x 300 1.97 and 2.15, 100 x 1100 2.62 and 3.08, 1900 x 1500 1.88 and 2.35; even or up to 5 %
+  // slower at 256 between 4 and 8 rows per CU (100 x 600 2.34 and 2.32, 37 x 1024 1.17 and
+  // 1.11).  With one block per CU or max_blocks (pick_block): 2500 x 600 3.06 and 2.23,
+  // 200 x 400 in 64 blocks 1.84 and 1.34.
+  int abs_ = kBlock;
+  if (adaptive_kernel(m, kBlock)) {
+    int capa[2] = {0, 0};
+    for (int i = 0; i < 2; ++i) {
+      const int bs = i == 0 ? kBlock : kBlockSmall;
+      int nba = 0;
+      const int rc = blocks_per_cu(adaptive_kernel(m, bs), bs, adaptive_dyn_lds(m), &nba);
+      if (rc) return rc;
+      capa[i] = std::min(cus * nba, kMaxBlocks);
+      if (m->p.max_blocks > 0) capa[i] = std::min(capa[i], (int)m->p.max_blocks);
+    }
+    abs_ = pick_block(m->rows > kBlock / 64 && (m->nf == 2 || block_of_rows(m->rows, cus) == kBlockSmall), m->rows,
+                      capa[0], capa[1]);
+    cap_adaptive = capa[abs_ == kBlock ? 0 : 1];
+    if (cap_adaptive < 1) return fail(NB_EHIP, "adaptive kernel cannot be resident");
   }
   const Layout L = layout_of(m);
   if (bytes < L.need)

@@ -65,3 +65,17 @@ def test_default_block_size(nb, kw, bs):
     m.reset()
     m.run()
     np.testing.assert_array_equal(m.get_state().cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("kw", [dict(n_flavor=2, n_energy=1945, n_u=520), dict(n_flavor=2, n_energy=40, n_u=30, max_blocks=9),
+                                dict(n_flavor=3, n_energy=40, n_u=30, max_blocks=9)],
+                         ids=["lds", "2f-max_blocks", "3f-max_blocks"])
+def test_adaptive_runs_in_bounded_grids(nb, oracle, kw):
+    """Adaptive runs where the block size follows from the bound on the grid."""
+    d = workloads.small_params(n_steps=4, r_start_km=600.0, r_end_km=600.2, **kw)
+    o = oracle.Model(d)
+    so = o.run_adaptive(1e-7)
+    m = nb.Model(d, adaptive=True)
+    st = m.run_adaptive(1e-7)
+    assert (st["accepted"], st["rejected"]) == (so["accepted"], so["rejected"])
+    np.testing.assert_array_equal(m.get_state().cpu().numpy(), o.get_state())
