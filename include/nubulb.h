@@ -139,7 +139,7 @@ int64_t nb_step_index(const nb_model *m);
  * under graph capture, tight serving loops, harnesses that forbid allocation): nb_step
  * with the scratch of the stepping launches -- the barrier and reduction words and,
  * for batches, the moment accumulators -- taken from a static device array of the library
- * instead of the bound workspace (2.2 MB per device, held until the process ends).  Same
+ * instead of the bound workspace (1.8 MB per device, held until the process ends).  Same
  * kernels and the same bits as nb_step; the model's state, tables and step counter stay
  * in its workspace.  Allocates nothing.  Limits: at most 1024 models in a batch and 2048
  * blocks per launch (every launch shape nb_bind picks fits), NB_EINVAL beyond.  Every call

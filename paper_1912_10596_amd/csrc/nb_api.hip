@@ -1147,14 +1147,15 @@ extern "C" int nb_run(nb_model* m) {
 }
 
 // ------------------------------------------------- static scratch: stepping without allocation
-// nb_step_static takes the scratch of the stepping launches -- the barrier and tagged
-// reduction words (kSyncWords 32-bit words, enough for the largest grid of kMaxBlocks
-// blocks) and the batch kernel's moment accumulators (kStaticModels models) -- from this
-// array instead of the workspace.  Each device holds its own copy until the process ends.
+// nb_step_static takes the scratch of the stepping launches -- the barrier and reduction
+// words (kSyncWords 32-bit words, enough for the largest grid of kMaxBlocks blocks) and the
+// batch kernel's moment accumulators (kStaticModels models) -- from this array instead of
+// the workspace.  Each device holds its own copy until the process ends.
 constexpr int kStaticModels = 1024;
 constexpr size_t kStaticSync64 = ((size_t)kSyncWords + 1) / 2;         // sync words, as u64
 constexpr size_t kStaticAccOff = (kStaticSync64 + 31) / 32 * 32;       // 256-byte boundary
 constexpr size_t kStaticWords = kStaticAccOff + (size_t)kAccPerModel * kStaticModels;
+static_assert(kStaticWords * 8 / 100000 == 17, "nubulb.h says about 1.8 MB (1759744 bytes)");
 static __device__ __align__(256) unsigned long long scratch[kStaticWords];
 
 // Device address of this device's copy of scratch, looked up once per device with that

@@ -38,12 +38,12 @@ constexpr int kSyncStepEnd = kSyncStepPub + kRedCopies * kLineWords;
 // to): in two regions (even, odd epochs) the sums of the 8 dies, kTagLines lines each, then
 // one slot of kTagLines lines of partials per block.
 constexpr int kTagLines = 4;
-constexpr int kSyncJTag = kSyncStepEnd;
-constexpr int kSyncPart = kSyncJTag + 2 * 8 * kTagLines * kLineWords;
-constexpr int kSyncWords = kSyncPart + kMaxBlocks * kTagLines * kLineWords;
-constexpr int kTagWords64 = kTagLines * kLineWords / 2;   // 64-bit words per copy or slot
 constexpr int kAdjDieBlocks = 64;                         // most adjoint blocks of one die
 constexpr int kAdjMaxBlocks = 8 * kAdjDieBlocks;
+constexpr int kSyncJTag = kSyncStepEnd;
+constexpr int kSyncPart = kSyncJTag + 2 * 8 * kTagLines * kLineWords;
+constexpr int kSyncWords = kSyncPart + kAdjMaxBlocks * kTagLines * kLineWords;
+constexpr int kTagWords64 = kTagLines * kLineWords / 2;   // 64-bit words per copy or slot
 
 constexpr int kVacRows3 = 7;    // 3f table rows before the weights: 6 vacuum entries and e_k
 constexpr int kBlock = 512;       // threads per block: the most a stepping launch uses (8 waves),
