@@ -271,7 +271,8 @@ __device__ __forceinline__ void b_bar(AdjBeam& q, const double* Bb, double c, co
 // Broadcast of a moment adjoint (J0-bar | J1-bar) onto a stage state y at cos c:
 // y-bar = g S (J0-bar/c + J1-bar); the weight adjoint (S y).(J0-bar/c + J1-bar) feeds the
 // luminosity gradients.  Far out the two terms nearly cancel, so J0-bar/c is divided exactly
-// (a factor 1/c doubles the gradients' error), its three quotients from one reciprocal.
+// (a factor 1/c doubles the gradients' error), its three quotients from one reciprocal (0 < c <= 1;
+// below 2^-960, moment adjoints of cotangents that small, they are within two ulp).
 __device__ __forceinline__ void m_bar(AdjBeam& q, const double* Jb, double c, const double* y, double* yb) {
   const double sg = q.s ? -1.0 : 1.0;
   const double r = rcp_step(c, rcp_step(c, __builtin_amdgcn_rcp(c)));
@@ -519,10 +520,12 @@ __device__ __forceinline__ void adj_store(const AdjArgs& a, const AdjBeam& B, lo
   }
 }
 
-// BPT > 0: thread gt owns beams gt + i nthr (i < BPT) and keeps their adjoint registers for
-// the whole launch.  BPT = 0 (spill mode, any number of beams): each phase loops over the
+// BPT > 0: thread gt owns beams gt + i nthr (i < BPT) and keeps their adjoint state in its
+// registers, or what the compiler spills of it (at 256 VGPRs 104 bytes of scratch per lane for
+// two beams, 768 for four; none for one), for the whole launch.  BPT = 0 (spill mode, any number of beams): each phase loops over the
 // thread's beams gt, gt + nthr, ..., reading and writing their adjoint registers in the
-// workspace and recomputing the state and geometry from the tape.
+// workspace and recomputing the state and geometry from the tape.  Reverse pass of 24 steps, four beams
+// per thread against spill mode: 300k beams 1.62 and 1.38 ms, 400k 1.76 and 1.83, 520k 1.92 and 2.13.
 // Bound: VALU issue and the latency of a phase's chain (one rotation with its Jacobian) plus
 // the grid sums.  Between the publication of a step's last sum and the poll for it every
 // thread loads its next step's states and computes that step's geometry (one radius of three:

@@ -104,8 +104,8 @@ __device__ __forceinline__ void sincos_tab(double x, const double* c, double& sn
 
 // ------------------------------------------------- square root and division in range
 // The steps of the IEEE correctly rounded operations without their scaling and special
-// cases, for operands whose exponents leave room (each caller says why they do): the same
-// results with about a third fewer instructions.
+// cases, for operands whose exponents leave room: the same results with about a third fewer
+// instructions.
 // sqrt(x), 2^-767 <= x < 2^1022: rsq refined by Goldschmidt steps.  h is left at
 // 1 / (2 sqrt(x)) to about 2^-50.
 __device__ __forceinline__ double sqrt_in_range(double x, double& h) {
@@ -118,8 +118,12 @@ __device__ __forceinline__ double sqrt_in_range(double x, double& h) {
   g = fma(fma(-g, g, x), h, g);
   return fma(fma(-g, g, x), h, g);
 }
-// a / b from r = 1/b to rounding: the quotient's residual is exact, so its correction rounds
-// correctly.  2^-500 <= |b| <= 2^500, and a zero or as large (a = -0 gives +0).
+// a / b from r = 1/b to rounding: the quotient's residual a - b q is exact, so its correction
+// rounds correctly.  1/b and a/b normal, and a zero (-0 gives +0) or |a| >= 2^-960: b q has 106
+// bits, so the residual's last bit is then above 2^-1074.  Of a smaller a the residual rounds,
+// and the quotient is within two ulp (or the smallest subnormals, as any product's).  Where the
+// callers' operands lie: div_by_sqrt, exp3_apply; the adjoint's m_bar takes the caller's
+// cotangents as they come.
 __device__ __forceinline__ double div_by_rcp(double a, double b, double r) {
   const double q = a * r;
   return fma(fma(-b, q, a), r, q);
@@ -128,8 +132,10 @@ __device__ __forceinline__ double rcp_step(double b, double r) { return fma(r, f
 __device__ __forceinline__ double div_in_range(double a, double b) {
   return div_by_rcp(a, b, rcp_step(b, rcp_step(b, __builtin_amdgcn_rcp(b))));
 }
-// a / g with g = sqrt(x) of any x > 0 (so 2^-537 <= g) and h = 1 / (2 g) to about 2^-50, as
-// sqrt_in_range leaves it: one step from 2 h takes the place of a reciprocal and two.
+// a / g with g = sqrt(x) of any x > 0 (so 2^-537 <= g <= 2^512) and h = 1 / (2 g) to about 2^-50,
+// as sqrt_in_range leaves it: one step from 2 h takes the place of a reciprocal and two.  The
+// callers' a are the sine of g or g/2 (zero, or above 2^-540: that of a small angle is the angle,
+// and no double below 2^50 lies closer than about 2^-60 to a multiple of pi) and a step length.
 __device__ __forceinline__ double div_by_sqrt(double a, double g, double h) {
   return div_by_rcp(a, g, rcp_step(g, h + h));
 }

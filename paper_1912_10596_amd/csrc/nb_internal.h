@@ -132,8 +132,9 @@ struct BatchArgs {
 };
 
 // Arguments of the two-flavour reverse (adjoint) kernel.  Beam b belongs to thread
-// b mod (grid threads); its adjoint state stays in registers for the whole launch, or, when
-// the beams outnumber four per resident thread, in the workspace (spill).
+// b mod (grid threads); its adjoint state stays with the thread for the whole launch (registers, and
+// scratch for what does not fit them), or, when the beams outnumber four per resident
+// thread, in the workspace (spill).
 struct AdjArgs {
   const double* tab;       // [bx|bz|G0|G1] x NE
   const double* dtab;      // [dG0/dL_e | dG1/dL_ebar | dG/dL_x | dbx/dtheta | dbz/dtheta] x NE

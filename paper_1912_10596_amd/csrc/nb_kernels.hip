@@ -8,8 +8,8 @@
 //      stage storage: F_1..F_{i-1} are recomputed from J^(1..i-1)),
 //   3. applies the exact exponential to get the stage state Y_i (Eq. U),
 //   4. accumulates the beam's moment contribution as a 64-bit fixed-point integer; the
-//      row's energy sum is a wavefront butterfly of 128-bit integers, then the angle sum
-//      (1/cos weighting for J0) is added to per-lane totals,
+//      lanes' sums fold to the row's exact energy sum (wave_fold), then the angle sum (1/cos
+//      weighting for J0) is added to per-lane 128-bit totals,
 // then the block folds its waves through LDS and adds its partial to counted accumulators,
 // whose published totals every block reads as J^(i) (agent-scope atomics).
 // Four barriers per step; the final pass writes rho_{n+1} and also produces the next
@@ -629,8 +629,9 @@ __device__ __forceinline__ void group2(double* X, long long plane, long long gb0
   const int irow = 64 / NE, krow = 64 - irow * NE;   // a chunk further: irow rows, krow energies
   // a plane's base is uniform and the group's byte offsets fit 32 bits (at most kGroup rows of
   // kGroupMaxNE energies): one offset register serves all planes, and the next beam is found
-  // without a loop over lanes (256-model batch 2.92 -> 2.75 ms per step, extended 20M beams
-  // 858 -> 843 us, against 64-bit addresses and a loop that stepped k row by row)
+  // without a loop over lanes (passes of 4 steps with the state set and read back, with the
+  // sin/cos constants from scalar registers in both: 256-model batch 11.55 -> 11.02 ms, extended
+  // 20M beams 3.44 -> 3.36 ms, against 64-bit addresses and a loop that stepped k row by row)
   char *X0 = reinterpret_cast<char*>(X + gb0), *X1 = reinterpret_cast<char*>(X + gb0 + plane),
        *X2 = reinterpret_cast<char*>(X + gb0 + 2 * plane);
   const auto at = [](char* base, unsigned off) -> double& { return *reinterpret_cast<double*>(base + off); };
@@ -815,9 +816,10 @@ __device__ __forceinline__ void prep2(const StepArgs& a, const StepGeo& G, int l
 // Every other stage of the extended model takes a wavefront's row groups in reverse order, so that
 // it begins with the beams the stage before it touched last: of a state beyond the 256 MB
 // last-level cache the part that is still there is read from it, where a sweep in the same
-// direction each time finds none (20M beams, 480 MB: 865 -> 843 us per step; the 256-model
-// batch, 1.5 GB, gains nothing, 2.78 against 2.80 ms, so its sweeps keep one direction).  The
-// moments are integer sums, so the order does not change their bits.
+// direction each time finds none (passes of 4 steps with the state set and read back: 20M beams,
+// 480 MB, 3.46 -> 3.37 ms; the 256-model batch, 1.5 GB, gains nothing, 11.14 against 11.18 ms, so
+// its sweeps keep one direction).  The moments are integer sums, so the order does not change
+// their bits.
 __device__ constexpr bool backwards(int kind) { return (kind & 1) == 0; }
 
 template <int KIND, bool ADAPT = false, bool EXT = false>
@@ -2039,7 +2041,7 @@ __device__ __forceinline__ bool batch_stage(const BatchArgs& a, long long n, uns
   return true;
 }
 
-// Four wavefronts per SIMD (128 VGPRs; the row groups' set-up spills about 200 bytes per
+// Four wavefronts per SIMD (128 VGPRs; the row groups' set-up spills, 264 bytes of scratch per
 // lane, outside the chunk loop): the rows of a batch are short (50-400 energies), so a wave
 // spends much of its time on row set-up and the first load of each row, which more
 // wavefronts hide.  Measured on the 256-model batch before the chunks were streamed across
