@@ -630,8 +630,8 @@ __device__ __forceinline__ void group2(double* X, long long plane, long long gb0
   // a plane's base is uniform and the group's byte offsets fit 32 bits (at most kGroup rows of
   // kGroupMaxNE energies): one offset register serves all planes, and the next beam is found
   // without a loop over lanes (passes of 4 steps with the state set and read back, with the
-  // sin/cos constants from scalar registers in both: 256-model batch 11.55 -> 11.02 ms, extended
-  // 20M beams 3.44 -> 3.36 ms, against 64-bit addresses and a loop that stepped k row by row)
+  // sin/cos constants from scalar registers in both: 256-model batch 11.7 -> 11.0 ms, extended
+  // 20M beams 3.43 -> 3.37 ms, against 64-bit addresses and a loop that stepped k row by row)
   char *X0 = reinterpret_cast<char*>(X + gb0), *X1 = reinterpret_cast<char*>(X + gb0 + plane),
        *X2 = reinterpret_cast<char*>(X + gb0 + 2 * plane);
   const auto at = [](char* base, unsigned off) -> double& { return *reinterpret_cast<double*>(base + off); };
