@@ -12,7 +12,6 @@ constexpr int kMaxBlocks = 2048;  // upper bound on blocks of one stepping launc
 // block writes or polls sits on a 128-byte line of its own or in one of the reduction
 // regions below.
 constexpr int kLineWords = 32;
-constexpr int kSyncGo = 0;                   // stepping launches: 1 they go on, 2 the host had cancelled the model
 constexpr int kSyncAbort = 1 * kLineWords;   // set when any block gives up waiting
 constexpr int kSyncStatus = 2 * kLineWords;  // bit 0: fixed-point range error, bit 1: barrier timeout,
                                              // bit 2: cancelled by the host, bit 3: renormalisation

@@ -1522,7 +1522,7 @@ k_advance(StepArgs a) {
   const long long nw = (long long)gridDim.x * WPB;
   const double* tab = a.tab;
   const float* ftab = nullptr;
-  if (launch_aborted(a.sync)) return;
+  if (launch_aborted(a.sync, a.cancel)) return;
   red_init(R);
   if (NF == 2 && threadIdx.x == 0) sincos_coefs(s_sct);
   __syncthreads();
@@ -1556,7 +1556,6 @@ k_advance(StepArgs a) {
     if (a.host && blockIdx.x == 0 && threadIdx.x == 0) put_host(a.host, a.sync, step0);
     return;
   }
-  const unsigned seen = cancel_seen(a.cancel);
   unsigned epoch = 0;
   int err = 0;
   bool ok = true;
@@ -1599,9 +1598,8 @@ k_advance(StepArgs a) {
     if constexpr (NF == 3 && !F32) prefetch_first<6>(a, (const ST*)a.X, gw, nrow3, lane, pre);
     if constexpr (NF == 2 && !EXT) prefetch_first<3>(a, (const ST*)a.X, gw, nrow3, lane, pre);
     if (threadIdx.x < NV) sJ[0][threadIdx.x] = as_double((unsigned long long)a.step_ctl[kCtlMom + threadIdx.x]);
-    if (!launch_goes(a.sync, a.cancel, seen, a.timeout_ticks)) return;
+    __syncthreads();
   } else {
-    if (!launch_goes(a.sync, a.cancel, seen, a.timeout_ticks)) return;
     if constexpr (NF == 2) { stage2<0, false, EXT>(a, a.h, (const double*)a.X, (double*)a.X, sJ, tab, gw, nw, nrw, lane, fl, T, err, enone, snn, s_sct, rt); if (!EXT) prefetch_first<3>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
     else if constexpr (F32) stage3m<0, TLDS>(a, sJ, tab, ftab, snn, kr, sfv, gw, nw, nrw, lane, T, err);
     else { stage3<ST, 0, false, EXT>(a, a.h, (const ST*)a.X, (ST*)a.X, sJ, tab, snn, kr, sfv, gw, nw, nrw, lane, T, err, enone); prefetch_first<6>(a, (const ST*)a.X, gw, nrow3, lane, pre); }
@@ -1651,7 +1649,6 @@ k_advance(StepArgs a) {
     for (int i = threadIdx.x; i < kSyncRedEnd - kSyncRed; i += BS) a.sync[kSyncRed + i] = 0u;
     if (threadIdx.x == 0) {
       a.sync[kSyncDone] = 0u;
-      a.sync[kSyncGo] = 0u;
       a.step_ctl[0] = step0 + nsteps;
       a.step_ctl[kCtlMTag] = step0 + nsteps;
       a.step_ctl[kCtlMKind] = kind;

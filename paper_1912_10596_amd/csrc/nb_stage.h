@@ -53,49 +53,27 @@ __device__ __forceinline__ bool give_up(unsigned* sync, const unsigned* cancel, 
 // Read at the start of a persistent launch (all threads of the block call this; thread 0
 // reads, the block shares its answer): the abort word, set before the launch by the
 // sync-word clear when the host had cancelled the model (every block then returns at once,
-// leaving the state as it was), or during it by a block that gave up.
-__device__ __forceinline__ bool launch_aborted(const unsigned* sync) {
-  return __syncthreads_or(threadIdx.x == 0 &&
-                          __hip_atomic_load(sync + kSyncAbort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u);
-}
-// Launches that no clear precedes read the host's cancel word themselves: block 0, at its start
-// (cancel_seen), for all blocks, which after their set-up wait for its answer in the go word
-// (launch_goes; all threads of the block call this, and it is a block barrier).  A cancelled launch
-// so ends before a beam is touched, and the trip to the host hides behind the set-up.  (One
-// word read by every block: 0.1 us a block, 73 us at 768 blocks.)
-__device__ __forceinline__ unsigned cancel_seen(const unsigned* cancel) {
-  return (cancel && blockIdx.x == 0 && threadIdx.x == 0)
-             ? __hip_atomic_load(cancel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) : 0u;
-}
-__device__ __forceinline__ bool launch_goes(unsigned* sync, const unsigned* cancel, unsigned seen,
-                                            unsigned long long timeout_ticks) {
-  int ok = 1;
+// leaving the state as it was), or during it by a block that gave up.  cancel (launches that
+// may start without such a clear, on a stream that was idle when the host found the model not
+// cancelled): block 0 also reads the host's cancel word; if it was set since, that block
+// sets the abort word and status bit 2 and returns, and the others find the abort word at
+// their first wait, before any state is stored.  (Every block reading the host's word costs
+// 0.1 us a block; a go word from block 0 for which the others wait, 2.5 us of a pass of one
+// step with the state set and read back, 76 us, and 1-2 % of small models' steps by the registers
+// that it takes.)
+__device__ __forceinline__ bool launch_aborted(unsigned* sync, const unsigned* cancel = nullptr) {
+  int ab = 0;
   if (threadIdx.x == 0) {
-    if (blockIdx.x == 0) {
-      if (seen) {
-        __hip_atomic_store(sync + kSyncAbort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_or(sync + kSyncStatus, 4u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        ok = 0;
-      }
-      if (gridDim.x > 1)
-        __hip_atomic_store(sync + kSyncGo, seen ? 2u : 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-      const unsigned long long t0 = wall_clock64();
-      for (unsigned it = 1;; ++it) {
-        const unsigned go = __hip_atomic_load(sync + kSyncGo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (go) {
-          ok = go == 1u;
-          break;
-        }
-        if ((it & 31u) == 0u && give_up(sync, cancel, t0, timeout_ticks, it)) {
-          ok = 0;
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-      }
+    const unsigned c = (cancel && blockIdx.x == 0)
+                           ? __hip_atomic_load(cancel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) : 0u;
+    ab = __hip_atomic_load(sync + kSyncAbort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
+    if (c && !ab) {
+      __hip_atomic_store(sync + kSyncAbort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_fetch_or(sync + kSyncStatus, 4u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      ab = 1;
     }
   }
-  return __syncthreads_and(ok);
+  return __syncthreads_or(ab);
 }
 // The status word and the step counter into pinned host memory.
 __device__ __forceinline__ void put_host(long long* host, const unsigned* sync, long long step) {
