@@ -786,6 +786,25 @@ static int upload_partition(nb_model* m) {
   return NB_OK;
 }
 
+// Bytes of LDS that the arrays of kernel fn take, asked for once per kernel (a query takes
+// microseconds, and every graph launch checks its grid).
+static int static_lds(const void* fn, size_t* out) {
+  static std::mutex mu;
+  static struct { const void* fn; size_t bytes; } known[64];
+  static int n = 0;
+  std::lock_guard<std::mutex> lock(mu);
+  for (int i = 0; i < n; ++i)
+    if (known[i].fn == fn) {
+      *out = known[i].bytes;
+      return NB_OK;
+    }
+  hipFuncAttributes at{};
+  NB_HIP(hipFuncGetAttributes(&at, fn));
+  *out = at.sharedSizeBytes;
+  if (n < 64) known[n++] = {fn, *out};
+  return NB_OK;
+}
+
 // Blocks of bs threads of kernel fn that a CU holds at once with dyn bytes of dynamic LDS.  A
 // CU's 160 KB of LDS are given to blocks in units of 1280 bytes, to which the runtime's
 // occupancy query does not round: three blocks of 53984 bytes (two flavours, 1070 energies)
@@ -793,10 +812,11 @@ static int upload_partition(nb_model* m) {
 // waits at its first barrier for blocks that cannot start.
 static constexpr int kLdsUnit = 1280, kLdsUnits = 160 * 1024 / kLdsUnit;
 static int blocks_per_cu(const void* fn, int bs, size_t dyn, int* per) {
-  hipFuncAttributes at{};
-  NB_HIP(hipFuncGetAttributes(&at, fn));
+  size_t own = 0;
+  const int rc = static_lds(fn, &own);
+  if (rc) return rc;
   NB_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(per, fn, bs, dyn));
-  const long long units = ((long long)(at.sharedSizeBytes + dyn) + kLdsUnit - 1) / kLdsUnit;
+  const long long units = (long long)((own + dyn + kLdsUnit - 1) / kLdsUnit);
   if (units > 0) *per = (int)std::min<long long>(*per, kLdsUnits / units);
   return NB_OK;
 }
