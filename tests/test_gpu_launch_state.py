@@ -157,3 +157,39 @@ def test_cancelled_launch_ends_at_its_start(nb):
     m.cancel(False)
     m.step(1)
     assert m.step_index() == 7
+
+
+@pytest.mark.parametrize("nf", [2, 3])
+def test_cancel_while_other_work_is_queued(nb, nf):
+    """A cancel between the call and the launch's start, behind the caller's own work on the
+    stream: the launch leaves state and step as they were."""
+    import threading
+
+    import torch
+    d = workloads.small_params(n_flavor=nf, n_energy=70, n_u=30, n_steps=60)
+    s = torch.cuda.Stream()
+    m = nb.Model(d, stream=s)
+    m.step(3)
+    before = _state(m)
+    got = []
+
+    def call():
+        try:
+            m.step(4)
+            got.append(None)
+        except nb.NubulbError as e:
+            got.append(e.code)
+
+    with torch.cuda.stream(s):
+        torch.cuda._sleep(200_000_000)      # about 0.1 s of spinning
+    t = threading.Thread(target=call)
+    t.start()
+    time.sleep(0.02)
+    m.cancel(True)
+    t.join()
+    assert got == [nb.NB_ETIMEOUT]
+    assert m.step_index() == 3
+    np.testing.assert_array_equal(_state(m), before)
+    m.cancel(False)
+    m.step(4)
+    np.testing.assert_array_equal(_state(m), _stepped(nb, d, 3, 4))
