@@ -193,7 +193,8 @@ int nb_cancel(nb_model *m, int32_t on);
  * moments are exact integer sums, so every shape gives the same bits.  Default (until
  * nb_autotune or nb_set_tuning): 256 threads per block for two flavours and for three-flavour
  * models of 9 rows to four rows per CU, 512 otherwise and where that lets more wavefronts run
- * (energy tables of which one block fits a CU, max_blocks), at the full resident grid. */
+ * (energy tables of which one block fits a CU; max_blocks with three flavours), at the full
+ * resident grid. */
 typedef struct {
   int32_t block_threads;  /* threads per block: 512 (8 wavefronts) or 256 (4) */
   int32_t blocks;         /* block cap of a launch (nb_set_tuning: 0 = the resident capacity);

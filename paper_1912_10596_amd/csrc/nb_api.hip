@@ -617,7 +617,7 @@ static int block_of_rows(long long rows, int cus) {
 }
 // 256 threads where preferred, unless a grid of 512-thread blocks gives more rows a wavefront of
 // their own: with large energy tables one block fits a CU's LDS at either size, and
-// p.max_blocks counts blocks (cap512, cap256: the most blocks of a launch; us per step at 256 and
+// max_blocks counts blocks (cap512, cap256: the most blocks of a launch; us per step at 256 and
 // 512 threads: 2000 x 1500 bins 243 and 204, every flavour tracked 1350 x 700 173 and 147, extended
 // 2200 x 200 x 8 331 and 235; three flavours 200 x 500 in 128 blocks 62 and 43).
 static int pick_block(bool prefer256, long long rows, int cap512, int cap256) {
@@ -945,9 +945,14 @@ extern "C" int nb_bind(nb_model* m, void* dev_ws, size_t bytes, void* hip_stream
   // Default shape: two flavours (single, batched or extended) at 256 threads per block
   // (three wavefronts per SIMD, and small models spread over twice as many CUs: 200k model
   // 23.4 against 25.0 us per step, 1024 beams 13.1 against 14.1); three flavours by their rows
-  // (block_of_rows); either at 512 where that holds more wavefronts (pick_block).
-  if (!m->tuned)
+  // (block_of_rows); either at 512 where that holds more wavefronts (pick_block), except two-flavour
+  // grids that max_blocks alone bounds: where rows are short or many wavefronts add to the same
+  // counters more of them cost more (one batched model of 57 x 218 bins in 40 blocks: 32.0 us per
+  // step at 256 threads, 38.3 at 512; extended 5 x 63 x 2 in 40 blocks 27.6 and 34.2).
+  if (!m->tuned) {
     m->bs = pick_block(m->nf == 2 || block_of_rows(m->rows, cus) == kBlockSmall, m->rows, cap[0], cap[1]);
+    if (m->nf == 2 && cap[1] >= 1 && (m->batch || cap[1] == m->p.max_blocks)) m->bs = kBlockSmall;
+  }
   if (capacity(m, m->bs) < 1) m->bs = kBlock;   // a tuned block size this device cannot hold
   if (m->tune_blocks > capacity(m, m->bs)) m->tune_blocks = 0;
   m->nblocks = launch_blocks(m);

@@ -41,13 +41,13 @@ def test_full_grids_are_resident(nb, name, kw):
     np.testing.assert_array_equal(got[0], got[256])
 
 
-# rows of their own wavefronts: grids bounded by LDS (one block per CU at either size) or by
-# max_blocks hold more at 512 threads; others keep 256
+# grids bounded by LDS (one block per CU at either size), and three-flavour grids bounded by
+# max_blocks, give more rows a wavefront of their own at 512 threads; others keep 256
 BLOCKS = [(dict(n_flavor=2, n_energy=1943, n_u=600), 256), (dict(n_flavor=2, n_energy=1944, n_u=512), 256),
           (dict(n_flavor=2, n_energy=1944, n_u=513), 512), (dict(n_flavor=2, n_energy=1350, n_u=300, track_all=1), 512),
           (dict(n_flavor=2, n_energy=1200, n_u=60, n_phi=9), 512),
           (dict(n_flavor=2, n_energy=20, n_u=40, max_blocks=20), 256),
-          (dict(n_flavor=2, n_energy=20, n_u=41, max_blocks=20), 512),
+          (dict(n_flavor=2, n_energy=20, n_u=41, max_blocks=20), 256),
           (dict(n_flavor=3, n_energy=20, n_u=40, max_blocks=20), 256),
           (dict(n_flavor=3, n_energy=20, n_u=41, max_blocks=20), 512),
           (dict(n_flavor=3, n_energy=20, n_u=512), 256), (dict(n_flavor=3, n_energy=20, n_u=513), 512)]
@@ -65,6 +65,12 @@ def test_default_block_size(nb, kw, bs):
     m.reset()
     m.run()
     np.testing.assert_array_equal(m.get_state().cpu().numpy(), want)
+
+
+def test_default_block_size_of_batches(nb):
+    """Batches keep 256 threads, also where max_blocks bounds the grid."""
+    ds = [workloads.small_params(n_flavor=2, n_energy=20, n_u=n, n_steps=2, max_blocks=4) for n in (9, 20)]
+    assert nb.Model(ds).get_tuning() == dict(nb.Model(ds).get_tuning(), block_threads=256, blocks=4)
 
 
 @pytest.mark.parametrize("kw", [dict(n_flavor=2, n_energy=1945, n_u=520), dict(n_flavor=2, n_energy=40, n_u=30, max_blocks=9),
