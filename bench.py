@@ -114,8 +114,9 @@ def timed_steps(m, K: int, W: int):
 
 
 def traffic_from_profile(name: str, launch_steps: int, nb: int):
-    """HBM bytes per launch from committed counter runs, scaled by the copy-kernel
-    calibration, or None if missing or taken on other kernel sources."""
+    """Bytes per launch that left L2 (for HBM or the last-level cache before it) from committed
+    counter runs, scaled by the copy-kernel calibration, or None if missing or taken on
+    other kernel sources."""
     path = os.path.join(ROOT, "profiles", f"traffic_{name}.json")
     if not os.path.exists(path):
         return None
@@ -490,7 +491,7 @@ def main():
     beam_steps = float(m.nb) * K
     value = beam_steps / wall
     ms_per_step = wall * 1e3 / K
-    # roofline of the dominant kernel (one cooperative launch for the K steps)
+    # roofline of the dominant kernel (one launch for the K steps)
     flops = FLOPS_PER_BEAM_STEP[3] * beam_steps
     alg_bytes = bytes_per_beam_step(3, False) * beam_steps
     tflops = flops / ev / 1e12
