@@ -1236,7 +1236,9 @@ extern "C" int nb_step_static(nb_model* m, int64_t n) {
   m->acc_static = s + kStaticAccOff;
   // the previous call on this device left its epochs (and maybe a status) in the array
   rc = zero_sync(m, 0, step_sync_words(m));
+  m->own_work = true;   // this clear also looks for a cancel
   if (!rc) rc = nb_step(m, n);
+  m->own_work = false;
   m->sync_static = nullptr;
   m->acc_static = nullptr;
   return rc;
