@@ -180,9 +180,10 @@ int nb_graph_capture(nb_model *m, int64_t n_steps);
 int nb_graph_launch(nb_model *m);
 
 /* Cancel: while on != 0, every persistent launch of the model (stepping, graph replays,
- * adaptive, adjoint) that starts returns at once without touching the state, and one that
- * is waiting in a grid barrier gives up within about a millisecond; both end in
- * NB_ETIMEOUT ("cancelled by the host").  on = 0 lets launches run again.  The flag is a
+ * adaptive, adjoint) that starts returns at once without touching the state (a stepping
+ * launch of a single model that the call enqueued before the cancel: by the end of its first
+ * stage), and one that is waiting in a grid barrier gives up within about a millisecond;
+ * both end in NB_ETIMEOUT ("cancelled by the host").  on = 0 lets launches run again.  The flag is a
  * word of fine-grained pinned host memory: this call may come from any host thread at any
  * time, including while another thread is inside nb_step or nb_graph_launch of the model.
  * Requires a bound model. */

@@ -166,8 +166,6 @@ struct nb_model {
   int adj_blocks = 0, adj_bpt = 0, adj_bs = kBlock;   // adj_bpt -1: spill mode
   long long* pinned = nullptr;       // [0] status (-1: not reported), [1] step, [8..12] adjoint gradients
   bool sync_dirty = false;           // the reduction words need a clear before a stepping launch
-  bool own_work = false;             // before the next launch the stream was idle but for a short kernel or
-                                     // copy of the library's own (nb_reset, the adjoint's checkpoints)
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
   long long graph_steps = 0;
@@ -727,7 +725,6 @@ extern "C" int nb_reset(nb_model* m) {
   long long per_species = m->batch ? m->nb : s0.NE * s0.NU * s0.NP;
   int nfl = m->batch ? 1 : s0.NS / 2;
   long long* ctl = (long long*)(m->ws + m->off_ctl);
-  m->own_work = !capturing(m->stream) && hipStreamQuery(m->stream) == hipSuccess;
   void* args[] = {&X, &nb_, &plane, &nsc, &per_species, &nfl, &ctl};
   int rc = launch_1d(state_fp32(m) ? (const void*)&k_init<float> : (const void*)&k_init<double>,
                      m->nb, args, m->stream);
@@ -1037,24 +1034,17 @@ static long long launch_chunk(const nb_model* m) {
 // cost 15-18 us more per call, and processes that had made cooperative launches crashed in
 // the runtime's exit handler under rocprofv3 (ordinary launches exit cleanly).
 //
-// Whether a launch enqueued now needs the clear kernel to look for a cancel at its start: the model
-// is cancelled already, or a caller's work on the stream comes first, during which it may be.
-static bool cancel_may_come_first(nb_model* m) {
-  const bool own = m->own_work;
-  m->own_work = false;
-  return __atomic_load_n(m->cancel, __ATOMIC_SEQ_CST) != 0u || (!own && hipStreamQuery(m->stream) != hipSuccess);
-}
-
 // Enqueue one stepping launch of k steps (from the device step counter) on the stream.  A
 // single model's launch that ends well clears the reduction words after itself, so only
 // batches, launches after an adaptive run, captured launches (whose predecessors' status the
-// library may not have seen) and launches that a cancel may precede have a clear before
-// them (4 us; the query of an idle stream 0.07 us).  report: the launch writes its status to the
-// pinned words.
+// library may not have seen) and launches of a cancelled model have a clear before them (4 us);
+// with the cancel word set it sets the abort word, and every block of the launch returns at its
+// start.  report: the launch writes its status to the pinned words.
 static int enqueue_advance(nb_model* m, long long k, bool report) {
   unsigned int* sync = sync_words(m);
   const bool cap = capturing(m->stream);
-  if (cap || m->batch || (m->sync_dirty && !m->sync_static) || cancel_may_come_first(m)) {
+  if (cap || m->batch || (m->sync_dirty && !m->sync_static) ||
+      __atomic_load_n(m->cancel, __ATOMIC_SEQ_CST) != 0u) {
     const int rc = zero_sync(m, 1, step_sync_words(m));
     if (rc) return rc;
     if (!m->sync_static && !cap) m->sync_dirty = false;
@@ -1236,9 +1226,7 @@ extern "C" int nb_step_static(nb_model* m, int64_t n) {
   m->acc_static = s + kStaticAccOff;
   // the previous call on this device left its epochs (and maybe a status) in the array
   rc = zero_sync(m, 0, step_sync_words(m));
-  m->own_work = true;   // this clear also looks for a cancel
   if (!rc) rc = nb_step(m, n);
-  m->own_work = false;
   m->sync_static = nullptr;
   m->acc_static = nullptr;
   return rc;
@@ -1845,8 +1833,6 @@ extern "C" int nb_adjoint(nb_model* m, const double* dev_dl_dpee, double* grad_o
   // forward pass: checkpoint at the start of every segment, every stage's moments recorded
   m->jhist = (double*)(m->ws + m->off_jhist);
   for (long long sg = 0; sg < nseg; ++sg) {
-    // a segment ends with the stream drained
-    m->own_work = sg > 0 || m->own_work || hipStreamQuery(m->stream) == hipSuccess;
     const hipError_t e = hipMemcpyAsync(ck + sg * pl3, m->ws + m->off_X, sizeof(double) * pl3,
                                         hipMemcpyDeviceToDevice, m->stream);
     if (e != hipSuccess) {

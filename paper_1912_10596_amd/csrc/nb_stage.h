@@ -53,14 +53,14 @@ __device__ __forceinline__ bool give_up(unsigned* sync, const unsigned* cancel, 
 // Read at the start of a persistent launch (all threads of the block call this; thread 0
 // reads, the block shares its answer): the abort word, set before the launch by the
 // sync-word clear when the host had cancelled the model (every block then returns at once,
-// leaving the state as it was), or during it by a block that gave up.  cancel (launches that
-// may start without such a clear, on a stream that was idle when the host found the model not
-// cancelled): block 0 also reads the host's cancel word; if it was set since, that block
-// sets the abort word and status bit 2 and returns, and the others find the abort word at
-// their first wait, before any state is stored.  (Every block reading the host's word costs
-// 0.1 us a block; a go word from block 0 for which the others wait, 2.5 us of a pass of one
-// step with the state set and read back, 76 us, and 1-2 % of small models' steps by the registers
-// that it takes.)
+// leaving the state as it was), or during it by a block that gave up.  cancel (launches
+// without such a clear: the host found the model not cancelled when it enqueued them): block 0
+// also reads the host's cancel word; if it was set since, that block sets the abort word and
+// status bit 2 and returns, and the others find the abort word at their first wait, before
+// any state is stored.  (Every block reading the host's word costs 0.1 us a block; a go word
+// from block 0 for which the others wait, 2.5 us of a pass of one step with the state set and
+// read back, 76 us, and 1-2 % of small models' steps by the registers that it takes; a clear where
+// the stream is not idle, 18 us for the query of a busy stream.)
 __device__ __forceinline__ bool launch_aborted(unsigned* sync, const unsigned* cancel = nullptr) {
   int ab = 0;
   if (threadIdx.x == 0) {
