@@ -787,7 +787,9 @@ __device__ __forceinline__ void group2(double* X, long long plane, long long gb0
 }
 
 // rt: the wavefront's row-constant table, kGroup2 blocks of kRowC doubles (extended model) or
-// kRowKeep of kRowP (bulb model, which keeps up to kRowKeep rows through a step).
+// kRowKeep of kRowP (bulb model, which keeps up to kRowKeep rows through a step; 17 KB of a
+// block of 256 threads, so that of energy tables of 1064-1215 energies two blocks fit a CU
+// where three would without it: the kept rows gain more, 1120 x 2000 bins 161 -> 135 us per step).
 constexpr int kGroup2 = 16;
 constexpr int row_table2(bool ext) { return ext ? kGroup2 * kRowC : kRowKeep * kRowP; }
 // Rows gw, gw + nw, ... of nrow.
